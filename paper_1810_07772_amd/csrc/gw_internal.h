@@ -163,13 +163,17 @@ hipError_t newton_step(const double2 *a, int n, const double2 *x, double2 *t, do
                        hipStream_t s);
 
 // Learned band-tail correction (tail.hip).
-size_t tail_ws_floats(int n);
+// Workspace floats for n rows and `parts` partial gradients of a training step: tail_parts_most(n) at best,
+// tail_parts_least(n) where the workspace may not grow, 0 for every other call.
+int tail_parts_most(int n);
+int tail_parts_least(int n);
+size_t tail_ws_floats(int n, int parts);
 hipError_t tail_features(const float2 *p, int ng, const int *miller, const double *q, double a_bohr, int nc,
                          double e_max, float *feat, hipStream_t s);
 hipError_t tail_target(const float2 *full, const float2 *trunc, int ng, float2 *t, hipStream_t s);
-hipError_t tail_forward(const gw_mlp &w, const float *feat, int n, float *ws, float *out, hipStream_t s);
+hipError_t tail_forward(const gw_mlp &w, const float *feat, int n, float *out, hipStream_t s);
 hipError_t tail_train_step(const gw_mlp &w, const gw_adam &a, const float *feat, const float2 *target, int n,
-                           float *ws, float *loss_out, int *step_dev, int set_step, hipStream_t s);
+                           float *ws, int parts, float *loss_out, int *step_dev, int set_step, hipStream_t s);
 void tail_graphs_release(gw_ctx *ctx);
 hipError_t tail_residual_parts(const gw_mlp &w, const float *feat, const float2 *target, int n, float *ws,
                                float *parts, hipStream_t s);

@@ -41,10 +41,27 @@ int tail_small(gw_ctx *ctx, char **p, hipStream_t s) {
 
 int tail_ws(gw_ctx *ctx, int n, float **ws, hipStream_t s) {
   void *p;
-  GWX_STATUS(api_ws_get(ctx, WS_TAIL, tail_ws_floats(n) * sizeof(float), &p, s));
+  GWX_STATUS(api_ws_get(ctx, WS_TAIL, tail_ws_floats(n, 0) * sizeof(float), &p, s));
   *ws = (float *)p;
   return GW_OK;
 }
+
+// Workspace of training steps on at most n rows; *most tells whether it holds tail_parts_most partial
+// gradients (for every count of rows up to n), else tail_parts_least: the smaller one is taken where the
+// larger does not fit under the cap or on the device.
+int tail_train_ws(gw_ctx *ctx, int n, float **ws, bool *most, hipStream_t s) {
+  void *p;
+  *most = true;
+  if (api_ws_get(ctx, WS_TAIL, tail_ws_floats(n, tail_parts_most(n)) * sizeof(float), &p, s) != GW_OK) {
+    ctx->err.clear();
+    *most = false;
+    GWX_STATUS(api_ws_get(ctx, WS_TAIL, tail_ws_floats(n, tail_parts_least(n)) * sizeof(float), &p, s));
+  }
+  *ws = (float *)p;
+  return GW_OK;
+}
+
+int tail_parts(bool most, int n) { return most ? tail_parts_most(n) : tail_parts_least(n); }
 
 // Cached training-step graphs: one per (model, optimiser, system, workspace) combination.
 struct TailGraphs {
@@ -64,13 +81,13 @@ uint64_t fbits(float f) {
 }
 
 int tail_step_graph(gw_ctx *ctx, const gw_mlp &w, const gw_adam &a, const float *feat, const float2 *target, int ng,
-                    float *ws, float *loss, int *step_dev, hipGraphExec_t *out) {
+                    float *ws, int parts, float *loss, int *step_dev, hipGraphExec_t *out) {
   TailGraphs *tg = tail_graphs(ctx);
   const std::vector<uint64_t> key = {(uint64_t)w.w, (uint64_t)w.b, (uint64_t)w.norm, (uint64_t)w.rank,
                                      (uint64_t)a.master, (uint64_t)a.m, (uint64_t)a.v, (uint64_t)a.grad,
                                      fbits(a.lr), fbits(a.beta1), fbits(a.beta2), fbits(a.eps),
                                      (uint64_t)feat, (uint64_t)target, (uint64_t)ng, (uint64_t)ws, (uint64_t)loss,
-                                     (uint64_t)step_dev};
+                                     (uint64_t)step_dev, (uint64_t)parts};
   auto it = tg->execs.find(key);
   if (it != tg->execs.end()) {
     *out = it->second;
@@ -78,7 +95,7 @@ int tail_step_graph(gw_ctx *ctx, const gw_mlp &w, const gw_adam &a, const float 
   }
   if (!tg->cs) GWX_HIP(ctx, hipStreamCreateWithFlags(&tg->cs, hipStreamNonBlocking));
   GWX_HIP(ctx, hipStreamBeginCapture(tg->cs, hipStreamCaptureModeThreadLocal));
-  const hipError_t ce = tail_train_step(w, a, feat, target, ng, ws, loss, step_dev, -1, tg->cs);
+  const hipError_t ce = tail_train_step(w, a, feat, target, ng, ws, parts, loss, step_dev, -1, tg->cs);
   hipGraph_t g = nullptr;
   const hipError_t ee = hipStreamEndCapture(tg->cs, &g);
   if (ce != hipSuccess || ee != hipSuccess) {
@@ -157,10 +174,7 @@ int gw_tail_forward(gw_ctx *ctx, const gw_mlp *w, const float *feat, int ng, flo
   GWX_CHECK(ctx, feat && out, "feat and out must not be NULL");
   GWX_CHECK(ctx, ng > 0 && ng <= 65536, "ng must be in [1, 65536]");
   if (ctx->device < 0) return GW_OK;
-  hipStream_t s = as_stream(stream);
-  float *ws;
-  GWX_STATUS(tail_ws(ctx, ng, &ws, s));
-  GWX_HIP(ctx, tail_forward(*w, feat, ng, ws, out, s));
+  GWX_HIP(ctx, tail_forward(*w, feat, ng, out, as_stream(stream)));
   return GW_OK;
 }
 
@@ -175,10 +189,11 @@ int gw_tail_train_step(gw_ctx *ctx, gw_mlp *w, gw_adam *opt, const float *feat, 
   hipStream_t s = as_stream(stream);
   float *ws;
   char *small;
-  GWX_STATUS(tail_ws(ctx, ng, &ws, s));
+  bool most;
+  GWX_STATUS(tail_train_ws(ctx, ng, &ws, &most, s));
   GWX_STATUS(tail_small(ctx, &small, s));
-  GWX_HIP(ctx, tail_train_step(*w, *opt, feat, (const float2 *)target, ng, ws, loss_out, (int *)(small + 64),
-                               opt->step + 1, s));
+  GWX_HIP(ctx, tail_train_step(*w, *opt, feat, (const float2 *)target, ng, ws, tail_parts(most, ng), loss_out,
+                               (int *)(small + 64), opt->step + 1, s));
   opt->step += 1;
   return GW_OK;
 }
@@ -271,15 +286,16 @@ int gw_tail_train_steps(gw_ctx *ctx, gw_mlp *w, gw_adam *opt, int nsys, const fl
   hipStream_t s = as_stream(stream);
   float *ws;
   char *small;
-  GWX_STATUS(tail_ws(ctx, ngmax, &ws, s));          // sized for every system before any capture
+  bool most;
+  GWX_STATUS(tail_train_ws(ctx, ngmax, &ws, &most, s));          // sized for every system before any capture
   GWX_STATUS(tail_small(ctx, &small, s));
   int *step_dev = (int *)(small + 64);
   GWX_HIP(ctx, launch_fill_int(step_dev, opt->step, s));
   for (int k = 0; k < nsteps; ++k) {
     const int j = order[k];
     hipGraphExec_t exec = nullptr;
-    GWX_STATUS(tail_step_graph(ctx, *w, *opt, feats[j], (const float2 *)targets[j], ngs[j], ws, loss_out + j, step_dev,
-                               &exec));
+    GWX_STATUS(tail_step_graph(ctx, *w, *opt, feats[j], (const float2 *)targets[j], ngs[j], ws,
+                               tail_parts(most, ngs[j]), loss_out + j, step_dev, &exec));
     GWX_HIP(ctx, hipGraphLaunch(exec, s));
   }
   opt->step += nsteps;

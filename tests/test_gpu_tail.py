@@ -236,3 +236,27 @@ def test_training_and_gain_on_larger_systems(gw):
         assert row["diag"][1] < 0.5 * row["diag"][0]
         assert row["offdiag"][1] <= row["offdiag"][0]
         assert row["eps_inv"][1] < 0.5 * row["eps_inv"][0]
+
+
+# A training step at the edges of its row blocks (16 rows), of the T U kernel's rows (4) and of its chunks of
+# 1024 columns, with more row blocks than workgroups (4200 rows), and under workspace caps that leave room
+# for one partial gradient (100 rows, 400 kB) or for none (40 rows, 150 kB).  Tolerance: FP32 sums of at most
+# 4200 terms in blocks of 16 with relative rounding 6e-8 each stay below 1e-5 of the gradient's norm.
+@pytest.mark.parametrize("n,rank,cap", [(1, 16, 0), (15, 16, 0), (16, 3, 0), (17, 16, 0), (1025, 16, 0), (4200, 2, 0),
+                                        (100, 16, 400_000), (40, 5, 150_000)])
+def test_train_step_row_blocks(gw, n, rank, cap):
+    x, norm, t = random_case(n, seed=n)
+    master = gs.mlp_init(3)
+    ctx = gw.Context(0, workspace_cap=cap) if cap else None
+    model = gw.TailModel(master, norm, rank=rank, ctx=ctx)
+    print(f"[case] n={n} rank={rank} cap={cap}", flush=True)
+    loss = float(model.train_step(dev(x), dev(t)).cpu().numpy()[0])
+    g = model.grad.cpu().numpy().astype(np.float64)
+    params = oracle_params(master)
+    o, cache = mo.forward(x.astype(np.float64), params, norm[:4].astype(np.float64), norm[4:8].astype(np.float64))
+    s, t64 = np.exp(x[:, 1].astype(np.float64)), t.astype(np.complex128)
+    assert abs(loss - mo.loss(o, s, t64, rank=rank)) < 1e-5 * abs(loss)
+    g_ref = mo.flatten(mo.backward(mo.loss_grad_o(o, s, t64, rank=rank), params, cache))
+    assert orc.rel_f(g, g_ref) < 1e-5
+    if cap:
+        assert ctx.workspace_bytes <= cap
