@@ -58,7 +58,7 @@ void set_err(gw_ctx *ctx, const char *fmt, ...) {
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
 // grow-only workspace slot
-int ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
+int ws_alloc(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
   if (bytes == 0) bytes = 256;
   bytes = (bytes + 255) & ~(size_t)255;
   if ((int)ctx->slots.size() <= slot) ctx->slots.resize(slot + 1);
@@ -88,6 +88,40 @@ int ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
   ctx->held += bytes;
   *out = p;
   return GW_OK;
+}
+
+// Frees the buffers that calls can do without (hipFree waits for the kernels that use them).
+bool ws_release_optional(gw_ctx *ctx) {
+  bool any = false;
+  for (int slot : kOptionalSlots) {
+    if ((int)ctx->slots.size() <= slot || !ctx->slots[slot].ptr) continue;
+    gw_ctx::Slot &sl = ctx->slots[slot];
+    if (hipFree(sl.ptr) != hipSuccess) (void)hipGetLastError();
+    ctx->held -= sl.bytes;
+    sl.ptr = nullptr;
+    sl.bytes = 0;
+    any = true;
+  }
+  return any;
+}
+
+// A buffer that the call needs: where it does not fit, the optional buffers make room for it.
+int ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
+  int st = ws_alloc(ctx, slot, bytes, out, s);
+  if (st == GW_E_NOMEM && ws_release_optional(ctx)) {
+    ctx->err.clear();
+    st = ws_alloc(ctx, slot, bytes, out, s);
+  }
+  return st;
+}
+
+// A buffer of kOptionalSlots, or NULL where it does not fit under the cap or on the device.  The next ws_get
+// may free it, so it is asked for right before the launches that use it.
+void *ws_try(gw_ctx *ctx, int slot, size_t bytes, hipStream_t s) {
+  void *p = nullptr;
+  if (ws_alloc(ctx, slot, bytes, &p, s) == GW_OK) return p;
+  ctx->err.clear();
+  return nullptr;
 }
 
 int begin(gw_ctx *ctx) {
@@ -426,7 +460,12 @@ int polarizability_r_impl(gw_ctx *ctx, const float2 *psi_v, int nv, const float2
   }
   int tile = o.tile;
   if (tile < 0) tile = tuned_tile(ctx, nr, nv, nc, o.precision);   // -1 when nothing is tuned: the default
-  GW_HIP(ctx, launch_herk(o.precision, tile, psi_v, psi_c, scale, scale_ld(nc), bexp, p_rr, nr, nv, nc, o.accumulate, s));
+  // a tile that the caller or the tuner chose runs as it is; the default one may share its last tiles
+  void *part = nullptr;
+  const size_t pbytes = tile < 0 ? herk_part_bytes(o.precision, nr, nv, nc) : 0;
+  if (pbytes) part = ws_try(ctx, WS_HERK_PART, pbytes, s);
+  GW_HIP(ctx, launch_herk(o.precision, tile, psi_v, psi_c, scale, scale_ld(nc), bexp, p_rr, nr, nv, nc, o.accumulate, s,
+                          part));
   return GW_OK;
 }
 
@@ -809,6 +848,7 @@ int gw_eps_inverse_newton(gw_ctx *ctx, const gw_c32 *p_gg, int ng, gw_grid grid,
 // Batched q (gw_batched.cpp) reuses the pieces above.
 namespace gwi {
 int api_ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) { return ws_get(ctx, slot, bytes, out, s); }
+void *api_ws_try(gw_ctx *ctx, int slot, size_t bytes, hipStream_t s) { return ws_try(ctx, slot, bytes, s); }
 int api_check_energies(gw_ctx *ctx, const double *e_v, int nv, const double *e_c, int nc) {
   return check_energies(ctx, e_v, nv, e_c, nc);
 }

@@ -63,8 +63,14 @@ enum SlotId {
   WS_ORB_A1,      // orbital transform intermediates
   WS_ORB_A2,
   WS_ORB_MAP,     // int maps of the orbital transform
+  WS_TAIL_PART,   // partial gradients of a training step (optional)
+  WS_HERK_PART,   // partial sums of shared update tiles (optional)
   WS_COUNT_BASE
 };
+
+// Slots that only make a call faster: api_ws_try fills them where they fit, and they are freed again when a
+// buffer that a call needs does not.
+constexpr int kOptionalSlots[] = {WS_TAIL_PART, WS_HERK_PART};
 
 // Kernel launchers.  All return hipSuccess or the launch error; all run on `s`.
 // Pair scales s_vc = sqrt(p / (E_c - E_v)) as float [nv][ldsc], zero for nc <= c < ldsc.
@@ -82,7 +88,11 @@ const char *herk_tile_name(int tile);
 bool herk_tile_supports(int tile, int precision);
 int herk_default_tile(int precision, int nr);
 hipError_t launch_herk(int precision, int tile, const float2 *psi_v, const float2 *psi_c, const float *scale, int ldsc,
-                       const int *band_exp, float2 *p, int nr, int nv, int nc, int accumulate, hipStream_t s);
+                       const int *band_exp, float2 *p, int nr, int nv, int nc, int accumulate, hipStream_t s,
+                       void *part = nullptr);
+// Bytes of `part`, with which launch_herk runs the precision's default tile (whatever `tile` says) and lets idle
+// CUs share the stages of its last tiles; 0 where that does not pay.
+size_t herk_part_bytes(int precision, int nr, int nv, int nc);
 hipError_t launch_band_exponents(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr,
                                  const float *scale, int ldsc, int *band_exp, hipStream_t s);
 // ints needed by launch_band_exponents' buffer (exponents, band order, sorted exponents, row maxima)
@@ -163,17 +173,18 @@ hipError_t newton_step(const double2 *a, int n, const double2 *x, double2 *t, do
                        hipStream_t s);
 
 // Learned band-tail correction (tail.hip).
-// Workspace floats for n rows and `parts` partial gradients of a training step: tail_parts_most(n) at best,
-// tail_parts_least(n) where the workspace may not grow, 0 for every other call.
+// Workspace floats for n rows, of which a training step's own partial gradients (tail_parts_least(n) of them)
+// only with train; tail_parts_most(n) partial gradients of tail_part_floats() each in an optional buffer.
 int tail_parts_most(int n);
 int tail_parts_least(int n);
-size_t tail_ws_floats(int n, int parts);
+size_t tail_part_floats();
+size_t tail_ws_floats(int n, bool train);
 hipError_t tail_features(const float2 *p, int ng, const int *miller, const double *q, double a_bohr, int nc,
                          double e_max, float *feat, hipStream_t s);
 hipError_t tail_target(const float2 *full, const float2 *trunc, int ng, float2 *t, hipStream_t s);
 hipError_t tail_forward(const gw_mlp &w, const float *feat, int n, float *out, hipStream_t s);
 hipError_t tail_train_step(const gw_mlp &w, const gw_adam &a, const float *feat, const float2 *target, int n,
-                           float *ws, int parts, float *loss_out, int *step_dev, int set_step, hipStream_t s);
+                           float *ws, float *parts, float *loss_out, int *step_dev, int set_step, hipStream_t s);
 void tail_graphs_release(gw_ctx *ctx);
 hipError_t tail_residual_parts(const gw_mlp &w, const float *feat, const float2 *target, int n, float *ws,
                                float *parts, hipStream_t s);
@@ -252,6 +263,7 @@ int upload_plan(gw_ctx *ctx, gw_grid g, const int *miller, int ng, int map_slot,
 
 // ---- shared host helpers of gw_api.cpp used by the batched path ---------------------------------
 int api_ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s);
+void *api_ws_try(gw_ctx *ctx, int slot, size_t bytes, hipStream_t s);
 int api_check_energies(gw_ctx *ctx, const double *e_v, int nv, const double *e_c, int nc);
 int api_check_sphere(gw_ctx *ctx, gw_grid g, const int *m, int ng);
 int api_check_opts(gw_ctx *ctx, const gw_opts *o);

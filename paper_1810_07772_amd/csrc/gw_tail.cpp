@@ -39,29 +39,18 @@ int tail_small(gw_ctx *ctx, char **p, hipStream_t s) {
   return GW_OK;
 }
 
-int tail_ws(gw_ctx *ctx, int n, float **ws, hipStream_t s) {
+int tail_ws(gw_ctx *ctx, int n, bool train, float **ws, hipStream_t s) {
   void *p;
-  GWX_STATUS(api_ws_get(ctx, WS_TAIL, tail_ws_floats(n, 0) * sizeof(float), &p, s));
+  GWX_STATUS(api_ws_get(ctx, WS_TAIL, tail_ws_floats(n, train) * sizeof(float), &p, s));
   *ws = (float *)p;
   return GW_OK;
 }
 
-// Workspace of training steps on at most n rows; *most tells whether it holds tail_parts_most partial
-// gradients (for every count of rows up to n), else tail_parts_least: the smaller one is taken where the
-// larger does not fit under the cap or on the device.
-int tail_train_ws(gw_ctx *ctx, int n, float **ws, bool *most, hipStream_t s) {
-  void *p;
-  *most = true;
-  if (api_ws_get(ctx, WS_TAIL, tail_ws_floats(n, tail_parts_most(n)) * sizeof(float), &p, s) != GW_OK) {
-    ctx->err.clear();
-    *most = false;
-    GWX_STATUS(api_ws_get(ctx, WS_TAIL, tail_ws_floats(n, tail_parts_least(n)) * sizeof(float), &p, s));
-  }
-  *ws = (float *)p;
-  return GW_OK;
+// Partial gradients of training steps on at most n rows (NULL: the steps use the fewer of their workspace).
+// Asked for after every buffer that the call needs.
+float *tail_parts(gw_ctx *ctx, int n, hipStream_t s) {
+  return (float *)api_ws_try(ctx, WS_TAIL_PART, (size_t)tail_parts_most(n) * tail_part_floats() * sizeof(float), s);
 }
-
-int tail_parts(bool most, int n) { return most ? tail_parts_most(n) : tail_parts_least(n); }
 
 // Cached training-step graphs: one per (model, optimiser, system, workspace) combination.
 struct TailGraphs {
@@ -81,7 +70,7 @@ uint64_t fbits(float f) {
 }
 
 int tail_step_graph(gw_ctx *ctx, const gw_mlp &w, const gw_adam &a, const float *feat, const float2 *target, int ng,
-                    float *ws, int parts, float *loss, int *step_dev, hipGraphExec_t *out) {
+                    float *ws, float *parts, float *loss, int *step_dev, hipGraphExec_t *out) {
   TailGraphs *tg = tail_graphs(ctx);
   const std::vector<uint64_t> key = {(uint64_t)w.w, (uint64_t)w.b, (uint64_t)w.norm, (uint64_t)w.rank,
                                      (uint64_t)a.master, (uint64_t)a.m, (uint64_t)a.v, (uint64_t)a.grad,
@@ -189,10 +178,9 @@ int gw_tail_train_step(gw_ctx *ctx, gw_mlp *w, gw_adam *opt, const float *feat, 
   hipStream_t s = as_stream(stream);
   float *ws;
   char *small;
-  bool most;
-  GWX_STATUS(tail_train_ws(ctx, ng, &ws, &most, s));
+  GWX_STATUS(tail_ws(ctx, ng, true, &ws, s));
   GWX_STATUS(tail_small(ctx, &small, s));
-  GWX_HIP(ctx, tail_train_step(*w, *opt, feat, (const float2 *)target, ng, ws, tail_parts(most, ng), loss_out,
+  GWX_HIP(ctx, tail_train_step(*w, *opt, feat, (const float2 *)target, ng, ws, tail_parts(ctx, ng, s), loss_out,
                                (int *)(small + 64), opt->step + 1, s));
   opt->step += 1;
   return GW_OK;
@@ -207,7 +195,7 @@ int gw_tail_loss(gw_ctx *ctx, const gw_mlp *w, const float *feat, const gw_c32 *
   if (ctx->device < 0) return GW_OK;
   hipStream_t s = as_stream(stream);
   float *ws;
-  GWX_STATUS(tail_ws(ctx, ng, &ws, s));
+  GWX_STATUS(tail_ws(ctx, ng, false, &ws, s));
   GWX_HIP(ctx, tail_loss(*w, feat, (const float2 *)target, ng, ws, loss_out, s));
   return GW_OK;
 }
@@ -230,7 +218,7 @@ int gw_tail_correct(gw_ctx *ctx, const gw_mlp *w, const gw_c32 *p_trunc, int ng,
     return GW_OK;
   }
   float *ws;
-  GWX_STATUS(tail_ws(ctx, ng, &ws, s));
+  GWX_STATUS(tail_ws(ctx, ng, false, &ws, s));
   GWX_HIP(ctx, tail_apply(*w, feat, (const float2 *)p_trunc, ng, ws, (float2 *)p_corr, s));
   GWX_HIP(ctx, hipStreamSynchronize(s));
   *used_fallback = 0;
@@ -246,7 +234,7 @@ int gw_tail_residual_parts(gw_ctx *ctx, const gw_mlp *w, const float *feat, cons
   if (ctx->device < 0) return GW_OK;
   hipStream_t s = as_stream(stream);
   float *ws;
-  GWX_STATUS(tail_ws(ctx, ng, &ws, s));
+  GWX_STATUS(tail_ws(ctx, ng, false, &ws, s));
   GWX_HIP(ctx, tail_residual_parts(*w, feat, (const float2 *)target, ng, ws, parts, s));
   return GW_OK;
 }
@@ -286,16 +274,16 @@ int gw_tail_train_steps(gw_ctx *ctx, gw_mlp *w, gw_adam *opt, int nsys, const fl
   hipStream_t s = as_stream(stream);
   float *ws;
   char *small;
-  bool most;
-  GWX_STATUS(tail_train_ws(ctx, ngmax, &ws, &most, s));          // sized for every system before any capture
+  GWX_STATUS(tail_ws(ctx, ngmax, true, &ws, s));          // sized for every system before any capture
   GWX_STATUS(tail_small(ctx, &small, s));
+  float *parts = tail_parts(ctx, ngmax, s);
   int *step_dev = (int *)(small + 64);
   GWX_HIP(ctx, launch_fill_int(step_dev, opt->step, s));
   for (int k = 0; k < nsteps; ++k) {
     const int j = order[k];
     hipGraphExec_t exec = nullptr;
     GWX_STATUS(tail_step_graph(ctx, *w, *opt, feats[j], (const float2 *)targets[j], ngs[j], ws,
-                               tail_parts(most, ngs[j]), loss_out + j, step_dev, &exec));
+                               parts, loss_out + j, step_dev, &exec));
     GWX_HIP(ctx, hipGraphLaunch(exec, s));
   }
   opt->step += nsteps;

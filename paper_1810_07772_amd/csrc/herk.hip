@@ -113,23 +113,60 @@ __device__ __forceinline__ void store_tile_after_folds(float2 *__restrict__ P, i
 }
 
 // ---------------------------------------------------------------------------------------------
+// Split K: where the tiles (or what is left of them after whole rounds of one per CU) would leave most CUs
+// idle, each tile's stages are cut into S parts, one workgroup each.  A part leaves its accumulators in `part`
+// and herk_part_sum_kernel adds a tile's parts in order and stores it, so the result does not depend on
+// timing.  Each quadrant of a part holds its registers as they lie in the lanes, 16 bytes per lane and store:
+// [rb][cb][re, im][e / 4][lane] of f32x4.  (One workgroup per CU running through an even share of all stages
+// balances better, but the loop around the kernel's body cost the wide kernel 161 spilled registers.)
+// ---------------------------------------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int QPART = 2 * 2 * 2 * 4 * 64;   // f32x4 per quadrant of a segment
+
+__device__ __forceinline__ void store_part(f32x4 *__restrict__ q, bool add, const f32x16 (&re)[2][2],
+                                           const f32x16 (&im)[2][2], int lane) {
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const f32x16 &a = c ? im[rb][cb] : re[rb][cb];
+          f32x4 v = {a[4 * e], a[4 * e + 1], a[4 * e + 2], a[4 * e + 3]};
+          f32x4 *d = q + (((rb * 2 + cb) * 2 + c) * 4 + e) * 64 + lane;
+          if (add) v += *d;
+          *d = v;
+        }
+}
+
+// ---------------------------------------------------------------------------------------------
 // FP32 variant
 // ---------------------------------------------------------------------------------------------
 constexpr int KC32 = 16;   // unoccupied bands per stage
 
-template <bool FOLD, bool COUTER>
+template <bool FOLD, bool COUTER, bool SPLIT>
 __global__ __launch_bounds__(NTHR, 1) void herk_fp32_kernel(const float2 *__restrict__ psi_v,
                                                              const float2 *__restrict__ psi_c,
                                                              const float *__restrict__ scale, int ldsc,
                                                              float2 *__restrict__ P, int nr, int nv, int nc,
-                                                             int ntiles, int accumulate) {
+                                                             int ntiles, int accumulate, int tile0,
+                                                             int parts, f32x4 *__restrict__ part) {
   // [buf][pair][component][point]; A: f on the tile's rows, B: f on its columns, Y: (im, -re) of B.
   __shared__ float sA[2][KC32][2][HB];
   __shared__ float sB[2][KC32][2][HB];
   __shared__ float sY[2][KC32][2][HB];
 
+  const int nchc = (nc + KC32 - 1) / KC32;
+  const int nch = nv * nchc;
+  // this workgroup's stages: tile tile0 + t, from ch0 to ch1 (all of its tile unless SPLIT)
+  const int w = xcd_remap(blockIdx.x, SPLIT ? ntiles * parts : ntiles);
+  const int t = SPLIT ? w / parts : w;
+  const int ch0 = SPLIT ? (int)((long long)nch * (w - t * parts) / parts) : 0;
+  const int ch1 = SPLIT ? (int)((long long)nch * (w - t * parts + 1) / parts) : nch;
   int bi, bj;
-  tile_of(xcd_remap(blockIdx.x, ntiles), bi, bj);
+  tile_of(tile0 + t, bi, bj);
   const int I0 = bi * HB, J0 = bj * HB;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wr = wave >> 1, wc = wave & 1;
@@ -138,9 +175,6 @@ __global__ __launch_bounds__(NTHR, 1) void herk_fp32_kernel(const float2 *__rest
   const int ri = I0 + 2 * cp, rj = J0 + 2 * cp;
   const bool oki0 = ri < nr, oki1 = ri + 1 < nr, okj0 = rj < nr, okj1 = rj + 1 < nr;
 
-  const int nchc = (nc + KC32 - 1) / KC32;
-  const int nch = nv * nchc;
-
   float2 vI[2], vJ[2];              // psi_v of the staged chunk
   float2 cI[4][2], cJ[4][2];        // psi_c of the staged chunk
   float sc[4];
@@ -148,7 +182,7 @@ __global__ __launch_bounds__(NTHR, 1) void herk_fp32_kernel(const float2 *__rest
   // Stage ch covers occupied band v and unoccupied bands c0 .. c0+KC32-1.  With COUTER the
   // unoccupied chunk is the outer index and v the inner one, so the psi_c chunk stays in
   // registers for nv consecutive stages and only psi_v (one value per point) is loaded per stage.
-  auto load_chunk = [&](int ch) {
+  auto load_chunk = [&](int ch, bool first) {
     const int v = COUTER ? ch % nv : ch / nchc;
     const int c0 = (COUTER ? ch / nv : ch % nchc) * KC32;
     const float2 z = make_float2(0.f, 0.f);
@@ -160,7 +194,7 @@ __global__ __launch_bounds__(NTHR, 1) void herk_fp32_kernel(const float2 *__rest
       const int c = c0 + prow + 4 * i;
       const bool okc = c < nc;
       sc[i] = okc ? scale[v * ldsc + c] : 0.f;
-      if (!COUTER || v == 0) {
+      if (!COUTER || v == 0 || first) {
         const float2 *pc = psi_c + (size_t)(okc ? c : 0) * nr;
         cI[i][0] = (okc && oki0) ? pc[ri] : z;  cI[i][1] = (okc && oki1) ? pc[ri + 1] : z;
         cJ[i][0] = (okc && okj0) ? pc[rj] : z;  cJ[i][1] = (okc && okj1) ? pc[rj + 1] : z;
@@ -197,12 +231,12 @@ __global__ __launch_bounds__(NTHR, 1) void herk_fp32_kernel(const float2 *__rest
   const int comp = lane >> 5, idx = lane & 31;
   const int ar0 = wr * 64 + idx, bc0 = wc * 64 + idx;
 
-  load_chunk(0);
+  load_chunk(ch0, true);
   produce(0);
   __syncthreads();
-  for (int ch = 0; ch < nch; ++ch) {
-    const int buf = ch & 1;
-    if (ch + 1 < nch) load_chunk(ch + 1);
+  for (int ch = ch0; ch < ch1; ++ch) {
+    const int buf = (ch - ch0) & 1;
+    if (ch + 1 < ch1) load_chunk(ch + 1, false);
 #pragma unroll 4
     for (int p = 0; p < KC32; ++p) {
       const float a0 = sA[buf][p][comp][ar0], a1 = sA[buf][p][comp][ar0 + 32];
@@ -230,10 +264,23 @@ __global__ __launch_bounds__(NTHR, 1) void herk_fp32_kernel(const float2 *__rest
           for (int e = 0; e < 16; ++e) { accR[a][b][e] = 0.f; accI[a][b][e] = 0.f; }
         }
     }
-    if (ch + 1 < nch) produce(buf ^ 1);
+    if (ch + 1 < ch1) produce(buf ^ 1);
     __syncthreads();
   }
-  if (FOLD) {
+  if (SPLIT && FOLD) {                       // a part may end inside a block of the K loop
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        runR[a][b] += accR[a][b];
+        runI[a][b] += accI[a][b];
+      }
+  }
+  if (SPLIT) {
+    f32x4 *q = part + ((size_t)w * 4 + wave) * QPART;
+    if (FOLD) store_part(q, false, runR, runI, lane);
+    else store_part(q, false, accR, accI, lane);
+  } else if (FOLD) {
     store_tile(P, nr, I0, J0, bi != bj, accumulate, runR, runI, wr, wc, lane);
   } else {
     store_tile(P, nr, I0, J0, bi != bj, accumulate, accR, accI, wr, wc, lane);
@@ -970,10 +1017,11 @@ constexpr int PW_RW = 36;   // 32-bit words per row point and buffer: 4 groups x
 constexpr int PW_CW = 20;   // per column point: 4 groups x [Re, Im] (4 words), 4 words of padding
 constexpr unsigned PW_SIGNS = 0x80008000u;   // the sign bits of both narrow halves of a word
 
-template <typename T, bool SCALED>
+template <typename T, bool SCALED, bool SPLIT>
 __global__ __launch_bounds__(3 * NTHR, 1) void herk_split_wide_planar_kernel(
     const float2 *__restrict__ psi_v, const float2 *__restrict__ psi_c, const float *__restrict__ scale, int ldsc,
-    const int *__restrict__ band_exp, float2 *__restrict__ P, int nr, int nv, int nc, int nblocks, int accumulate) {
+    const int *__restrict__ band_exp, float2 *__restrict__ P, int nr, int nv, int nc, int nblocks, int accumulate,
+    int tile0, int parts, f32x4 *__restrict__ part) {
   typedef typename SplitTraits<T>::vec vec;
   __shared__ __attribute__((aligned(16))) unsigned sRH[2][HB][PW_RW];
   __shared__ __attribute__((aligned(16))) unsigned sRL[2][HB][PW_RW];
@@ -982,14 +1030,20 @@ __global__ __launch_bounds__(3 * NTHR, 1) void herk_split_wide_planar_kernel(
   const int *order = SCALED ? band_exp + nv : nullptr, *esorted = SCALED ? band_exp + 2 * nv : nullptr;
   const int *bshift = SCALED ? band_exp + 4 * nv + nc : nullptr;
 
-  int bi, jp;
-  wide_block_of(xcd_remap(blockIdx.x, nblocks), bi, jp);
-  const int I0 = bi * HB, J0 = 2 * jp * HB;
-  const int ncb = (2 * jp + 1 <= bi) ? 2 : 1;          // column blocks of the pair on or below the diagonal
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nchc = (nc + WK - 1) / WK;
   const int nch = nv * nchc;
+
+  // this workgroup's stages: block tile0 + t, from ch0 to ch1 (all of its block unless SPLIT)
+  const int w = xcd_remap(blockIdx.x, SPLIT ? nblocks * parts : nblocks);
+  const int t = SPLIT ? w / parts : w;
+  const int ch0 = SPLIT ? (int)((long long)nch * (w - t * parts) / parts) : 0;
+  const int ch1 = SPLIT ? (int)((long long)nch * (w - t * parts + 1) / parts) : nch;
+  int bi, jp;
+  wide_block_of(tile0 + t, bi, jp);
+  const int I0 = bi * HB, J0 = 2 * jp * HB;
+  const int ncb = (2 * jp + 1 <= bi) ? 2 : 1;          // column blocks of the pair on or below the diagonal
 
   if (wave >= 8) {
     // ---- producers: row point rpt (pairs 8 rh .. 8 rh + 7 of each stage), column point cpt (all 16)
@@ -1067,23 +1121,23 @@ __global__ __launch_bounds__(3 * NTHR, 1) void herk_split_wide_planar_kernel(
     };
     // stage ch is (occupied band ch % nv, unoccupied chunk ch / nv); the indices of stages ch + 1 and
     // ch + 2 advance by counters
-    int v1 = 1 % nv, v2 = 2 % nv, c2 = 2 / nv;
-    load_c(rc, cc, 0);
-    load_v(0, 0);
+    int v1 = (ch0 + 1) % nv, v2 = (ch0 + 2) % nv, c2 = (ch0 + 2) / nv;
+    load_c(rc, cc, ch0 / nv);
+    load_v(ch0 % nv, (ch0 / nv) * WK);
     produce(0);
-    if (nch > 1) load_v(v1, (1 / nv) * WK);
-    if (nv == 1 && nch > 1) load_c(rcn, ccn, 1);
+    if (ch0 + 1 < ch1) load_v(v1, ((ch0 + 1) / nv) * WK);
+    if (v1 == 0 && ch0 + 1 < ch1) load_c(rcn, ccn, (ch0 + 1) / nv);
     __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) {
-      if (ch + 1 < nch) {
+    for (int ch = ch0; ch < ch1; ++ch) {
+      if (ch + 1 < ch1) {
         if (v1 == 0) {                                     // stage ch+1 opens the next unoccupied chunk
 #pragma unroll
           for (int k = 0; k < 8; ++k) rc[k] = rcn[k];
 #pragma unroll
           for (int k = 0; k < 16; ++k) cc[k] = ccn[k];
         }
-        produce((ch & 1) ^ 1);
-        if (ch + 2 < nch) {
+        produce(((ch - ch0) & 1) ^ 1);
+        if (ch + 2 < ch1) {
           load_v(v2, c2 * WK);
           if (v2 == 0) load_c(rcn, ccn, c2);
         }
@@ -1125,11 +1179,13 @@ __global__ __launch_bounds__(3 * NTHR, 1) void herk_split_wide_planar_kernel(
   const bool mirror_q = mcol != mrow;
   int nfold = 0;
   // one stage per call; the buffer index is a constant of each copy, so the LDS addresses are immediates
-  auto stage = [&](int ch, auto bufc) {
+  f32x4 *const q = SPLIT ? part + ((size_t)w * 8 + wave) * QPART : nullptr;
+  // stage ch0 + l
+  auto stage = [&](int l, auto bufc) {
     constexpr int buf = decltype(bufc)::value;
     if (active) {
-      if (SCALED && ch > 0 && (ch % FOLD_STAGES) != 0) {
-        const int vi = ch % nv;
+      if (SCALED && l > 0 && (l % FOLD_STAGES) != 0) {
+        const int vi = (ch0 + l) % nv;
         const int d = esorted[vi] - esorted[vi == 0 ? nv - 1 : vi - 1];
         if (d != 0) {
           const float f = ldexpf(1.0f, 2 * d);
@@ -1176,11 +1232,12 @@ __global__ __launch_bounds__(3 * NTHR, 1) void herk_split_wide_planar_kernel(
 #undef GW_PROD4
       }
       // FOLD_STAGES is even, so a fold follows only odd stages, which use buffer 1
-      if (buf == 1 && (ch + 1) % FOLD_STAGES == 0 && ch + 1 < nch) {
-        if (SCALED) unscale(esorted[ch % nv]);
+      if (buf == 1 && (l + 1) % FOLD_STAGES == 0 && ch0 + l + 1 < ch1) {
+        if (SCALED) unscale(esorted[(ch0 + l) % nv]);
         int lane_f = lane;
         asm volatile("" : "+v"(lane_f));
-        store_tile(P, nr, I0, J0, accumulate && mirror_q, accumulate || nfold > 0, accR, accI, wr, wc, lane_f);
+        if (SPLIT) store_part(q, nfold > 0, accR, accI, lane_f);
+        else store_tile(P, nr, I0, J0, accumulate && mirror_q, accumulate || nfold > 0, accR, accI, wr, wc, lane_f);
         ++nfold;
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -1194,16 +1251,72 @@ __global__ __launch_bounds__(3 * NTHR, 1) void herk_split_wide_planar_kernel(
   };
   static_assert(FOLD_STAGES % 2 == 0, "folds must follow odd stages");
   __syncthreads();
-  int ch = 0;
-  for (; ch + 1 < nch; ch += 2) {
-    stage(ch, std::integral_constant<int, 0>{});
-    stage(ch + 1, std::integral_constant<int, 1>{});
+  int l = 0;
+  for (; ch0 + l + 1 < ch1; l += 2) {
+    stage(l, std::integral_constant<int, 0>{});
+    stage(l + 1, std::integral_constant<int, 1>{});
   }
-  if (ch < nch) stage(ch, std::integral_constant<int, 0>{});
+  if (ch0 + l < ch1) stage(l, std::integral_constant<int, 0>{});
   if (!active) return;
-  if (SCALED) unscale(esorted[(nch - 1) % nv]);
-  if (nfold == 0 || accumulate) store_tile(P, nr, I0, J0, mirror_q, accumulate || nfold > 0, accR, accI, wr, wc, lane);
+  if (SCALED) unscale(esorted[(ch1 - 1) % nv]);
+  if (SPLIT) store_part(q, nfold > 0, accR, accI, lane);
+  else if (nfold == 0 || accumulate) store_tile(P, nr, I0, J0, mirror_q, accumulate || nfold > 0, accR, accI, wr, wc, lane);
   else store_tile_after_folds(P, nr, I0, J0, mirror_q, accR, accI, wr, wc, lane);
+}
+
+// Adds the parts of a split tile in the order of their stages and stores it (P = -sum, with accumulate
+// P += -sum) and its mirror: one wave per 32 x 32 block, 16-byte reads as the parts were written.  WIDE: 128 x 256 blocks (herk_split_wide_planar_kernel), else
+// 128 x 128 tiles.
+template <bool WIDE>
+__global__ __launch_bounds__(NTHR) void herk_part_sum_kernel(const f32x4 *__restrict__ part, int parts, int tile0,
+                                                             float2 *__restrict__ P, int nr,
+                                                             int accumulate) {
+  constexpr int NQ = WIDE ? 8 : 4;                      // quadrants; a workgroup takes one, a wave a 32 x 32 block
+  const int t = blockIdx.x / NQ, quad = blockIdx.x % NQ;
+  const int lane = threadIdx.x & 63, blk = threadIdx.x >> 6;
+  int bi, bj, wr, wc;
+  if (WIDE) {
+    int jp;
+    wide_block_of(tile0 + t, bi, jp);
+    wr = quad >> 2;
+    wc = quad & 3;
+    bj = 2 * jp + (wc >> 1);
+    wc &= 1;
+    if (bj > bi) return;                                // a column block above the diagonal
+  } else {
+    tile_of(tile0 + t, bi, bj);
+    wr = quad >> 1;
+    wc = quad & 1;
+  }
+  f32x4 acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+  for (int k = 0; k < parts; ++k) {
+    const f32x4 *src = part + (((size_t)t * parts + k) * NQ + quad) * QPART + blk * 8 * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] += src[i * 64];
+  }
+  const int row0 = bi * HB + wr * 64 + (blk >> 1) * 32 + 4 * (lane >> 5);
+  const int col = bj * HB + wc * 64 + (blk & 1) * 32 + (lane & 31);
+  if (col >= nr) return;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = row0 + 8 * e + i;
+      if (row < nr) {
+        float2 v = make_float2(-acc[e][i], -acc[4 + e][i]);
+        float2 *d = P + (size_t)row * nr + col;
+        if (accumulate) { const float2 o = *d; *d = make_float2(o.x + v.x, o.y + v.y); }
+        else *d = v;
+        if (bi != bj) {
+          float2 *m = P + (size_t)col * nr + row;
+          if (accumulate) { const float2 o = *m; *m = make_float2(o.x + v.x, o.y - v.y); }
+          else *m = make_float2(v.x, -v.y);
+        }
+      }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1365,22 +1478,109 @@ int herk_default_tile(int precision, int nr) {
   return -1;
 }
 
+// How the default tile of a precision runs on (nr, nv, nc): the first `whole` tiles one per workgroup, the other
+// `count` in S parts each (S = 1: none are cut).  All three default kernels hold one workgroup per CU, so tiles
+// run in rounds of one per CU, and what the last round leaves idle is what cutting can win.  The rule compares
+// that round as it is with `rounds` rounds of shorter parts, each of which stores its sums (tile_us), plus the
+// pass that adds them: its launch, its reads, and the chain of a tile's parts.  Measured, update alone (us,
+// uncut -> cut): FP32 12^3, 8 x 64 bands 170 -> 113 (105 tiles, S = 2); FP32 10^3, 20 x 100 669 -> 134 (36 tiles,
+// S = 7); BF16 16^3, 32 x 128 982 -> 678 (272 blocks, the last 16 with S = 16); BF16 18^3, 16 x 160 992 -> 832
+// (552 blocks, the last 40 with S = 6).  Cutting loses where a tile has few stages or the last round is nearly
+// full: BF16 15^3, 10 x 60 (196 blocks of 40 stages) 110 -> 140, FP32 24^3, 4 x 20 1214 -> 1249.  Over 15 shapes
+// and three precisions the rule's choice is within 7% of the best S.
+struct HerkPlan { int whole, count, S; };
+static HerkPlan herk_plan(int precision, int nr, int nv, int nc) {
+  constexpr int CUS = 256;
+  const int nb = (nr + HB - 1) / HB;
+  const bool wide = precision != GW_FP32;
+  const int tiles = wide ? wide_block_count(nb) : nb * (nb + 1) / 2;
+  const int nch = nv * ((nc + WK - 1) / WK);
+  static_assert(WK == KC32, "both kernels stage 16 pairs");
+  const int rem = tiles % CUS;
+  HerkPlan p{tiles, 0, 1};
+  if (rem == 0) return p;
+  const double stage_us = wide ? 1.55 : 5.3;             // one stage of a tile
+  const double tile_us = wide ? 12.0 : 6.0;              // every CU storing one part
+  double best = 0.95 * (nch * stage_us + tile_us);
+  for (int S = 2; S <= 32 && 2 * S <= nch; ++S) {
+    const int rounds = (rem * S + CUS - 1) / CUS;
+    const double sum_us = 6.0 + tile_us * rem * S / CUS + 1.5 * S;
+    const double cost = rounds * ((nch + S - 1) / S * stage_us + tile_us) + sum_us;
+    if (cost < best) {
+      best = cost;
+      p = HerkPlan{tiles - rem, rem, S};
+    }
+  }
+  return p;
+}
+
+size_t herk_part_bytes(int precision, int nr, int nv, int nc) {
+  const HerkPlan p = herk_plan(precision, nr, nv, nc);
+  return p.S > 1 ? (size_t)p.count * p.S * (precision == GW_FP32 ? 4 : 8) * QPART * sizeof(f32x4) : 0;
+}
+
+// The default tile with its last tiles shared (part: herk_part_bytes).
+static hipError_t launch_herk_shared(int precision, const float2 *psi_v, const float2 *psi_c, const float *scale,
+                                     int ldsc, const int *band_exp, float2 *p, int nr, int nv, int nc, int accumulate,
+                                     void *part, hipStream_t s) {
+  const HerkPlan pl = herk_plan(precision, nr, nv, nc);
+  f32x4 *pt = (f32x4 *)part;
+  if (precision == GW_SPLIT_FP16_SCALED && !band_exp) return hipErrorInvalidValue;
+#define GW_SHARED(PLAIN, SHARE, THREADS, ...)                                                                         \
+  do {                                                                                                                \
+    if (pl.whole)                                                                                                     \
+      hipLaunchKernelGGL(HIP_KERNEL_NAME(PLAIN), dim3(pl.whole), dim3(THREADS), 0, s, __VA_ARGS__, p, nr, nv, nc,     \
+                         pl.whole, accumulate, 0, 1, (f32x4 *)nullptr);                                               \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(SHARE), dim3(pl.count * pl.S), dim3(THREADS), 0, s, __VA_ARGS__, p, nr, nv,    \
+                       nc, pl.count, accumulate, pl.whole, pl.S, pt);                                                 \
+  } while (0)
+  switch (precision) {
+    case GW_FP32:
+      GW_SHARED((herk_fp32_kernel<true, true, false>), (herk_fp32_kernel<true, true, true>), NTHR, psi_v, psi_c, scale,
+                ldsc);
+      break;
+    case GW_SPLIT_BF16:
+      GW_SHARED((herk_split_wide_planar_kernel<__bf16, false, false>),
+                (herk_split_wide_planar_kernel<__bf16, false, true>), 3 * NTHR, psi_v, psi_c, scale, ldsc, band_exp);
+      break;
+    default:
+      GW_SHARED((herk_split_wide_planar_kernel<_Float16, true, false>),
+                (herk_split_wide_planar_kernel<_Float16, true, true>), 3 * NTHR, psi_v, psi_c, scale, ldsc, band_exp);
+  }
+#undef GW_SHARED
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (precision == GW_FP32)
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(herk_part_sum_kernel<false>), dim3(pl.count * 4), dim3(NTHR), 0, s, pt, pl.S,
+                       pl.whole, p, nr, accumulate);
+  else
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(herk_part_sum_kernel<true>), dim3(pl.count * 8), dim3(NTHR), 0, s, pt, pl.S,
+                       pl.whole, p, nr, accumulate);
+  return hipGetLastError();
+}
+
 hipError_t launch_herk(int precision, int tile, const float2 *psi_v, const float2 *psi_c, const float *scale, int ldsc,
-                       const int *band_exp, float2 *p, int nr, int nv, int nc, int accumulate, hipStream_t s) {
+                       const int *band_exp, float2 *p, int nr, int nv, int nc, int accumulate, hipStream_t s,
+                       void *part) {
+  if (part) return launch_herk_shared(precision, psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, accumulate, part, s);
   if (tile < 0) tile = herk_default_tile(precision, nr);
   const int nb = (nr + HB - 1) / HB;
   const int ntiles = nb * (nb + 1) / 2;
+  f32x4 *const none = nullptr;
   dim3 grid(ntiles), block(NTHR);
 #define GW_LAUNCH(KERNEL, ...) \
   hipLaunchKernelGGL(HIP_KERNEL_NAME(KERNEL), grid, block, 0, s, __VA_ARGS__)
   switch (tile) {
-    case 0: GW_LAUNCH((herk_fp32_kernel<true, false>), psi_v, psi_c, scale, ldsc, p, nr, nv, nc, ntiles, accumulate); break;
-    case 1: GW_LAUNCH((herk_fp32_kernel<false, false>), psi_v, psi_c, scale, ldsc, p, nr, nv, nc, ntiles, accumulate); break;
+    case 0: GW_LAUNCH((herk_fp32_kernel<true, false, false>), psi_v, psi_c, scale, ldsc, p, nr, nv, nc, ntiles, accumulate, 0, 1,
+                      none); break;
+    case 1: GW_LAUNCH((herk_fp32_kernel<false, false, false>), psi_v, psi_c, scale, ldsc, p, nr, nv, nc, ntiles, accumulate, 0, 1,
+                      none); break;
     case 2: GW_LAUNCH((herk_split_kernel<__bf16, false, false>), psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, ntiles,
                       accumulate); break;
     case 3: GW_LAUNCH((herk_split_kernel<_Float16, true, false>), psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, ntiles,
                       accumulate); break;
-    case 4: GW_LAUNCH((herk_fp32_kernel<true, true>), psi_v, psi_c, scale, ldsc, p, nr, nv, nc, ntiles, accumulate); break;
+    case 4: GW_LAUNCH((herk_fp32_kernel<true, true, false>), psi_v, psi_c, scale, ldsc, p, nr, nv, nc, ntiles, accumulate, 0, 1,
+                      none); break;
     case 5: GW_LAUNCH((herk_split_kernel<__bf16, false, true>), psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, ntiles,
                       accumulate); break;
 #define GW_WS(T_, KW_, PRIO_, SC_, NPW_)                                                                  \
@@ -1418,11 +1618,11 @@ hipError_t launch_herk(int precision, int tile, const float2 *psi_v, const float
       const int nw = wide_block_count(nb);
       if (tile == 16 && !band_exp) return hipErrorInvalidValue;
       if (tile == 15)
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(herk_split_wide_planar_kernel<__bf16, false>), dim3(nw), dim3(3 * NTHR), 0,
-                           s, psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, nw, accumulate);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(herk_split_wide_planar_kernel<__bf16, false, false>), dim3(nw), dim3(3 * NTHR),
+                           0, s, psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, nw, accumulate, 0, 1, none);
       else
-        hipLaunchKernelGGL(HIP_KERNEL_NAME(herk_split_wide_planar_kernel<_Float16, true>), dim3(nw), dim3(3 * NTHR), 0,
-                           s, psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, nw, accumulate);
+        hipLaunchKernelGGL(HIP_KERNEL_NAME(herk_split_wide_planar_kernel<_Float16, true, false>), dim3(nw), dim3(3 * NTHR),
+                           0, s, psi_v, psi_c, scale, ldsc, band_exp, p, nr, nv, nc, nw, accumulate, 0, 1, none);
       break;
     }
     default:

@@ -213,8 +213,7 @@ constexpr int TUR = 4;
 constexpr int TUC = 1024;        // g' per LDS chunk
 __global__ __launch_bounds__(256) void tail_tu_kernel(const float2 *__restrict__ t, const float2 *__restrict__ u,
                                                       int n, float2 *__restrict__ w, float *__restrict__ tpart,
-                                                      const float2 *__restrict__ gpart, int ngpart,
-                                                      float2 *__restrict__ gm) {
+                                                      const float2 *gpart, int ngpart, float2 *gm) {
   __shared__ float2 st[TUR][TUC];
   __shared__ float2 red[16][TUR][TR];
   __shared__ float rt[4];
@@ -709,18 +708,21 @@ __global__ void tail_stats_final_kernel(const double *__restrict__ acc, double t
 static int row_blocks(int n) { return (n + TRB - 1) / TRB; }
 static int tu_blocks(int n) { return (n + TUR - 1) / TUR; }
 
-// Partial gradients of a training step: one workgroup per block of rows up to one per CU.  Where the workspace
-// may not grow so far, a step runs with as many as fit into the room of two arrays of back-propagated rows
+// Partial gradients of a training step: one workgroup per block of rows up to one per CU.  Where there is no
+// room for so many, a step runs with as many as fit into the room of two arrays of back-propagated rows
 // (2 TW n floats); none: a single workgroup, whose part lives in the caller's gradient.
 constexpr int TAIL_WGS = 256;
 int tail_parts_most(int n) { return std::min(row_blocks(n), TAIL_WGS); }
-int tail_parts_least(int n) { return std::min(tail_parts_most(n), (int)(2LL * TW * n / TGP)); }
+int tail_parts_least(int n) { return std::min(tail_parts_most(n), std::max(0, (int)((2LL * TW * n - 1024) / TGP))); }
 
-size_t tail_ws_floats(int n, int parts) {
+size_t tail_part_floats() { return TGP; }
+
+size_t tail_ws_floats(int n, bool train) {
   // xn 4n, z1 h1 z2 h2 4*128n, o 33n, d n, u w 2*(32n), residual parts 4n, ||T||^2 parts, G parts and G,
   // loss parts, partial gradients
-  return (size_t)n * (4 + 4 * TW + TO + 1 + 4 * TR + 4) + tu_blocks(n) + 2 * TR * TR * ((size_t)row_blocks(n) + 1) +
-         TAIL_WGS + (size_t)parts * TGP;
+  return (size_t)n * (4 + 4 * TW + TO + 1 + 4 * TR + 4) + tu_blocks(n) +
+         2 * TR * TR * ((size_t)row_blocks(n) + (row_blocks(n) > 1 ? 1 : 0)) + tail_parts_most(n) +
+         (train ? (size_t)tail_parts_least(n) * TGP : 0);
 }
 
 struct TailWs {
@@ -728,7 +730,7 @@ struct TailWs {
   float2 *u, *w, *gm, *gpart;
 };
 
-static TailWs carve(float *base, int n, int parts) {
+static TailWs carve(float *base, int n) {
   TailWs t;
   float *p = base;
   t.z1 = p; p += (size_t)TW * n;
@@ -737,15 +739,15 @@ static TailWs carve(float *base, int n, int parts) {
   t.h2 = p; p += (size_t)TW * n;
   t.u = (float2 *)p; p += 2 * (size_t)TR * n;
   t.w = (float2 *)p; p += 2 * (size_t)TR * n;
-  t.gm = (float2 *)p; p += 2 * TR * TR;
+  t.gm = (float2 *)p; p += row_blocks(n) > 1 ? 2 * TR * TR : 0;   // a single part of G is G
   t.gpart = (float2 *)p; p += 2 * (size_t)TR * TR * row_blocks(n);
   t.xn = p; p += 4 * (size_t)n;
   t.part = p; p += 4 * (size_t)n;
-  t.gpar = p; p += (size_t)parts * TGP;
   t.o = p; p += (size_t)TO * n;
   t.d = p; p += n;
   t.tpart = p; p += tu_blocks(n);
-  t.lpart = p;
+  t.lpart = p; p += tail_parts_most(n);
+  t.gpar = p;
   return t;
 }
 
@@ -791,7 +793,7 @@ static hipError_t loss_pass(const gw_mlp &w, const float *feat, const float2 *ta
 
 hipError_t tail_loss(const gw_mlp &w, const float *feat, const float2 *target, int n, float *ws, float *loss_out,
                      hipStream_t s) {
-  const TailWs t = carve(ws, n, 0);
+  const TailWs t = carve(ws, n);
   const int wgs = tail_parts_most(n);
   hipError_t e = loss_pass(w, feat, target, n, t, wgs, nullptr, nullptr, 0, s);
   if (e != hipSuccess) return e;
@@ -799,13 +801,14 @@ hipError_t tail_loss(const gw_mlp &w, const float *feat, const float2 *target, i
   return hipGetLastError();
 }
 
-// One training step, four launches.  The Adam step count lives in step_dev: with set_step >= 0 the forward
+// One training step, four launches; the partial gradients go to `parts` (tail_parts_most(n) of them) or, where
+// that is NULL, to the fewer that the workspace holds.  The Adam step count lives in step_dev: with set_step >= 0 the forward
 // kernel writes it (eager calls), with set_step < 0 it advances it by one (the form a captured graph replays).
 hipError_t tail_train_step(const gw_mlp &w, const gw_adam &a, const float *feat, const float2 *target, int n,
-                           float *ws, int parts, float *loss_out, int *step_dev, int set_step, hipStream_t s) {
-  const TailWs t = carve(ws, n, parts);
-  const int wgs = std::max(1, parts);
-  float *gpar = parts > 0 ? t.gpar : a.grad;
+                           float *ws, float *parts, float *loss_out, int *step_dev, int set_step, hipStream_t s) {
+  const TailWs t = carve(ws, n);
+  const int least = tail_parts_least(n), wgs = parts ? tail_parts_most(n) : std::max(1, least);
+  float *gpar = parts ? parts : least > 0 ? t.gpar : a.grad;
   hipError_t e = loss_pass(w, feat, target, n, t, wgs, gpar, step_dev, set_step, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(tail_adam_kernel, dim3((GW_TAIL_NPARAM + TAP - 1) / TAP + 1), dim3(256), 0, s, a.master, a.m, a.v,
@@ -828,7 +831,7 @@ hipError_t tail_check_box(const float *feat, int n, const float *norm, int *flag
 
 hipError_t tail_apply(const gw_mlp &w, const float *feat, const float2 *p, int n, float *ws, float2 *out,
                       hipStream_t s) {
-  const TailWs t = carve(ws, n, 0);
+  const TailWs t = carve(ws, n);
   hipError_t e = forward(w, feat, n, &t, false, t.o, nullptr, 0, s);
   if (e != hipSuccess) return e;
   T_LAUNCH(tail_apply_kernel, (size_t)n * n, p, t.d, t.u, n, out);
@@ -837,7 +840,7 @@ hipError_t tail_apply(const gw_mlp &w, const float *feat, const float2 *p, int n
 
 hipError_t tail_residual_parts(const gw_mlp &w, const float *feat, const float2 *target, int n, float *ws,
                                float *parts, hipStream_t s) {
-  const TailWs t = carve(ws, n, 0);
+  const TailWs t = carve(ws, n);
   hipError_t e = forward(w, feat, n, &t, false, t.o, nullptr, 0, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(tail_parts_kernel, dim3(n), dim3(256), 0, s, t.d, t.u, target, n, t.part);
