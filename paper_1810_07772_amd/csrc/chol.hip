@@ -34,8 +34,7 @@ struct Zg2 {
 __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, const double2 *__restrict__ A, long long lda,
                                                     int transA, const double2 *__restrict__ B, long long ldb,
                                                     int transB, double2 *__restrict__ C, long long ldc, double alpha,
-                                                    double beta, int lower_only, int tri_k, int kchunk,
-                                                    long long cz_stride, Zg2 z2) {
+                                                    double beta, int lower_only, int tri_k, Zg2 z2) {
   // lower_only == 2: a square product over a one-dimensional grid of its lower tiles only, numbered row
   // by row (t = r (r + 1) / 2 + c), so consecutive workgroups, which the dispatcher deals out to the XCDs
   // in turn, carry equal work and no workgroup is launched for an upper tile
@@ -59,12 +58,7 @@ __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, cons
     row0 = blockIdx.y * GT;
     col0 = blockIdx.x * GT;
   }
-  // split K: workgroup z takes k in [z kchunk, (z+1) kchunk) and writes its own partial C
-  int kend = K;
-  if (kchunk > 0) {
-    C += blockIdx.z * cz_stride;
-    kend = min(K, (int)(blockIdx.z + 1) * kchunk);
-  }
+  const int kend = K;
   if (lower_only == 1 && col0 >= row0 + GT) return;
   // two LDS stages: the global loads of stage k+1 are in flight in registers while stage k's MFMAs run
   __shared__ double sA[2][GK][2][GT];
@@ -79,7 +73,7 @@ __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, cons
 #pragma unroll
       for (int e = 0; e < 4; ++e) { accR[a][b][e] = 0.0; accI[a][b][e] = 0.0; }
 
-  int kbeg = kchunk > 0 ? (int)blockIdx.z * kchunk : 0;
+  int kbeg = 0;
   if (tri_k) kbeg = (max(row0, col0) / GK) * GK;
   const int kl = lane >> 4, li = lane & 15;
   constexpr int PER = (GT * GK) / 256;   // elements of each operand per thread and stage
@@ -209,12 +203,12 @@ static hipError_t zgemm(int M, int N, int K, const double2 *A, long long lda, in
   if (lower_only && M == N) {
     const long long nt = (N + GT - 1) / GT;
     hipLaunchKernelGGL(zgemm_kernel, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, M, N, K, A, lda, transA, B,
-                       ldb, transB, C, ldc, alpha, beta, 2, tri_k, 0, 0LL, Zg2{});
+                       ldb, transB, C, ldc, alpha, beta, 2, tri_k, Zg2{});
     return hipGetLastError();
   }
   dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
   hipLaunchKernelGGL(zgemm_kernel, grid, dim3(256), 0, s, M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha,
-                     beta, lower_only, tri_k, 0, 0LL, Zg2{});
+                     beta, lower_only, tri_k, Zg2{});
   return hipGetLastError();
 }
 
@@ -226,55 +220,7 @@ static hipError_t zgemm_lower_and_full(int M, int N2, int K, const double2 *A, l
   if (M <= 0) return hipSuccess;
   const long long nt = (M + GT - 1) / GT, nt1 = nt * (nt + 1) / 2, nt2 = N2 > 0 ? nt * ((N2 + GT - 1) / GT) : 0;
   hipLaunchKernelGGL(zgemm_kernel, dim3((unsigned)(nt1 + nt2)), dim3(256), 0, s, M, M, K, A, lda, 0, B1, ldb, 1, C1,
-                     ldc, alpha, beta, 3, 0, 0, 0LL, Zg2{B2, C2, 0, N2, (int)nt1});
-  return hipGetLastError();
-}
-
-// c[i][j] = alpha sum_z w[z][i][j] + beta c[i][j]   (w packed [kz][M][N])
-__global__ void splitk_reduce_kernel(const double2 *__restrict__ w, int kz, int M, int N, double2 *__restrict__ c,
-                                     long long ldc, double alpha, double beta) {
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= (size_t)M * N) return;
-  const int i = (int)(idx / N), j = (int)(idx % N);
-  double re = 0.0, im = 0.0;
-  for (int z = 0; z < kz; ++z) {
-    const double2 v = w[(size_t)z * M * N + idx];
-    re += v.x;
-    im += v.y;
-  }
-  double2 *d = c + (long long)i * ldc + j;
-  double2 out = make_double2(alpha * re, alpha * im);
-  if (beta != 0.0) {
-    const double2 o = *d;
-    out.x += beta * o.x;
-    out.y += beta * o.y;
-  }
-  *d = out;
-}
-
-size_t zgemm_splitk_ws_elems(int M, int N, int K) {
-  const long long tiles = (long long)((M + GT - 1) / GT) * ((N + GT - 1) / GT);
-  if (tiles >= 256 || K < 4 * GK) return 0;
-  const int kz = (int)std::min<long long>(std::max<long long>(1, 512 / tiles), (K + 255) / 256);
-  return kz > 1 ? (size_t)kz * M * N : 0;
-}
-
-hipError_t launch_zgemm_splitk(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
-                               long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
-                               double2 *ws, size_t ws_elems, hipStream_t s) {
-  if (M <= 0 || N <= 0) return hipSuccess;
-  const size_t need = zgemm_splitk_ws_elems(M, N, K);
-  if (need == 0 || ws == nullptr || ws_elems < need)
-    return zgemm(M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, 0, 0, s);
-  const int kz = (int)(need / ((size_t)M * N));
-  int kchunk = (K + kz - 1) / kz;
-  kchunk = (kchunk + GK - 1) / GK * GK;
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, kz);
-  // each z slice writes every (i, j) of its partial (padded k past kend reads zero), so ws needs no clearing
-  hipLaunchKernelGGL(zgemm_kernel, grid, dim3(256), 0, s, M, N, K, A, lda, transA, B, ldb, transB, ws, (long long)N,
-                     1.0, 0.0, 0, 0, kchunk, (long long)M * N, Zg2{});
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(((size_t)M * N + 255) / 256)), dim3(256), 0, s, ws, kz, M,
-                     N, C, ldc, alpha, beta);
+                     ldc, alpha, beta, 3, 0, Zg2{B2, C2, 0, N2, (int)nt1});
   return hipGetLastError();
 }
 

@@ -549,15 +549,23 @@ int gw_create(gw_ctx **ctx, int hip_device, size_t cap) {
       return GW_E_HIP;
     }
     if (hipSetDevice(hip_device) != hipSuccess ||
-        hipHostMalloc((void **)&c->pivot_host, sizeof(int), hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void **)&c->pivot_host, 2 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
       delete c;
       return GW_E_HIP;
     }
     *c->pivot_host = 0;
+    c->result_host = reinterpret_cast<double *>(c->pivot_host) + 1;
+    if (hipEventCreateWithFlags(&c->result_event, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      (void)hipHostFree(c->pivot_host);
+      delete c;
+      return GW_E_HIP;
+    }
     // the allocation-free update's scratch array: this device's address, resolved with the device current
     if (gwi::noalloc_resolve(hip_device) != hipSuccess) {
       (void)hipGetLastError();
+      (void)hipEventDestroy(c->result_event);
       (void)hipHostFree(c->pivot_host);
       delete c;
       return GW_E_HIP;
@@ -576,6 +584,7 @@ int gw_destroy(gw_ctx *ctx) {
     gwi::tail_graphs_release(ctx);
     for (auto &sl : ctx->slots)
       if (sl.ptr) (void)hipFree(sl.ptr);
+    if (ctx->result_event) (void)hipEventDestroy(ctx->result_event);
     if (ctx->pivot_host) (void)hipHostFree(ctx->pivot_host);
   }
   delete ctx;

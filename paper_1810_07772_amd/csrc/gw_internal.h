@@ -25,6 +25,8 @@ struct gw_ctx {
   struct Slot { void *ptr = nullptr; size_t bytes = 0; };
   std::vector<Slot> slots;    // grow-only named workspace buffers
   int *pivot_host = nullptr;  // pinned host word for the Cholesky pivot flag
+  double *result_host = nullptr;       // pinned host word for an iteration's residual (same allocation)
+  hipEvent_t result_event = nullptr;   // recorded after the copy into it
   void *graph_cache = nullptr;  // batched-q graphs (owned; see gw_batched.cpp)
   void *tail_graphs = nullptr;  // training-step graphs of the learned tail (owned; see gw_tail.cpp)
   std::map<std::string, int> tuned;   // autotuned update tiles, keyed by arch and shape
@@ -130,13 +132,6 @@ hipError_t launch_fill_int(int *p, int value, hipStream_t s);
 hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
                         long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
                         hipStream_t s);
-// The same for thin outputs (fewer than 256 output tiles): K is split over workgroups into partial
-// products in ws (zgemm_splitk_ws_elems(M, N, K) complex128 elements; 0 means no split is used) and
-// summed by a second kernel.  Falls back to the plain product when ws is too small.
-size_t zgemm_splitk_ws_elems(int M, int N, int K);
-hipError_t launch_zgemm_splitk(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
-                               long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
-                               double2 *ws, size_t ws_elems, hipStream_t s);
 // Plasmon-pole kernels (pp.hip)
 hipError_t launch_density(const float2 *psi, int nv, int nr, double occ, double2 *rho, hipStream_t s);
 hipError_t launch_density_transform(double2 *rho, double2 *tmp, int n1, int n2, int n3, hipStream_t s);
@@ -144,13 +139,28 @@ hipError_t launch_screening(const double2 *ei, const double *sv, int ng, double2
 hipError_t launch_sum_rule(const int *miller, int ng, const double *q, double a_bohr, const double *sv,
                            const double2 *rho_g, int n1, int n2, int n3, double2 *m, hipStream_t s);
 hipError_t launch_start_block(double2 *x, int ng, int b, unsigned long long seed, hipStream_t s);
-hipError_t launch_herm_jacobi(const double2 *h, int b, int ldh, double *evals, double2 *z, int ldz, hipStream_t s);
-hipError_t launch_col_normalize(double2 *w, int rows, int ld, int cols, hipStream_t s);
-hipError_t launch_svqb_scale(double2 *u, const double *lam, int b, double rel, hipStream_t s);
-hipError_t launch_ritz_residual(const double2 *x, const double2 *y, int ng, int ld, const double *theta, int nm,
-                                double *out, hipStream_t s);
+// Blocks [ng][b] complex128, b <= 32.  Thin product: part = the K-splits of A B (thin_part_elems), summed by
+// launch_thin_sum; launch_block_gram leaves partial matrices of x^H y in gpart (gram_part_elems) for the eigensolver
+// and the Cholesky factorisation to add.
+size_t thin_part_elems(int M, int N, int K);
+size_t gram_part_elems(int ng, int b);
+size_t rotate_part_doubles(int ng, int b);
+hipError_t launch_thin_product(int M, int N, int K, const double2 *A, long long lda, const double2 *B, int ldb,
+                               double2 *part, hipStream_t s);
+hipError_t launch_thin_sum(const double2 *part, int M, int N, int K, double alpha, double2 *y, hipStream_t s);
+hipError_t launch_block_gram(const double2 *x, const double2 *y, int ng, int b, double2 *gpart, hipStream_t s);
+hipError_t launch_herm_jacobi(const double2 *gpart, int ng, int b, double *evals, double2 *z, hipStream_t s);
+hipError_t launch_block_chol(const double2 *gpart, int ng, int b, double2 *u, hipStream_t s);
+hipError_t launch_block_rotate(const double2 *x, const double2 *z, int ng, int b, double2 *w, hipStream_t s);
+// w = x z, t = y z and out = max over the first nm columns of ||t_j - theta_j w_j|| / theta_0
+hipError_t launch_block_ritz(const double2 *x, const double2 *y, const double2 *z, int ng, int b, const double *theta,
+                             int nm, double2 *w, double2 *t, double *rpart, double *out, hipStream_t s);
 hipError_t launch_pp_frequency(const double2 *a, int lda, const double2 *t, int ldt, int ng, const double *theta,
                                int nm, double *sigma, double *omega, hipStream_t s);
+// One pass of the pole form where pp_pole_fits(nm); else weights, the product and the division follow.
+bool pp_pole_fits(int nm);
+hipError_t launch_pp_pole(const double2 *modes, int ng, int nm, const double *sigma, const double *omega, double w,
+                          const double *sv, const double2 *ei_static, double2 *e, hipStream_t s);
 hipError_t launch_pp_weight(const double2 *modes, int ng, int nm, const double *sigma, const double *omega, double w,
                             double2 *out, hipStream_t s);
 hipError_t launch_pp_finish(double2 *e, const double2 *ei_static, const double *sv, int ng, hipStream_t s);

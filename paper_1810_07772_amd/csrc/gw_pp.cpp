@@ -1,13 +1,13 @@
 // C ABI of the plasmon-pole model (the paper's section on the dynamic inverse dielectric matrix):
 // the few most negative eigenpairs of S = sqrt(V)(eps^-1 - I)sqrt(V) by block subspace iteration
 // with a Rayleigh-Ritz step per iteration, their frequencies from the Johnson sum rule, and the
-// pole-form eps^-1(w).  Kernels in pp.hip; the large products on the FP64 MFMA GEMM.
+// pole-form eps^-1(w).  Kernels in pp.hip; the pole form's product on the FP64 MFMA GEMM.
 //
 // Iteration (all on the device, one host read of the residual per iteration):
-//   Y = -S X;  H = X^H Y;  H = Z diag(theta) Z^H (Jacobi, descending);  X <- X Z, Y <- Y Z
-//   stop when max_{a < n_modes} ||Y_a - theta_a X_a|| <= tol * theta_0
-//   X <- orthonormal basis of Y (columns to unit length, then X = Y U diag(lambda)^-1/2 from the
-//        eigenpairs of Y^H Y: the SVQB orthonormalisation of Stathopoulos and Wu, 2002)
+//   Y = -S X;  H = X^H Y;  H = Z diag(theta) Z^H (Jacobi, descending);  W = X Z, T = Y Z
+//   stop when max_{a < n_modes} ||T_a - theta_a W_a|| <= tol * theta_0
+//   X <- T u, u from the Cholesky factor of T^H T: an orthonormal basis of T
+// The next X is formed while the host waits for the residual.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -24,14 +24,12 @@ constexpr int kBlock = 32;      // subspace size (the Jacobi kernel's limit)
 constexpr int kMaxModes = 24;   // at least 8 guard vectors beyond the wanted modes
 
 enum {
-  PP_MILLER = 40, PP_SQRTV, PP_RHO, PP_RHO_T, PP_S, PP_M, PP_X, PP_Y, PP_W, PP_T, PP_SMALL, PP_B, PP_SPLITK
+  PP_MILLER = 40, PP_SQRTV, PP_RHO, PP_RHO_T, PP_S, PP_M, PP_X, PP_Y, PP_W, PP_T, PP_SMALL, PP_B
 };
 
-struct Small {            // b x b matrices and eigenvalues of the iteration
-  double2 *h, *z, *g, *u;
-  double *theta, *lam, *res;
-  double2 *ws;             // split-K partial products of the thin products
-  size_t ws_elems;
+struct Small {            // b x b matrices, eigenvalues and partial sums of the iteration
+  double2 *z, *u, *gpart;
+  double *theta, *res, *rpart;
 };
 
 int upload_sphere(gw_ctx *ctx, const int *miller, int ng, const double *q, double a_bohr, int **dm, double **dsv,
@@ -46,13 +44,11 @@ int upload_sphere(gw_ctx *ctx, const int *miller, int ng, const double *q, doubl
   return GW_OK;
 }
 
-// x = orthonormal basis of the columns of w (w is overwritten by its column-normalised copy)
+// x = orthonormal basis of the columns of w
 int orthonormalize(gw_ctx *ctx, double2 *w, int ng, int b, const Small &sm, double2 *x, hipStream_t s) {
-  GWX_HIP(ctx, launch_col_normalize(w, ng, b, b, s));
-  GWX_HIP(ctx, launch_zgemm_splitk(b, b, ng, w, b, 1, w, b, 0, sm.g, b, 1.0, 0.0, sm.ws, sm.ws_elems, s));
-  GWX_HIP(ctx, launch_herm_jacobi(sm.g, b, b, sm.lam, sm.u, b, s));
-  GWX_HIP(ctx, launch_svqb_scale(sm.u, sm.lam, b, 1e-14, s));
-  GWX_HIP(ctx, launch_zgemm(ng, b, b, w, b, 0, sm.u, b, 0, x, b, 1.0, 0.0, s));
+  GWX_HIP(ctx, launch_block_gram(w, w, ng, b, sm.gpart, s));
+  GWX_HIP(ctx, launch_block_chol(sm.gpart, ng, b, sm.u, s));
+  GWX_HIP(ctx, launch_block_rotate(w, sm.u, ng, b, x, s));
   return GW_OK;
 }
 
@@ -90,12 +86,16 @@ int gw_plasmon_pole(gw_ctx *ctx, const gw_c64 *eps_inv, int ng, gw_grid grid, co
   GWX_STATUS(api_ws_get(ctx, PP_RHO, (size_t)nr * sizeof(double2), &rho, s));
   GWX_STATUS(api_ws_get(ctx, PP_RHO_T, (size_t)nr * sizeof(double2), &rho_t, s));
   GWX_STATUS(api_ws_get(ctx, PP_S, (size_t)ng * ng * sizeof(double2), &sp, s));
-  GWX_STATUS(api_ws_get(ctx, PP_M, (size_t)ng * ng * sizeof(double2), &mp, s));
+  // M's buffer, filled after the iteration, holds the iteration's partial sums until then; the last product's
+  // are left in S's
+  const size_t tp_el = thin_part_elems(ng, b, ng), gp_el = gram_part_elems(ng, b);
+  GWX_STATUS(api_ws_get(ctx, PP_M, std::max((size_t)ng * ng * sizeof(double2), (tp_el + gp_el) * sizeof(double2) +
+                                                                      rotate_part_doubles(ng, b) * sizeof(double)),
+                        &mp, s));
   GWX_HIP(ctx, launch_density((const float2 *)psi_v, nv, nr, occupation, (double2 *)rho, s));
   GWX_HIP(ctx, launch_density_transform((double2 *)rho, (double2 *)rho_t, grid.n1, grid.n2, grid.n3, s));
   double2 *S = (double2 *)sp, *M = (double2 *)mp;
   GWX_HIP(ctx, launch_screening((const double2 *)eps_inv, sv, ng, S, s));
-  GWX_HIP(ctx, launch_sum_rule(dm, ng, q, grid.a_bohr, sv, (const double2 *)rho_t, grid.n1, grid.n2, grid.n3, M, s));
   // block buffers
   void *xp, *yp, *wp, *tp, *smp;
   const size_t blk = (size_t)ng * b * sizeof(double2);
@@ -104,45 +104,40 @@ int gw_plasmon_pole(gw_ctx *ctx, const gw_c64 *eps_inv, int ng, gw_grid grid, co
   GWX_STATUS(api_ws_get(ctx, PP_W, blk, &wp, s));
   GWX_STATUS(api_ws_get(ctx, PP_T, blk, &tp, s));
   const size_t bb = (size_t)b * b;
-  GWX_STATUS(api_ws_get(ctx, PP_SMALL, 4 * bb * sizeof(double2) + (3 * b + 8) * sizeof(double), &smp, s));
+  GWX_STATUS(api_ws_get(ctx, PP_SMALL, 2 * bb * sizeof(double2) + (b + 8) * sizeof(double), &smp, s));
   Small sm;
-  sm.h = (double2 *)smp;
-  sm.z = sm.h + bb;
-  sm.g = sm.z + bb;
-  sm.u = sm.g + bb;
+  sm.z = (double2 *)smp;
+  sm.u = sm.z + bb;
   sm.theta = (double *)(sm.u + bb);
-  sm.lam = sm.theta + b;
-  sm.res = sm.lam + b;
-  sm.ws_elems = std::max({zgemm_splitk_ws_elems(ng, b, ng), zgemm_splitk_ws_elems(b, b, ng),
-                          zgemm_splitk_ws_elems(ng, n_modes, ng)});
-  sm.ws = nullptr;
-  if (sm.ws_elems) {
-    void *w;
-    GWX_STATUS(api_ws_get(ctx, PP_SPLITK, sm.ws_elems * sizeof(double2), &w, s));
-    sm.ws = (double2 *)w;
-  }
+  sm.res = sm.theta + b;
+  double2 *part = M;
+  sm.gpart = part + tp_el;
+  sm.rpart = (double *)(sm.gpart + gp_el);
   double2 *X = (double2 *)xp, *Y = (double2 *)yp, *W = (double2 *)wp, *T = (double2 *)tp;
   GWX_HIP(ctx, launch_start_block(T, ng, b, 0x5eedULL, s));
   GWX_STATUS(orthonormalize(ctx, T, ng, b, sm, X, s));
   double res = INFINITY;
   int it = 0;
   for (it = 1; it <= max_iter; ++it) {
-    GWX_HIP(ctx, launch_zgemm_splitk(ng, b, ng, S, ng, 0, X, b, 0, Y, b, -1.0, 0.0, sm.ws, sm.ws_elems, s));  // -S X
-    GWX_HIP(ctx, launch_zgemm_splitk(b, b, ng, X, b, 1, Y, b, 0, sm.h, b, 1.0, 0.0, sm.ws, sm.ws_elems, s));  // X^H Y
-    GWX_HIP(ctx, launch_herm_jacobi(sm.h, b, b, sm.theta, sm.z, b, s));
-    GWX_HIP(ctx, launch_zgemm(ng, b, b, X, b, 0, sm.z, b, 0, W, b, 1.0, 0.0, s));   // Ritz vectors
-    GWX_HIP(ctx, launch_zgemm(ng, b, b, Y, b, 0, sm.z, b, 0, T, b, 1.0, 0.0, s));   // -S times them
-    GWX_HIP(ctx, launch_ritz_residual(W, T, ng, b, sm.theta, n_modes, sm.res, s));
-    GWX_HIP(ctx, hipMemcpyAsync(&res, sm.res, sizeof(double), hipMemcpyDeviceToHost, s));
-    GWX_HIP(ctx, hipStreamSynchronize(s));
+    GWX_HIP(ctx, launch_thin_product(ng, b, ng, S, ng, X, b, part, s));
+    GWX_HIP(ctx, launch_thin_sum(part, ng, b, ng, -1.0, Y, s));                      // Y = -S X
+    GWX_HIP(ctx, launch_block_gram(X, Y, ng, b, sm.gpart, s));                       // X^H Y
+    GWX_HIP(ctx, launch_herm_jacobi(sm.gpart, ng, b, sm.theta, sm.z, s));
+    GWX_HIP(ctx, launch_block_ritz(X, Y, sm.z, ng, b, sm.theta, n_modes, W, T, sm.rpart, sm.res, s));
+    GWX_HIP(ctx, hipMemcpyAsync(ctx->result_host, sm.res, sizeof(double), hipMemcpyDeviceToHost, s));
+    GWX_HIP(ctx, hipEventRecord(ctx->result_event, s));
+    if (it < max_iter && b < ng) GWX_STATUS(orthonormalize(ctx, T, ng, b, sm, X, s));
+    GWX_HIP(ctx, hipEventSynchronize(ctx->result_event));
+    res = *ctx->result_host;
     if (!std::isfinite(res)) break;
     if (res <= tol || b == ng) break;      // converged (a full-space block is exact after one step)
-    GWX_STATUS(orthonormalize(ctx, T, ng, b, sm, X, s));
   }
   *iterations = std::min(it, max_iter);
   if (residual) *residual = res;
   // frequencies from the sum rule: t = M A, omega_a^2 = Re(a^H t_a) / theta_a
-  GWX_HIP(ctx, launch_zgemm_splitk(ng, n_modes, ng, M, ng, 0, W, b, 0, Y, n_modes, 1.0, 0.0, sm.ws, sm.ws_elems, s));
+  GWX_HIP(ctx, launch_sum_rule(dm, ng, q, grid.a_bohr, sv, (const double2 *)rho_t, grid.n1, grid.n2, grid.n3, M, s));
+  GWX_HIP(ctx, launch_thin_product(ng, n_modes, ng, M, ng, W, b, S, s));
+  GWX_HIP(ctx, launch_thin_sum(S, ng, n_modes, ng, 1.0, Y, s));
   GWX_HIP(ctx, launch_pp_frequency(W, b, Y, n_modes, ng, sm.theta, n_modes, sigma, omega, s));
   GWX_HIP(ctx, hipMemcpy2DAsync(modes, (size_t)n_modes * sizeof(double2), W, (size_t)b * sizeof(double2),
                                 (size_t)n_modes * sizeof(double2), ng, hipMemcpyDeviceToDevice, s));
@@ -177,6 +172,12 @@ int gw_pp_eps_inverse(gw_ctx *ctx, const gw_c64 *eps_inv_static, int ng, gw_grid
   int *dm;
   double *sv;
   GWX_STATUS(upload_sphere(ctx, g_miller, ng, q, grid.a_bohr, &dm, &sv, s));
+  if (pp_pole_fits(n_modes)) {
+    for (int f = 0; f < nf; ++f)
+      GWX_HIP(ctx, launch_pp_pole((const double2 *)modes, ng, n_modes, sigma, omega, freqs[f], sv,
+                                  (const double2 *)eps_inv_static, (double2 *)out + (size_t)f * ng * ng, s));
+    return GW_OK;
+  }
   void *bp;
   GWX_STATUS(api_ws_get(ctx, PP_B, (size_t)ng * n_modes * sizeof(double2), &bp, s));
   for (int f = 0; f < nf; ++f) {

@@ -3,9 +3,11 @@
 //   S = A diag(sigma) A^H                       Eq.(eigdecomp), the few most negative sigma
 //   omega_a^2 = (A^H M A)_aa / |sigma_a|,  M(g,g') = V V' [(q+g).(q+g')] rho_{g-g'}   Eq.(ppfreq)
 //   S(w) = sum_a A_a sigma_a omega_a^2 / (omega_a^2 - w^2) A_a^H                  Eq.(ppform)
-// Kernels for the density and its transform, S and M, the small dense eigenproblems of the
-// block iteration (one-workgroup Jacobi), and the pole-form evaluation.  Large products use
-// the complex FP64 MFMA GEMM.
+// Kernels for the density and its transform, S and M, the products, small dense eigenproblems and
+// orthonormalisation of the block iteration, and the pole-form evaluation (its large product is the complex
+// FP64 MFMA GEMM).
+#include <algorithm>
+
 #include "gw_internal.h"
 
 namespace gwi {
@@ -91,13 +93,233 @@ __global__ void start_block_kernel(double2 *__restrict__ x, int ng, int b, unsig
   x[idx] = make_double2(2.0 * (double)(u >> 11) * s - 1.0, 2.0 * (double)(w >> 11) * s - 1.0);
 }
 
+// ---- the block iteration's products: blocks are [ng][b] complex128 row-major, b <= 32 -----------------------
+constexpr int JMAX = 32;         // largest block
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// part[z] = A B over k in split z, A [M][K] (read once, from memory) and B [K][N], N <= 32 (from cache).
+// 64 rows per workgroup, 16 complex k per stage, so a workgroup has 16 KB of A in flight in registers while the
+// FP64 MFMAs of the stage before run (k' = (k, re/im) as in zgemm_kernel: Re C += [Re A, Im A] . [Re B; -Im B],
+// Im C += [Re A, Im A] . [Im B; Re B]); wave w owns rows 16 w .. +15 and all 32 columns.  Bound by memory and the
+// matrix cores alike (16 bytes and 256 flop per entry of A).  The 64 x 64 tiles of zgemm_kernel, half of whose
+// columns are padding here, took 103 us for 3071 x 3071 by 32 columns; 59 us.
+constexpr int TPM = 64, TPK = 16;
+__global__ __launch_bounds__(256) void thin_product_kernel(int M, int N, int K, const double2 *__restrict__ A,
+                                                           long long lda, const double2 *__restrict__ B, int ldb,
+                                                           double2 *__restrict__ part, int kchunk) {
+  constexpr int LA = TPM + 1, LB = JMAX + 1;      // odd strides: the transposing LDS writes spread over the banks
+  __shared__ double sA[2][TPK][2][LA];
+  __shared__ double sB[2][TPK][2][LB];            // [Re B; -Im B]
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kl = lane >> 4, li = lane & 15;
+  const int row0 = blockIdx.x * TPM, k_beg = blockIdx.y * kchunk, k_end = min(K, k_beg + kchunk);
+  double2 va[4], vb[2];
+  const int ar = tid / TPK, ak = tid % TPK;       // A: rows ar + 16 i, offset ak
+  const int bc = tid % JMAX, bk = tid / JMAX;     // B: k offsets bk + 8 i, column bc
+  auto gload = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = row0 + ar + 16 * i, k = k0 + ak;
+      const bool in = r < M && k < k_end;
+      va[i] = A[(long long)min(r, M - 1) * lda + min(k, K - 1)];
+      if (!in) va[i] = make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int k = k0 + bk + 8 * i;
+      const bool in = bc < N && k < k_end;
+      vb[i] = B[(long long)min(k, K - 1) * ldb + min(bc, N - 1)];
+      if (!in) vb[i] = make_double2(0.0, 0.0);
+    }
+  };
+  auto lstore = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sA[buf][ak][0][ar + 16 * i] = va[i].x;
+      sA[buf][ak][1][ar + 16 * i] = va[i].y;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      sB[buf][bk + 8 * i][0][bc] = vb[i].x;
+      sB[buf][bk + 8 * i][1][bc] = -vb[i].y;
+    }
+  };
+  f64x4 accR[2], accI[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { accR[c][e] = 0.0; accI[c][e] = 0.0; }
+  const int comp = kl & 1;
+  const unsigned long long flip = comp ? 0ull : 0x8000000000000000ull;   // [Im B; Re B] = [-X_1; X_0]
+  int buf = 0;
+  if (k_beg < k_end) {
+    gload(k_beg);
+    lstore(0);
+  }
+  __syncthreads();
+  for (int k0 = k_beg; k0 < k_end; k0 += TPK) {
+    const bool more = k0 + TPK < k_end;
+    if (more) gload(k0 + TPK);
+#pragma unroll
+    for (int s = 0; s < TPK / 2; ++s) {
+      const int kk = 2 * s + (kl >> 1);
+      const double av = sA[buf][kk][comp][16 * wave + li];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const double xv = sB[buf][kk][comp][16 * c + li], ys = sB[buf][kk][comp ^ 1][16 * c + li];
+        const double yv = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, ys) ^ flip);
+        accR[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, xv, accR[c], 0, 0, 0);
+        accI[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, yv, accI[c], 0, 0, 0);
+      }
+    }
+    if (more) lstore(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+  double2 *out = part + (size_t)blockIdx.y * M * N;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = row0 + 16 * wave + 4 * e + kl, col = 16 * c + li;
+      if (row < M && col < N) out[(size_t)row * N + col] = make_double2(accR[c][e], accI[c][e]);
+    }
+}
+
+// Splits of K: three workgroups per CU (their LDS fits; at 3071 rows 58.6 us against 67.9 with two and 77.6 with one and
+// a half), at least four stages each.
+static int thin_splits(int M, int K) {
+  const int tiles = (M + TPM - 1) / TPM;
+  return std::max(1, std::min(768 / tiles, K / (4 * TPK)));
+}
+size_t thin_part_elems(int M, int N, int K) { return (size_t)thin_splits(M, K) * M * N; }
+
+// The share of X^H Y of the rows [blockIdx.x chunk, +chunk) into gpart[block].  Thread (i, j0) of 32 x 8 forms the
+// entries (i, j0 + 8 q); 16 rows at a time in LDS.
+constexpr int GRAM_ROWS = 16;
+constexpr int GRAM_BLOCKS = 64;  // partial Gram matrices that their consumer, one workgroup, adds
+__global__ __launch_bounds__(256) void block_gram_kernel(const double2 *__restrict__ x, const double2 *__restrict__ y,
+                                                         int ng, int b, int chunk, double2 *__restrict__ gpart) {
+  __shared__ double2 sx[GRAM_ROWS][JMAX + 1], sy[GRAM_ROWS][JMAX + 1];
+  const int tid = threadIdx.x, i = tid % JMAX, j0 = tid / JMAX;
+  const int r_beg = blockIdx.x * chunk, r_end = min(ng, r_beg + chunk);
+  double2 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = make_double2(0.0, 0.0);
+  for (int r0 = r_beg; r0 < r_end; r0 += GRAM_ROWS) {
+    if (r0 != r_beg) __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int rr = j0 + 8 * h, r = r0 + rr;
+      double2 xv = make_double2(0.0, 0.0), yv = xv;
+      if (r < r_end && i < b) {
+        const size_t at = (size_t)r * b + i;
+        xv = x[at];
+        yv = y[at];
+      }
+      sx[rr][i] = xv;
+      sy[rr][i] = yv;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int rr = 0; rr < GRAM_ROWS; ++rr) {
+      const double2 u = sx[rr][i];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double2 v = sy[rr][j0 + 8 * q];        // conj(u) v
+        acc[q].x += u.x * v.x + u.y * v.y;
+        acc[q].y += u.x * v.y - u.y * v.x;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (i < b && j0 + 8 * q < b) gpart[(size_t)blockIdx.x * b * b + i * b + j0 + 8 * q] = acc[q];
+}
+
+static int gram_chunk(int ng) {
+  const int c = std::max(3 * GRAM_ROWS, (ng + GRAM_BLOCKS - 1) / GRAM_BLOCKS);
+  return (c + GRAM_ROWS - 1) / GRAM_ROWS * GRAM_ROWS;
+}
+static int gram_blocks(int ng) { return (ng + gram_chunk(ng) - 1) / gram_chunk(ng); }
+size_t gram_part_elems(int ng, int b) { return (size_t)gram_blocks(ng) * b * b; }
+
+// Entries tid, tid + THREADS, ... (i JMAX + j each) of the sum of the partial Gram matrices, in block order, into
+// g; entries outside b x b are zero.  32 loads are in flight per thread: one workgroup reads all parts, and
+// eight at a time cost it 20 us of the factorisation's 29 us for 48 parts.
+template <int THREADS>
+__device__ __forceinline__ void gram_sum(const double2 *__restrict__ gpart, int nblk, int b,
+                                         double2 (*__restrict__ g)[JMAX + 1]) {
+  constexpr int NE = JMAX * JMAX / THREADS, U = 32 / NE;
+  double2 a[NE];
+  const double2 *src[NE];
+  bool in[NE];
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int idx = threadIdx.x + e * THREADS, i = idx / JMAX, j = idx % JMAX;
+    in[e] = i < b && j < b;
+    src[e] = gpart + (in[e] ? i * b + j : 0);
+    a[e] = make_double2(0.0, 0.0);
+  }
+  const size_t bb = (size_t)b * b;
+  int q = 0;
+  for (; q + U <= nblk; q += U) {
+    double2 v[NE][U];
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int k = 0; k < U; ++k) v[e][k] = src[e][(q + k) * bb];
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        a[e].x += v[e][k].x;
+        a[e].y += v[e][k].y;
+      }
+  }
+  for (; q < nblk; ++q)
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const double2 v = src[e][q * bb];
+      a[e].x += v.x;
+      a[e].y += v.y;
+    }
+#pragma unroll
+  for (int e = 0; e < NE; ++e) {
+    const int idx = threadIdx.x + e * THREADS;
+    g[idx / JMAX][idx % JMAX] = in[e] ? a[e] : make_double2(0.0, 0.0);
+  }
+}
+
 // ---- Hermitian Jacobi eigensolver for b <= 32, one workgroup ------------------------------------
 // Cyclic two-sided Jacobi with the round-robin (circle) ordering: each round rotates m/2 disjoint
-// index pairs at once.  For a pair (p, q) with a_pq = |a_pq| e^{i phi}, the rotation is
-// J = diag(1, e^{-i phi}) R, R the real symmetric Schur rotation of [[a_pp, |a_pq|], [|a_pq|, a_qq]];
-// A <- J^H A J, V <- V J.  Eigenvalues are returned in descending order with their vectors as
-// columns of z (row-major, leading dimension ldz).
-constexpr int JMAX = 32;
+// index pairs at once.  For a pair (p, q) the rotation is J = [[c, s], [-conj(s), c]] with complex s:
+// with d = (a_qq - a_pp) / 2 and r = sqrt(d^2 + |a_pq|^2), c = sqrt((1 + |d| / r) / 2) and
+// s = sign(d) a_pq / (2 r c), two reciprocal square roots in all; A <- J^H A J, V <- V J.
+// A round's time is its serial chain, so it has one barrier: thread (k, l) of the first four waves computes
+// the rotation of pair l from A, takes that of pair k from the lane that holds it (its own row of 16 lanes
+// has all 16 pairs), and applies both sides to the 2 x 2 block (pair k, pair l) in registers, from one
+// copy of A in LDS to the other.  The other four waves apply the previous round's rotations to V meanwhile.
+// (With the rotations passed through LDS and one barrier each for them, the columns and the rows, a round took
+// 2.4 us; about 0.6 us.)  At 3071 G and 16 modes the solves of the iteration went from 522 us
+// each (two per iteration) to 102 us (one).  The matrix is the Hermitian part of the sum of nblk partial ones, [b][b] each.
+// Eigenvalues are returned in descending order with their vectors as columns of z (row-major, leading dimension b).
+
+// 1 / x and 1 / sqrt(x), x > 0 normal: the hardware estimate refined by two Newton steps
+__device__ __forceinline__ double rcp_nr(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) r = fma(r, fma(-x, r, 1.0), r);
+  return r;
+}
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const double e = fma(-x * r, r, 1.0);
+    r = fma(0.5 * r, e, r);
+  }
+  return r;
+}
 
 // Sum of v over the 64 lanes of a wave.
 __device__ __forceinline__ double wave_sum(double v) {
@@ -106,179 +328,347 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-__global__ __launch_bounds__(256) void herm_jacobi_kernel(const double2 *__restrict__ h, int b, int ldh,
+// Pair t of a round over m indices (m even): (round + t, round - t) modulo m - 1, with m - 1 in place of the
+// second for t = 0; the next round's pair is one step on.
+struct JacobiPair {
+  int p, q, n;
+  bool fixed;
+  __device__ __forceinline__ JacobiPair(int t, int m) : p(t), q(t == 0 ? m - 1 : m - 1 - t), n(m - 1), fixed(t == 0) {}
+  __device__ __forceinline__ void step() {
+    p = p + 1 == n ? 0 : p + 1;
+    if (!fixed) q = q + 1 == n ? 0 : q + 1;
+  }
+};
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+
+__global__ __launch_bounds__(512) void herm_jacobi_kernel(const double2 *__restrict__ gpart, int nblk, int b,
                                                           double *__restrict__ evals, double2 *__restrict__ z,
-                                                          int ldz, int max_sweeps) {
-  __shared__ double2 A[JMAX][JMAX + 1];
+                                                          int max_sweeps) {
+  __shared__ double2 A[2][JMAX][JMAX + 1];
   __shared__ double2 V[JMAX][JMAX + 1];
-  __shared__ double rc[JMAX / 2], rs[JMAX / 2];
-  __shared__ double2 rph[JMAX / 2];
-  __shared__ int rp[JMAX / 2], rq[JMAX / 2];
-  __shared__ double red_off[4], red_all[4];
+  __shared__ double rc[2][JMAX / 2];
+  __shared__ double2 rs[2][JMAX / 2];
+  __shared__ double red_off[8], red_all[8];
   __shared__ int perm[JMAX];
-  __shared__ int stop;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = (b + 1) & ~1;          // even size; a padding index has a zero row and column
-  for (int idx = tid; idx < JMAX * JMAX; idx += 256) {
+  const int half = m / 2;
+  gram_sum<512>(gpart, nblk, b, A[1]);
+  for (int idx = tid; idx < JMAX * JMAX; idx += 512) {
     const int i = idx / JMAX, j = idx % JMAX;
-    double2 v = make_double2(0.0, 0.0);
-    if (i < b && j < b) {
-      const double2 a = h[(size_t)i * ldh + j], c = h[(size_t)j * ldh + i];
-      v = make_double2(0.5 * (a.x + c.x), 0.5 * (a.y - c.y));     // Hermitian part
-    }
-    A[i][j] = v;
     V[i][j] = make_double2(i == j ? 1.0 : 0.0, 0.0);
   }
   __syncthreads();
-  const int half = m / 2;
+  for (int idx = tid; idx < JMAX * JMAX; idx += 512) {
+    const int i = idx / JMAX, j = idx % JMAX;
+    const double2 a = A[1][i][j], c = A[1][j][i];
+    A[0][i][j] = make_double2(0.5 * (a.x + c.x), 0.5 * (a.y - c.y));     // Hermitian part
+  }
+  __syncthreads();
+  int cur = 0, done = 0;               // A's current copy; rounds done
+  const int l = lane & 15;             // this lane's pair of columns, and of rows (first four waves) k
+  const int k = (wave & 3) * 4 + (lane >> 4), i0 = (wave & 3) * 8 + (lane >> 4) * 2;
+  JacobiPair cols(l < half ? l : 0, m), rows(k < half ? k : 0, m);
+  auto rotate_v = [&](int par) {       // by waves 4 to 7: the last round's rotations on rows i0, i0 + 1
+    if (l >= half) return;
+    const int p = cols.p, q = cols.q;
+    const double c = rc[par][l];
+    const double2 s = rs[par][l];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double2 x = V[i0 + h][p], y = V[i0 + h][q];
+      // x' = c x - conj(s) y,  y' = s x + c y
+      V[i0 + h][p] = make_double2(c * x.x - (s.x * y.x + s.y * y.y), c * x.y - (s.x * y.y - s.y * y.x));
+      V[i0 + h][q] = make_double2(c * y.x + (s.x * x.x - s.y * x.y), c * y.y + (s.x * x.y + s.y * x.x));
+    }
+  };
   for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-    // convergence: off-diagonal mass against the whole
+    // convergence: off-diagonal mass against the whole (norm below 1e-15 relative)
     double off = 0.0, all = 0.0;
-    for (int idx = tid; idx < m * m; idx += 256) {
+    for (int idx = tid; idx < m * m; idx += 512) {
       const int i = idx / m, j = idx % m;
-      const double2 v = A[i][j];
+      const double2 v = A[cur][i][j];
       const double s2 = v.x * v.x + v.y * v.y;
       all += s2;
       if (i != j) off += s2;
     }
-    // wave sums, then the four waves' partials
     off = wave_sum(off);
     all = wave_sum(all);
     if (lane == 0) { red_off[wave] = off; red_all[wave] = all; }
     __syncthreads();
-    if (tid == 0) {
-      const double o = red_off[0] + red_off[1] + red_off[2] + red_off[3];
-      const double a = red_all[0] + red_all[1] + red_all[2] + red_all[3];
-      stop = (o <= 1e-30 * a) || a == 0.0;   // off-diagonal norm below 1e-15 relative
-    }
-    __syncthreads();
-    if (stop) break;
+    double o = 0.0, a = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) { o += red_off[w]; a += red_all[w]; }
+    if (o <= 1e-30 * a || a == 0.0) break;       // the same in every thread
     for (int round = 0; round < m - 1; ++round) {
-      if (tid < half) {
-        int p, q;
-        if (tid == 0) { p = round; q = m - 1; }
-        else { p = (round + tid) % (m - 1); q = (round - tid + (m - 1)) % (m - 1); }
-        if (p > q) { const int t = p; p = q; q = t; }
-        // one reciprocal square root gives the phase and tau; c = 1/sqrt(1 + t^2) is another (three
-        // long-latency operations in this serial chain instead of seven)
-        const double2 apq = A[p][q];
-        const double mag2 = apq.x * apq.x + apq.y * apq.y;
-        double c = 1.0, s = 0.0;
-        double2 ph = make_double2(1.0, 0.0);
-        if (mag2 > 0.0) {
-          const double inv_mag = rsqrt(mag2);
-          ph = make_double2(apq.x * inv_mag, apq.y * inv_mag);
-          const double tau = (A[q][q].x - A[p][p].x) * (0.5 * inv_mag);
-          const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-          c = rsqrt(1.0 + t * t);
-          s = t * c;
+      if (wave < 4) {
+        const int pl = cols.p, ql = cols.q, pk = rows.p, qk = rows.q;
+        cols.step();
+        rows.step();
+        const double2(*Ac)[JMAX + 1] = A[cur];
+        const double app = Ac[pl][pl].x, aqq = Ac[ql][ql].x;
+        const double2 apq = Ac[pl][ql];
+        double2 x00 = Ac[pk][pl], x01 = Ac[pk][ql], x10 = Ac[qk][pl], x11 = Ac[qk][ql];
+        const double dd = 0.5 * (aqq - app);
+        const double r2 = fma(dd, dd, fma(apq.x, apq.x, apq.y * apq.y));
+        double c = 1.0;
+        double2 s = make_double2(0.0, 0.0);
+        if (r2 > 1e-290) {                        // below it the block is diagonal to any relative accuracy
+          const double ir = rsqrt_nr(r2);
+          const double c2 = fma(0.5 * fabs(dd), ir, 0.5);
+          const double ic = rsqrt_nr(c2);
+          c = c2 * ic;
+          const double f = copysign(0.5 * ir * ic, dd);
+          s = make_double2(f * apq.x, f * apq.y);
         }
-        rp[tid] = p; rq[tid] = q; rc[tid] = c; rs[tid] = s; rph[tid] = ph;
+        const int src = (lane & 48) | (k & 15);
+        const double ck = __shfl(c, src, 64);
+        const double2 sk = make_double2(__shfl(s.x, src, 64), __shfl(s.y, src, 64));
+        if (lane < 16 && wave == 0 && l < half) { rc[done & 1][l] = c; rs[done & 1][l] = s; }
+        if (k < half && l < half) {
+          // columns: x_i0' = c x_i0 - conj(s) x_i1,  x_i1' = s x_i0 + c x_i1 (pair l), then rows with the
+          // conjugates: x_0j' = ck x_0j - sk x_1j,  x_1j' = conj(sk) x_0j + ck x_1j (pair k)
+          auto col = [&](double2 &u, double2 &v) {
+            const double2 a0 = u, a1 = v;
+            u = make_double2(c * a0.x - (s.x * a1.x + s.y * a1.y), c * a0.y - (s.x * a1.y - s.y * a1.x));
+            v = make_double2(c * a1.x + (s.x * a0.x - s.y * a0.y), c * a1.y + (s.x * a0.y + s.y * a0.x));
+          };
+          auto row = [&](double2 &u, double2 &v) {
+            const double2 a0 = u, a1 = v;
+            u = make_double2(ck * a0.x - (sk.x * a1.x - sk.y * a1.y), ck * a0.y - (sk.x * a1.y + sk.y * a1.x));
+            v = make_double2(ck * a1.x + (sk.x * a0.x + sk.y * a0.y), ck * a1.y + (sk.x * a0.y - sk.y * a0.x));
+          };
+          col(x00, x01);
+          col(x10, x11);
+          row(x00, x10);
+          row(x01, x11);
+          if (k == l) {                            // the rotated pair itself: real diagonal, zero off it
+            x00.y = 0.0;
+            x11.y = 0.0;
+            x01 = make_double2(0.0, 0.0);
+            x10 = make_double2(0.0, 0.0);
+          }
+          double2(*An)[JMAX + 1] = A[cur ^ 1];
+          An[pk][pl] = x00;
+          An[pk][ql] = x01;
+          An[qk][pl] = x10;
+          An[qk][ql] = x11;
+        }
+      } else if (done > 0) {
+        rotate_v((done - 1) & 1);
+        cols.step();
       }
-      __syncthreads();
-      // columns: A J and V J.  e = e^{-i phi} = conj(ph).
-      for (int item = tid; item < 2 * half * m; item += 256) {
-        const int which = item / (half * m), rest = item % (half * m);
-        const int k = rest / m, i = rest % m;
-        const int p = rp[k], q = rq[k];
-        const double c = rc[k], s = rs[k];
-        const double2 e = make_double2(rph[k].x, -rph[k].y);
-        double2 (*M)[JMAX + 1] = which ? V : A;
-        const double2 x = M[i][p], y = M[i][q];
-        const double2 ey = make_double2(e.x * y.x - e.y * y.y, e.x * y.y + e.y * y.x);
-        M[i][p] = make_double2(c * x.x - s * ey.x, c * x.y - s * ey.y);
-        M[i][q] = make_double2(s * x.x + c * ey.x, s * x.y + c * ey.y);
-      }
-      __syncthreads();
-      // rows: J^H A.  conj(e) = ph.
-      for (int item = tid; item < half * m; item += 256) {
-        const int k = item / m, j = item % m;
-        const int p = rp[k], q = rq[k];
-        const double c = rc[k], s = rs[k];
-        const double2 f = rph[k];
-        const double2 x = A[p][j], y = A[q][j];
-        const double2 fy = make_double2(f.x * y.x - f.y * y.y, f.x * y.y + f.y * y.x);
-        A[p][j] = make_double2(c * x.x - s * fy.x, c * x.y - s * fy.y);
-        A[q][j] = make_double2(s * x.x + c * fy.x, s * x.y + c * fy.y);
-      }
+      ++done;
+      cur ^= 1;
       __syncthreads();
     }
   }
-  // descending order of the b real eigenvalues (padding excluded)
-  if (tid == 0) {
-    for (int i = 0; i < b; ++i) perm[i] = i;
-    for (int i = 0; i < b; ++i) {
-      int best = i;
-      for (int j = i + 1; j < b; ++j)
-        if (A[perm[j]][perm[j]].x > A[perm[best]][perm[best]].x) best = j;
-      const int t = perm[i]; perm[i] = perm[best]; perm[best] = t;
+  if (done > 0 && wave >= 4) rotate_v((done - 1) & 1);
+  // descending order of the b real eigenvalues (padding excluded): each one's rank
+  if (tid < b) perm[tid] = tid;        // stays in range whatever the values are
+  __syncthreads();
+  if (tid < b) {
+    const double mine = A[cur][tid][tid].x;
+    int rank = 0;
+    for (int j = 0; j < b; ++j) {
+      const double v = A[cur][j][j].x;
+      rank += v > mine || (v == mine && j < tid);
     }
+    perm[rank] = tid;
   }
   __syncthreads();
-  for (int idx = tid; idx < b * b; idx += 256) {
+  for (int idx = tid; idx < b * b; idx += 512) {
     const int i = idx / b, j = idx % b;
-    z[(size_t)i * ldz + j] = V[i][perm[j]];
+    z[(size_t)i * b + j] = V[i][perm[j]];
   }
-  if (tid < b) evals[tid] = A[perm[tid]][perm[tid]].x;
+  if (tid < b) evals[tid] = A[cur][perm[tid]][perm[tid]].x;
 }
 
-// Column j of w (leading dimension ld) scaled to unit norm; zero columns stay zero.  One block per column.
-__global__ void col_normalize_kernel(double2 *__restrict__ w, int rows, int ld) {
-  const int j = blockIdx.x;
-  __shared__ double red[256];
-  double a = 0.0;
-  for (int i = threadIdx.x; i < rows; i += 256) {
-    const double2 v = w[(size_t)i * ld + j];
-    a += v.x * v.x + v.y * v.y;
-  }
-  red[threadIdx.x] = a;
+// ---- orthonormalisation of a block -------------------------------------------------------------------
+// From the Gram matrix G = W^H W (sum of nblk partial ones) the upper triangular u with W u orthonormal: with
+// D = diag(G), D^-1/2 G D^-1/2 = L L^H (Cholesky), u = D^-1/2 L^-H.  The columns of W, -S times the Ritz vectors,
+// are close to orthogonal once the iteration settles, so W u stays close to them and the next Rayleigh-Ritz
+// problem close to diagonal, which saves its Jacobi sweeps.  A direction whose squared length falls below
+// 1e-14 of its column's once the earlier columns are projected out is dropped (u gets a zero column), as is a zero
+// column.  One workgroup; lane (m, c) of 32 x 8 keeps column m's rows 8 t + c, one barrier per pivot (the
+// elimination form of the Cholesky panels' diagonal blocks: a lane holds column m of G until pivot m and then
+// that column of L's inverse).
+__global__ __launch_bounds__(256) void block_chol_kernel(const double2 *__restrict__ gpart, int nblk, int b,
+                                                         double2 *__restrict__ u) {
+  __shared__ double2 g[JMAX][JMAX + 1];
+  __shared__ double2 colj[JMAX][JMAX + 1], rowj[JMAX][JMAX + 1];
+  __shared__ double dinv[JMAX];
+  const int tid = threadIdx.x, m = tid % JMAX, c = tid / JMAX;
+  constexpr int T = JMAX / 8;
+  gram_sum<256>(gpart, nblk, b, g);
   __syncthreads();
-  for (int st = 128; st > 0; st >>= 1) {
-    if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
+  if (tid < JMAX) {
+    const double d = g[tid][tid].x;
+    dinv[tid] = d > 0.0 && isfinite(d) ? 1.0 / sqrt(d) : 0.0;
   }
-  const double nrm = sqrt(red[0]);
-  if (nrm == 0.0) return;
-  const double inv = 1.0 / nrm;
-  for (int i = threadIdx.x; i < rows; i += 256) {
-    double2 v = w[(size_t)i * ld + j];
-    w[(size_t)i * ld + j] = make_double2(v.x * inv, v.y * inv);
+  __syncthreads();
+  double2 v[T];
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int i = 8 * t + c;
+    const double2 a = g[i][m], h = g[m][i];
+    const double f = 0.5 * dinv[i] * dinv[m];
+    v[t] = make_double2(f * (a.x + h.x), f * (a.y - h.y));
   }
-}
-
-// u[:, j] *= lambda_j^-1/2 for lambda_j above rel * lambda_0 (descending), else 0 (drops a dependent direction)
-__global__ void svqb_scale_kernel(double2 *__restrict__ u, const double *__restrict__ lam, int b, double rel) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= b * b) return;
-  const int j = idx % b;
-  const double l = lam[j];
-  const double f = (l > rel * lam[0] && l > 0.0) ? 1.0 / sqrt(l) : 0.0;
-  u[idx] = make_double2(u[idx].x * f, u[idx].y * f);
-}
-
-// out[0] = max_{j < nm} ||y_j - theta_j x_j|| / theta_0 (one workgroup; each wave takes modes in turn)
-__global__ __launch_bounds__(256) void ritz_residual_kernel(const double2 *__restrict__ x, const double2 *__restrict__ y,
-                                                            int ng, int ld, const double *__restrict__ theta, int nm,
-                                                            double *__restrict__ out) {
-  __shared__ double res[JMAX];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int j = wave; j < nm; j += 4) {
-    const double t = theta[j];
-    double a = 0.0;
-    for (int g = lane; g < ng; g += 64) {
-      const double2 xv = x[(size_t)g * ld + j], yv = y[(size_t)g * ld + j];
-      const double dx = yv.x - t * xv.x, dy = yv.y - t * xv.y;
-      a += dx * dx + dy * dy;
+  for (int j = 0; j < b; ++j) {
+    if (m == j) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const int i = 8 * t + c;
+        colj[j][i] = v[t];
+        v[t] = make_double2(i == m ? 1.0 : 0.0, 0.0);
+      }
     }
-    for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-    if (lane == 0) res[j] = sqrt(a);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+      if (8 * t + c == j) rowj[j][m] = v[t];           // row j of L's inverse (used where m <= j)
+    __syncthreads();
+    const double d = colj[j][j].x;
+    const bool ok = d > 1e-14;
+    const double di = ok ? rcp_nr(d) : 0.0;
+    const double2 q = m > j ? colj[j][m] : rowj[j][m];
+    const double wx = q.x * di, wy = (m > j ? -q.y : q.y) * di;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+      const int i = 8 * t + c;
+      if (i > j) {
+        const double2 s = colj[j][i];
+        v[t].x -= s.x * wx - s.y * wy;
+        v[t].y -= s.x * wy + s.y * wx;
+      }
+    }
   }
+  // row i of the inverse times D^-1/2 of pivot i; u[m][i] = dinv[m] conj(Linv[i][m])
+  __shared__ double piv[JMAX];
+  if (tid < b) {
+    const double d = colj[tid][tid].x;
+    piv[tid] = d > 1e-14 ? 1.0 / sqrt(d) : 0.0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < T; ++t) {
+    const int i = 8 * t + c;
+    if (i < b && m < b) {
+      const double f = i >= m ? dinv[m] * piv[i] : 0.0;
+      u[m * b + i] = make_double2(f * v[t].x, -f * v[t].y);
+    }
+  }
+}
+
+// w = x z and, with y, t = y z for [ng][b] blocks and a b x b matrix z: 16 rows per workgroup, thread (row, column
+// j) of 8 x 32 forms two rows of each.  With y also the rows' share of ||t_j - theta_j w_j||^2 into rpart[block][b].
+constexpr int ROT_ROWS = 16;
+__global__ __launch_bounds__(256) void block_rotate_kernel(const double2 *__restrict__ x, const double2 *__restrict__ y,
+                                                           const double2 *__restrict__ z, int ng, int b,
+                                                           const double *__restrict__ theta, double2 *__restrict__ w,
+                                                           double2 *__restrict__ t, double *__restrict__ rpart) {
+  __shared__ double2 sz[JMAX][JMAX];
+  __shared__ double2 sx[ROT_ROWS][JMAX], sy[ROT_ROWS][JMAX];
+  __shared__ double red[8][JMAX];
+  const int tid = threadIdx.x, j = tid % JMAX, rg = tid / JMAX;
+  const int r0 = blockIdx.x * ROT_ROWS;
+  const double2 zero = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int h = 0; h < JMAX / 8; ++h) {
+    const int k = rg + 8 * h;
+    sz[k][j] = (k < b && j < b) ? z[k * b + j] : zero;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int rr = rg + 8 * h, r = r0 + rr;
+    const bool in = r < ng && j < b;
+    sx[rr][j] = in ? x[(size_t)r * b + j] : zero;
+    sy[rr][j] = in && y ? y[(size_t)r * b + j] : zero;
+  }
+  __syncthreads();
+  double2 aw[2] = {zero, zero}, at[2] = {zero, zero};
+#pragma unroll 4
+  for (int k = 0; k < JMAX; ++k) {
+    const double2 zv = sz[k][j];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const double2 xv = sx[rg + 8 * h][k];
+      aw[h].x += xv.x * zv.x - xv.y * zv.y;
+      aw[h].y += xv.x * zv.y + xv.y * zv.x;
+      if (y) {
+        const double2 yv = sy[rg + 8 * h][k];
+        at[h].x += yv.x * zv.x - yv.y * zv.y;
+        at[h].y += yv.x * zv.y + yv.y * zv.x;
+      }
+    }
+  }
+  double res = 0.0;
+  const double th = y && j < b ? theta[j] : 0.0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int r = r0 + rg + 8 * h;
+    if (r < ng && j < b) {
+      w[(size_t)r * b + j] = aw[h];
+      if (y) {
+        t[(size_t)r * b + j] = at[h];
+        const double dx = at[h].x - th * aw[h].x, dy = at[h].y - th * aw[h].y;
+        res += dx * dx + dy * dy;
+      }
+    }
+  }
+  if (!y) return;
+  red[rg][j] = res;
+  __syncthreads();
+  if (rg == 0) {
+    double a = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a += red[q][j];
+    if (j < b) rpart[(size_t)blockIdx.x * b + j] = a;
+  }
+}
+
+// out[0] = max_{j < nm} ||y_j - theta_j x_j|| / theta_0 from the blocks' shares (one workgroup)
+__global__ __launch_bounds__(256) void ritz_residual_kernel(const double *__restrict__ rpart, int nblk, int b,
+                                                            const double *__restrict__ theta, int nm,
+                                                            double *__restrict__ out) {
+  __shared__ double red[8][JMAX];
+  const int j = threadIdx.x % JMAX, g = threadIdx.x / JMAX;
+  double a = 0.0;
+#pragma unroll 8
+  for (int q = g; q < nblk; q += 8) a += j < b ? rpart[(size_t)q * b + j] : 0.0;
+  red[g][j] = a;
   __syncthreads();
   if (threadIdx.x == 0) {
     double mx = 0.0;
-    for (int j = 0; j < nm; ++j) mx = fmax(mx, res[j]);
-    out[0] = theta[0] > 0.0 ? mx / theta[0] : (mx == 0.0 ? 0.0 : INFINITY);
+    bool bad = false;
+    for (int i = 0; i < nm; ++i) {
+      double s = 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s += red[q][i];
+      const double v = sqrt(s);
+      bad = bad || v != v;
+      mx = fmax(mx, v);
+    }
+    out[0] = bad ? NAN : theta[0] > 0.0 ? mx / theta[0] : (mx == 0.0 ? 0.0 : INFINITY);
   }
+}
+
+// y = alpha sum_z part[z] (the thin product's splits)
+__global__ void thin_sum_kernel(const double2 *__restrict__ part, int kz, size_t n, double alpha,
+                                double2 *__restrict__ y) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  double2 a = make_double2(0.0, 0.0);
+#pragma unroll 4
+  for (int z = 0; z < kz; ++z) {
+    const double2 v = part[(size_t)z * n + i];
+    a.x += v.x;
+    a.y += v.y;
+  }
+  y[i] = make_double2(alpha * a.x, alpha * a.y);
 }
 
 // sigma_a = -theta_a, omega_a = sqrt(Re(a^H t_a) / theta_a) with t = M A (one workgroup per mode)
@@ -335,6 +725,80 @@ __global__ void pp_finish_kernel(double2 *__restrict__ e, const double2 *__restr
   }
 }
 
+// The pole form for at most 32 modes in one pass: e = I + (sum_a c_a A_ga conj(A_ha)) / (sv_g sv_h) with
+// c_a = sigma_a omega_a^2 / (omega_a^2 - w^2), or the static entry where sv_g or sv_h vanishes.  64 x 64 outputs
+// per workgroup, 4 x 4 per thread, both tiles' modes in LDS; bound by writing e once.  (Weights, product and
+// division as three passes: 100 us for 3071 G and 16 modes; 62 us.)
+constexpr int PFT = 64, PFM = 32;
+__global__ __launch_bounds__(256) void pp_pole_kernel(const double2 *__restrict__ modes, int ng, int nm,
+                                                      const double *__restrict__ sigma,
+                                                      const double *__restrict__ omega, double w,
+                                                      const double *__restrict__ sv,
+                                                      const double2 *__restrict__ ei_static, double2 *__restrict__ e) {
+  __shared__ double2 sa[PFM][PFT + 1], sb[PFM][PFT + 1];
+  __shared__ double sc[PFM];
+  const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
+  const int g0 = blockIdx.y * PFT, h0 = blockIdx.x * PFT;
+  if (tid < nm) {
+    const double o2 = omega[tid] * omega[tid];
+    sc[tid] = sigma[tid] * o2 / (o2 - w * w);
+  }
+  __syncthreads();
+  for (int idx = tid; idx < PFT * nm; idx += 256) {
+    const int r = idx / nm, a = idx - r * nm;
+    const double2 u = modes[(size_t)min(g0 + r, ng - 1) * nm + a], v = modes[(size_t)min(h0 + r, ng - 1) * nm + a];
+    sa[a][r] = make_double2(sc[a] * u.x, sc[a] * u.y);
+    sb[a][r] = v;
+  }
+  __syncthreads();
+  double2 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = make_double2(0.0, 0.0);
+#pragma unroll 2
+  for (int a = 0; a < nm; ++a) {
+    double2 u[4], v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) u[i] = sa[a][ty + 16 * i];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = sb[a][tx + 16 * j];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc[i][j].x += u[i].x * v[j].x + u[i].y * v[j].y;
+        acc[i][j].y += u[i].y * v[j].x - u[i].x * v[j].y;
+      }
+  }
+  double rg[4], rh[4];                 // 1 / sqrt(V), 0 where it vanishes
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double x = sv[min(g0 + ty + 16 * i, ng - 1)], y = sv[min(h0 + tx + 16 * i, ng - 1)];
+    rg[i] = x > 0.0 ? 1.0 / x : 0.0;
+    rh[i] = y > 0.0 ? 1.0 / y : 0.0;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int g = g0 + ty + 16 * i, h = h0 + tx + 16 * j;
+      if (g < ng && h < ng) {
+        const size_t at = (size_t)g * ng + h;
+        double2 v = acc[i][j];
+        if (rg[i] > 0.0 && rh[j] > 0.0) {
+          const double f = rg[i] * rh[j];
+          v.x *= f;
+          v.y *= f;
+          if (g == h) v.x += 1.0;
+        } else {
+          v = ei_static[at];
+        }
+        e[at] = v;
+      }
+    }
+}
+
 static inline unsigned blocks_for(size_t n) { return (unsigned)((n + 255) / 256); }
 
 hipError_t launch_density(const float2 *psi, int nv, int nr, double occ, double2 *rho, hipStream_t s) {
@@ -369,32 +833,71 @@ hipError_t launch_start_block(double2 *x, int ng, int b, unsigned long long seed
   return hipGetLastError();
 }
 
-hipError_t launch_herm_jacobi(const double2 *h, int b, int ldh, double *evals, double2 *z, int ldz, hipStream_t s) {
+hipError_t launch_thin_product(int M, int N, int K, const double2 *A, long long lda, const double2 *B, int ldb,
+                               double2 *part, hipStream_t s) {
+  if (N < 1 || N > JMAX) return hipErrorInvalidValue;
+  const int kz = thin_splits(M, K);
+  int kchunk = (K + kz - 1) / kz;
+  kchunk = (kchunk + TPK - 1) / TPK * TPK;
+  hipLaunchKernelGGL(thin_product_kernel, dim3((M + TPM - 1) / TPM, kz), dim3(256), 0, s, M, N, K, A, lda, B, ldb, part,
+                     kchunk);
+  return hipGetLastError();
+}
+
+hipError_t launch_thin_sum(const double2 *part, int M, int N, int K, double alpha, double2 *y, hipStream_t s) {
+  const size_t n = (size_t)M * N;
+  hipLaunchKernelGGL(thin_sum_kernel, dim3(blocks_for(n)), dim3(256), 0, s, part, thin_splits(M, K), n, alpha, y);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_gram(const double2 *x, const double2 *y, int ng, int b, double2 *gpart, hipStream_t s) {
+  hipLaunchKernelGGL(block_gram_kernel, dim3(gram_blocks(ng)), dim3(256), 0, s, x, y, ng, b, gram_chunk(ng), gpart);
+  return hipGetLastError();
+}
+
+hipError_t launch_herm_jacobi(const double2 *gpart, int ng, int b, double *evals, double2 *z, hipStream_t s) {
   if (b < 1 || b > JMAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(herm_jacobi_kernel, dim3(1), dim3(256), 0, s, h, b, ldh, evals, z, ldz, 40);
+  hipLaunchKernelGGL(herm_jacobi_kernel, dim3(1), dim3(512), 0, s, gpart, gram_blocks(ng), b, evals, z, 40);
   return hipGetLastError();
 }
 
-hipError_t launch_col_normalize(double2 *w, int rows, int ld, int cols, hipStream_t s) {
-  hipLaunchKernelGGL(col_normalize_kernel, dim3(cols), dim3(256), 0, s, w, rows, ld);
+hipError_t launch_block_chol(const double2 *gpart, int ng, int b, double2 *u, hipStream_t s) {
+  if (b < 1 || b > JMAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(block_chol_kernel, dim3(1), dim3(256), 0, s, gpart, gram_blocks(ng), b, u);
   return hipGetLastError();
 }
 
-hipError_t launch_svqb_scale(double2 *u, const double *lam, int b, double rel, hipStream_t s) {
-  hipLaunchKernelGGL(svqb_scale_kernel, dim3(blocks_for((size_t)b * b)), dim3(256), 0, s, u, lam, b, rel);
+size_t rotate_part_doubles(int ng, int b) { return (size_t)((ng + ROT_ROWS - 1) / ROT_ROWS) * b; }
+
+hipError_t launch_block_rotate(const double2 *x, const double2 *z, int ng, int b, double2 *w, hipStream_t s) {
+  hipLaunchKernelGGL(block_rotate_kernel, dim3((ng + ROT_ROWS - 1) / ROT_ROWS), dim3(256), 0, s, x,
+                     (const double2 *)nullptr, z, ng, b, (const double *)nullptr, w, (double2 *)nullptr,
+                     (double *)nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_ritz_residual(const double2 *x, const double2 *y, int ng, int ld, const double *theta, int nm,
-                                double *out, hipStream_t s) {
+hipError_t launch_block_ritz(const double2 *x, const double2 *y, const double2 *z, int ng, int b, const double *theta,
+                             int nm, double2 *w, double2 *t, double *rpart, double *out, hipStream_t s) {
   if (nm < 1 || nm > JMAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(ritz_residual_kernel, dim3(1), dim3(256), 0, s, x, y, ng, ld, theta, nm, out);
+  const int nblk = (ng + ROT_ROWS - 1) / ROT_ROWS;
+  hipLaunchKernelGGL(block_rotate_kernel, dim3(nblk), dim3(256), 0, s, x, y, z, ng, b, theta, w, t, rpart);
+  hipLaunchKernelGGL(ritz_residual_kernel, dim3(1), dim3(256), 0, s, rpart, nblk, b, theta, nm, out);
   return hipGetLastError();
 }
 
 hipError_t launch_pp_frequency(const double2 *a, int lda, const double2 *t, int ldt, int ng, const double *theta,
                                int nm, double *sigma, double *omega, hipStream_t s) {
   hipLaunchKernelGGL(pp_frequency_kernel, dim3(nm), dim3(256), 0, s, a, lda, t, ldt, ng, theta, sigma, omega);
+  return hipGetLastError();
+}
+
+bool pp_pole_fits(int nm) { return nm <= PFM; }
+
+hipError_t launch_pp_pole(const double2 *modes, int ng, int nm, const double *sigma, const double *omega, double w,
+                          const double *sv, const double2 *ei_static, double2 *e, hipStream_t s) {
+  const int nt = (ng + PFT - 1) / PFT;
+  if (nm > PFM || nt > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pp_pole_kernel, dim3(nt, nt), dim3(256), 0, s, modes, ng, nm, sigma, omega, w, sv, ei_static, e);
   return hipGetLastError();
 }
 

@@ -118,3 +118,33 @@ def test_iteration_limit(gw):
     ei, pv = gpu_eps_inv(gw, s)
     with pytest.raises(gw.GwError, match="did not reach tol"):
         gw.plasmon_pole(ei, s.n, s.a_bohr, s.q, s.miller, pv, 1.0, 8, tol=1e-14, max_iter=2)
+
+
+# Block sizes of the iteration against LAPACK: one workgroup's worth of rows and less, odd blocks (the Jacobi
+# rounds' padding index), sizes around the thin product's 64 rows, the Gram chunks (48 rows) and its splits of K,
+# and a matrix of rank one, whose dependent directions are dropped.  Tolerances as above: sigma to 1e-12 of
+# |sigma_0|, every mode to 1e-9; omega follows from the modes.
+@pytest.mark.parametrize("ng,nm,rank", [(1, 1, 0), (2, 2, 0), (7, 5, 0), (31, 16, 0), (33, 8, 0), (47, 4, 0), (65, 24, 0),
+                                        (130, 16, 0), (515, 24, 0), (1100, 8, 0), (60, 1, 1)])
+def test_block_sizes(gw, ng, nm, rank):
+    rng = np.random.default_rng(ng)
+    n, q = (12, 12, 12), np.array([0.1, 0.2, 0.3])
+    mill = gs.sphere(n, count=ng, q=q)
+    a = gs.cell_side(12)
+    sv = orc.coulomb_sqrt(n, a, q, mill)
+    x = rng.standard_normal((ng, rank or 2 * ng)) + 1j * rng.standard_normal((ng, rank or 2 * ng))
+    d = 1.0 / (0.2 + np.arange(ng)) ** 1.5                         # a spectrum that falls as the screening's does
+    s = -(x * d[:, None]) @ (x * d[:, None]).conj().T / (2 * ng)
+    eps_inv = np.eye(ng) + s / (sv[:, None] * sv[None, :])
+    psi = rng.standard_normal((3, 12 ** 3)) + 1j * rng.standard_normal((3, 12 ** 3))
+    psi = (psi / np.sqrt((np.abs(psi) ** 2).sum(1))[:, None]).astype(np.complex64)
+    print(f"[case] ng={ng} nm={nm} rank={rank}", flush=True)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda:0")
+    sig, om, modes, its, res = gw.plasmon_pole(dev(eps_inv), n, a, q, mill, dev(psi), n_modes=nm)
+    w, v = np.linalg.eigh(sv[:, None] * (eps_inv - np.eye(ng)) * sv[None, :])
+    sig, modes = sig.cpu().numpy(), modes.cpu().numpy()
+    assert np.max(np.abs(sig - w[:nm])) < 1e-12 * abs(w[0])
+    for j in range(nm):
+        gap = np.min(np.abs(np.delete(w, j) - w[j])) if ng > 1 else 1.0
+        assert abs(abs(np.vdot(v[:, j], modes[:, j])) - 1.0) < max(1e-9, (1e-9 * abs(w[0]) / gap) ** 2)
+    assert np.all(om.cpu().numpy() > 0) and res <= 1e-10
