@@ -390,6 +390,30 @@ int upload_plan(gw_ctx *ctx, gw_grid g, const int *miller, int ng, int map_slot,
   return GW_OK;
 }
 
+int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, hipStream_t s) {
+  const size_t nm = (size_t)ng * 3;
+  void *d;
+  GW_STATUS(ws_get(ctx, slot, nm * sizeof(int), &d, s));
+  std::unique_ptr<MillerCacheEntry> &e = ctx->millers[slot];
+  if (!e) {
+    e.reset(new (std::nothrow) MillerCacheEntry());
+    if (!e) {
+      set_err(ctx, "out of host memory for the Miller list");
+      return GW_E_NOMEM;
+    }
+  }
+  *dev = (int *)d;
+  if (e->dev == d && e->stream == (void *)s && e->miller.size() == nm &&
+      std::equal(miller, miller + nm, e->miller.begin()))
+    return GW_OK;
+  e->dev = nullptr;                       // not valid until the copy is queued
+  e->miller.assign(miller, miller + nm);
+  GW_HIP(ctx, hipMemcpyAsync(d, e->miller.data(), nm * sizeof(int), hipMemcpyHostToDevice, s));
+  e->dev = d;
+  e->stream = (void *)s;
+  return GW_OK;
+}
+
 }  // namespace gwi
 
 namespace {
@@ -440,8 +464,7 @@ int upload_scales(gw_ctx *ctx, const double *e_v, int nv, const double *e_c, int
   GW_STATUS(ws_get(ctx, WS_ENERGY, (size_t)(nv + nc) * sizeof(double), &eb, s));
   GW_STATUS(ws_get(ctx, WS_SCALE, scale_table_floats(nv, nc) * sizeof(float), &sb, s));
   double *de = (double *)eb;
-  GW_HIP(ctx, hipMemcpyAsync(de, e_v, nv * sizeof(double), hipMemcpyHostToDevice, s));
-  GW_HIP(ctx, hipMemcpyAsync(de + nv, e_c, nc * sizeof(double), hipMemcpyHostToDevice, s));
+  GW_HIP(ctx, upload_energies(e_v, nv, e_c, nc, de, s));
   GW_HIP(ctx, launch_scale_table(de, nv, de + nv, nc, prefactor, (float *)sb, ldsc, s));
   *scale = (float *)sb;
   return GW_OK;
@@ -479,11 +502,11 @@ int grid_supported(gw_ctx *ctx, gw_grid g) {
 
 int eps_build_impl(gw_ctx *ctx, const float2 *p_gg, int ng, gw_grid g, const double *q, const int *miller,
                    double head, double2 *eps, hipStream_t s) {
-  void *dm, *dsv;
-  GW_STATUS(ws_get(ctx, WS_MILLER, (size_t)ng * 3 * sizeof(int), &dm, s));
+  int *dm;
+  void *dsv;
+  GW_STATUS(upload_miller(ctx, miller, ng, WS_MILLER, &dm, s));
   GW_STATUS(ws_get(ctx, WS_SQRTV, (size_t)ng * sizeof(double), &dsv, s));
-  GW_HIP(ctx, hipMemcpyAsync(dm, miller, (size_t)ng * 3 * sizeof(int), hipMemcpyHostToDevice, s));
-  GW_HIP(ctx, launch_sqrtv((const int *)dm, ng, q[0], q[1], q[2], g.a_bohr, (double *)dsv, s));
+  GW_HIP(ctx, launch_sqrtv(dm, ng, q[0], q[1], q[2], g.a_bohr, (double *)dsv, s));
   GW_HIP(ctx, launch_eps_build(p_gg, ng, (const double *)dsv, head, eps, s));
   return GW_OK;
 }

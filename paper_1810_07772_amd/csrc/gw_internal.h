@@ -15,6 +15,7 @@
 
 namespace gwi {
 struct PlanCacheEntry;
+struct MillerCacheEntry;
 }
 
 struct gw_ctx {
@@ -34,6 +35,8 @@ struct gw_ctx {
   std::string arch;                   // device architecture name (cached)
   // the sphere plan last uploaded into each map slot, reused while grid, Miller list and stream match
   std::map<int, std::unique_ptr<gwi::PlanCacheEntry>> plans;
+  // the Miller list last uploaded into each slot, reused while list and stream match
+  std::map<int, std::unique_ptr<gwi::MillerCacheEntry>> millers;
   // the last spheres (grid and Miller list) that passed the argument checks, reused round-robin
   struct SphereSeen { int n1 = 0, n2 = 0, n3 = 0; std::vector<int> miller; };
   SphereSeen spheres_ok[4];
@@ -78,6 +81,7 @@ constexpr int kOptionalSlots[] = {WS_TAIL_PART, WS_HERK_PART};
 // Pair scales s_vc = sqrt(p / (E_c - E_v)) as float [nv][ldsc], zero for nc <= c < ldsc.
 int scale_ld(int nc);
 size_t scale_table_floats(int nv, int nc);   // s table, then s^2 table, each [nv][scale_ld(nc)]
+hipError_t upload_energies(const double *e_v, int nv, const double *e_c, int nc, double *dev, hipStream_t s);
 hipError_t launch_scale_table(const double *e_v, int nv, const double *e_c, int nc, double prefactor,
                               float *scale, int ldsc, hipStream_t s);
 hipError_t launch_pair_products(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr,
@@ -234,6 +238,14 @@ struct PlanCacheEntry {
   void *maps = nullptr;      // device copy of the maps (the slot's buffer at upload)
   SpherePlan plan;
 };
+struct MillerCacheEntry {
+  std::vector<int> miller;
+  void *stream = nullptr, *dev = nullptr;
+};
+// The device copy of a Miller list in workspace slot `slot`, which nothing else writes: a call with the list and
+// stream of the slot's last upload reuses it (a copy from pageable memory would block the host until the stream
+// has come to it).
+int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, hipStream_t s);
 struct SphereBuffers {
   float2 *a1, *a2, *ph, *pht, *q;  // pass intermediates, P^ [ng][nr], its transpose, Q [ng][ng]
   const int *dA, *dB, *dC;         // device copies of the plan's maps

@@ -34,12 +34,10 @@ struct Small {            // b x b matrices, eigenvalues and partial sums of the
 
 int upload_sphere(gw_ctx *ctx, const int *miller, int ng, const double *q, double a_bohr, int **dm, double **dsv,
                   hipStream_t s) {
-  void *m, *sv;
-  GWX_STATUS(api_ws_get(ctx, PP_MILLER, (size_t)ng * 3 * sizeof(int), &m, s));
+  void *sv;
+  GWX_STATUS(upload_miller(ctx, miller, ng, PP_MILLER, dm, s));
   GWX_STATUS(api_ws_get(ctx, PP_SQRTV, (size_t)ng * sizeof(double), &sv, s));
-  GWX_HIP(ctx, hipMemcpyAsync(m, miller, (size_t)ng * 3 * sizeof(int), hipMemcpyHostToDevice, s));
-  GWX_HIP(ctx, launch_sqrtv((const int *)m, ng, q[0], q[1], q[2], a_bohr, (double *)sv, s));
-  *dm = (int *)m;
+  GWX_HIP(ctx, launch_sqrtv(*dm, ng, q[0], q[1], q[2], a_bohr, (double *)sv, s));
   *dsv = (double *)sv;
   return GW_OK;
 }

@@ -58,11 +58,11 @@ int pair_transform(gw_ctx *ctx, const float2 *psi_n, int nn, const float2 *psi_v
 
 int sqrtv_on_device(gw_ctx *ctx, const int *miller, int ng, const double *q, double a_bohr, double **sv,
                     hipStream_t s) {
-  void *m, *d;
-  GWX_STATUS(api_ws_get(ctx, SG_MILLER, (size_t)ng * 3 * sizeof(int), &m, s));
+  int *m;
+  void *d;
+  GWX_STATUS(upload_miller(ctx, miller, ng, SG_MILLER, &m, s));
   GWX_STATUS(api_ws_get(ctx, SG_SQRTV, (size_t)ng * sizeof(double), &d, s));
-  GWX_HIP(ctx, hipMemcpyAsync(m, miller, (size_t)ng * 3 * sizeof(int), hipMemcpyHostToDevice, s));
-  GWX_HIP(ctx, launch_sqrtv((const int *)m, ng, q[0], q[1], q[2], a_bohr, (double *)d, s));
+  GWX_HIP(ctx, launch_sqrtv(m, ng, q[0], q[1], q[2], a_bohr, (double *)d, s));
   *sv = (double *)d;
   return GW_OK;
 }

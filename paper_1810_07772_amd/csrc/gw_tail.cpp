@@ -150,10 +150,9 @@ int gw_tail_features(gw_ctx *ctx, const gw_c32 *p_gg, int ng, gw_grid grid, cons
   GWX_STATUS(api_check_sphere(ctx, grid, g_miller, ng));
   if (ctx->device < 0) return GW_OK;
   hipStream_t s = as_stream(stream);
-  void *dm;
-  GWX_STATUS(api_ws_get(ctx, WS_MILLER, (size_t)ng * 3 * sizeof(int), &dm, s));
-  GWX_HIP(ctx, hipMemcpyAsync(dm, g_miller, (size_t)ng * 3 * sizeof(int), hipMemcpyHostToDevice, s));
-  GWX_HIP(ctx, tail_features((const float2 *)p_gg, ng, (const int *)dm, q, grid.a_bohr, nc, e_max, feat, s));
+  int *dm;
+  GWX_STATUS(upload_miller(ctx, g_miller, ng, WS_MILLER, &dm, s));
+  GWX_HIP(ctx, tail_features((const float2 *)p_gg, ng, dm, q, grid.a_bohr, nc, e_max, feat, s));
   return GW_OK;
 }
 

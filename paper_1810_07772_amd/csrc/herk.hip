@@ -1325,42 +1325,88 @@ __global__ __launch_bounds__(NTHR) void herk_part_sum_kernel(const f32x4 *__rest
 // scaled f of band v stays below 2^14 (FP16 max 65504) and its lo part stays normal for
 // every entry within 2^-10 of the band's largest.
 // ---------------------------------------------------------------------------------------------
-__global__ void absmax_rows_kernel(const float2 *__restrict__ psi, int nrows, int nr, float *__restrict__ out) {
+// One workgroup per orbital: out[row] = max_r |psi(r)| over the occupied bands, then the unoccupied ones; an
+// occupied band's workgroup also takes the largest of its pair scales (smax).  1024 threads: a row is one pass of a
+// few dependent loads, so with 256 it took 25 us per set at 24^3; both sets now take 10 us, and the
+// exponents with their order 4 us (27 us with one thread per band reading all unoccupied maxima).
+constexpr int ABS_THREADS = 1024;
+__global__ __launch_bounds__(ABS_THREADS) void absmax_rows_kernel(const float2 *__restrict__ psi_v, int nv,
+                                                                  const float2 *__restrict__ psi_c, int nr,
+                                                                  const float *__restrict__ scale, int ldsc, int nc,
+                                                                  float *__restrict__ out, float *__restrict__ smax) {
   const int row = blockIdx.x;
-  float m = 0.f;
-  for (int r = threadIdx.x; r < nr; r += blockDim.x) {
-    const float2 z = psi[(size_t)row * nr + r];
+  const float2 *src = row < nv ? psi_v + (size_t)row * nr : psi_c + (size_t)(row - nv) * nr;
+  float m = 0.f, sm = 0.f;
+#pragma unroll 4
+  for (int r = threadIdx.x; r < nr; r += ABS_THREADS) {
+    const float2 z = src[r];
     m = fmaxf(m, sqrtf(z.x * z.x + z.y * z.y));
   }
-  __shared__ float red[256];
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + s]);
-    __syncthreads();
+  if (row < nv)
+    for (int c = threadIdx.x; c < nc; c += ABS_THREADS) sm = fmaxf(sm, scale[(size_t)row * ldsc + c]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    m = fmaxf(m, __shfl_xor(m, off, 64));
+    sm = fmaxf(sm, __shfl_xor(sm, off, 64));
   }
-  if (threadIdx.x == 0) out[row] = red[0];
+  __shared__ float rm[ABS_THREADS / 64], rs[ABS_THREADS / 64];
+  if ((threadIdx.x & 63) == 0) {
+    rm[threadIdx.x >> 6] = m;
+    rs[threadIdx.x >> 6] = sm;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < ABS_THREADS / 64; ++w) {
+      m = fmaxf(m, rm[w]);
+      sm = fmaxf(sm, rs[w]);
+    }
+    out[row] = m;
+    if (row < nv) smax[row] = sm;
+  }
 }
 
-// shift[v] = floor(log2(max_c s_vc)): the planar kernel carries the whole weight s^2 on its row side and
-// none on its column side, and scales them by 2^{e_v - shift_v} and 2^{e_v + shift_v}, so both stay
-// within a factor 2 of the bound above (below 2^15) and their product keeps the factor 2^{2 e_v}.
-__global__ void band_exponent_kernel(const float *__restrict__ vmax, int nv, const float *__restrict__ cmax, int nc,
-                                     const float *__restrict__ scale, int ldsc, int *__restrict__ band_exp,
-                                     int *__restrict__ shift) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nv) return;
-  float cm = 0.f, sm = 0.f;
-  for (int c = 0; c < nc; ++c) { cm = fmaxf(cm, cmax[c]); sm = fmaxf(sm, scale[v * ldsc + c]); }
-  const float bound = vmax[v] * cm * sm;
-  int e = 0;
-  if (bound > 0.f) e = (int)floorf(log2f(16384.0f / bound));
-  band_exp[v] = max(-60, min(60, e));
-  shift[v] = sm > 0.f ? max(-30, min(30, (int)floorf(log2f(sm)))) : 0;
+// Exponents and shifts of all bands (one workgroup): shift[v] = floor(log2(max_c s_vc)): the planar kernel carries
+// the whole weight s^2 on its row side and none on its column side, and scales them by 2^{e_v - shift_v} and
+// 2^{e_v + shift_v}, so both stay within a factor 2 of the bound above (below 2^15) and their product keeps the
+// factor 2^{2 e_v}.  smax and shift share their memory.  For up to ORDER_BANDS bands their order by exponent
+// follows at once: order[k] is the k-th band (a band's place is the count of smaller exponents and of equal ones
+// before it), es[k] its exponent.
+constexpr int ORDER_BANDS = 1024;
+__global__ __launch_bounds__(256) void band_exponent_kernel(const float *__restrict__ vmax, int nv,
+                                                            const float *__restrict__ cmax, int nc,
+                                                            int *__restrict__ band_exp, int *shift,
+                                                            int *__restrict__ order, int *__restrict__ es) {
+  __shared__ float red[4];
+  __shared__ int se[ORDER_BANDS];
+  float cm = 0.f;
+  for (int c = threadIdx.x; c < nc; c += 256) cm = fmaxf(cm, cmax[c]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = cm;
+  __syncthreads();
+  cm = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  for (int v = threadIdx.x; v < nv; v += 256) {
+    const float sm = __int_as_float(shift[v]);
+    const float bound = vmax[v] * cm * sm;
+    int e = 0;
+    if (bound > 0.f) e = (int)floorf(log2f(16384.0f / bound));
+    e = max(-60, min(60, e));
+    band_exp[v] = e;
+    if (v < ORDER_BANDS) se[v] = e;
+    shift[v] = sm > 0.f ? max(-30, min(30, (int)floorf(log2f(sm)))) : 0;
+  }
+  if (nv > ORDER_BANDS) return;
+  __syncthreads();
+  for (int v = threadIdx.x; v < nv; v += 256) {
+    const int e = se[v];
+    int k = 0;
+    for (int u = 0; u < nv; ++u) k += se[u] < e || (se[u] == e && u < v);
+    order[k] = v;
+    es[k] = e;
+  }
 }
 
-// Bands ordered by exponent (a stable counting sort over the clamped range [-60, 60], one thread):
-// order[k] is the k-th band, es[k] its exponent.
+// More bands ordered by exponent (a stable counting sort over the clamped range [-60, 60], one thread).
 __global__ void band_order_kernel(const int *__restrict__ band_exp, int nv, int *__restrict__ order,
                                   int *__restrict__ es) {
   __shared__ int start[122];
@@ -1384,11 +1430,13 @@ hipError_t launch_band_exponents(const float2 *psi_v, int nv, const float2 *psi_
   // maxima as floats: occupied [nv], unoccupied [nc], then the per-band shifts [nv]
   float *vmax = reinterpret_cast<float *>(band_exp + 3 * nv);
   float *cmax = vmax + nv;
-  hipLaunchKernelGGL(absmax_rows_kernel, dim3(nv), dim3(256), 0, s, psi_v, nv, nr, vmax);
-  hipLaunchKernelGGL(absmax_rows_kernel, dim3(nc), dim3(256), 0, s, psi_c, nc, nr, cmax);
-  hipLaunchKernelGGL(band_exponent_kernel, dim3((nv + 63) / 64), dim3(64), 0, s, vmax, nv, cmax, nc, scale, ldsc,
-                     band_exp, band_exp + 4 * nv + nc);
-  hipLaunchKernelGGL(band_order_kernel, dim3(1), dim3(64), 0, s, band_exp, nv, band_exp + nv, band_exp + 2 * nv);
+  int *shift = band_exp + 4 * nv + nc;
+  hipLaunchKernelGGL(absmax_rows_kernel, dim3(nv + nc), dim3(ABS_THREADS), 0, s, psi_v, nv, psi_c, nr, scale, ldsc, nc,
+                     vmax, reinterpret_cast<float *>(shift));
+  hipLaunchKernelGGL(band_exponent_kernel, dim3(1), dim3(256), 0, s, vmax, nv, cmax, nc, band_exp, shift, band_exp + nv,
+                     band_exp + 2 * nv);
+  if (nv > ORDER_BANDS)
+    hipLaunchKernelGGL(band_order_kernel, dim3(1), dim3(64), 0, s, band_exp, nv, band_exp + nv, band_exp + 2 * nv);
   return hipGetLastError();
 }
 

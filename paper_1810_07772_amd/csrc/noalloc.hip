@@ -85,8 +85,7 @@ extern "C" int gw_polarizability_r_noalloc(gw_ctx *ctx, const gw_c32 *psi_v, int
   const int ldsc = scale_ld(nc);
   off += round256(scale_table_floats(nv, nc) * sizeof(float));
   int *bexp = o.precision == GW_SPLIT_FP16_SCALED ? reinterpret_cast<int *>(base + off) : nullptr;
-  GWX_HIP(ctx, hipMemcpyAsync(energy, e_v, (size_t)nv * sizeof(double), hipMemcpyHostToDevice, s));
-  GWX_HIP(ctx, hipMemcpyAsync(energy + nv, e_c, (size_t)nc * sizeof(double), hipMemcpyHostToDevice, s));
+  GWX_HIP(ctx, upload_energies(e_v, nv, e_c, nc, energy, s));
   GWX_HIP(ctx, launch_scale_table(energy, nv, energy + nv, nc, o.prefactor, scale, ldsc, s));
   if (bexp)
     GWX_HIP(ctx, launch_band_exponents((const float2 *)psi_v, nv, (const float2 *)psi_c, nc, nr, scale, ldsc, bexp, s));

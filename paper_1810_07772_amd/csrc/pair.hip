@@ -6,6 +6,8 @@
 // non-temporal stores, so many stores are in flight per thread and each wave writes 2 KB of a row of F
 // per band pair.  Chunks run fastest across the grid, so neighbouring workgroups write consecutive
 // stretches of the same rows of F.
+#include <algorithm>
+
 #include "gw_internal.h"
 
 namespace gwi {
@@ -23,6 +25,48 @@ __global__ void scale_table_kernel(const double *__restrict__ e_v, int nv, const
   const double q = c < nc ? prefactor / (e_c[c] - e_v[v]) : 0.0;
   scale[idx] = (float)sqrt(q);
   scale[(size_t)nv * ldsc + idx] = (float)q;
+}
+
+// Energies in the kernel's own arguments (a copy made at the launch): nothing on the host waits, whereas a copy
+// from pageable memory blocks until the stream has come to it, so back-to-back calls never overlapped with the
+// host (12 x 200 bands on 27^3: 139 us a call for an 88 us kernel).  ENERGY_ARG doubles fit beside the other
+// arguments into the 4 KB a launch takes; a longer list goes in several launches, and one of more than
+// ENERGY_LAUNCHES by a copy.
+constexpr int ENERGY_ARG = 496, ENERGY_LAUNCHES = 4;
+struct EnergyArg { double e[ENERGY_ARG]; };
+
+__global__ void energies_kernel(EnergyArg a, int n, double *__restrict__ out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = a.e[i];
+}
+
+static hipError_t upload_part(const double *e, int n, double *dst, hipStream_t s) {
+  EnergyArg a;
+  for (int i0 = 0; i0 < n; i0 += ENERGY_ARG) {
+    const int m = std::min(n - i0, ENERGY_ARG);
+    std::copy(e + i0, e + i0 + m, a.e);
+    hipLaunchKernelGGL(energies_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a, m, dst + i0);
+  }
+  return hipGetLastError();
+}
+
+// dev[0 .. nv) = e_v, dev[nv .. nv + nc) = e_c (host arrays, read before the call returns)
+hipError_t upload_energies(const double *e_v, int nv, const double *e_c, int nc, double *dev, hipStream_t s) {
+  const long long n = (long long)nv + nc;
+  if (n <= ENERGY_ARG) {
+    EnergyArg a;
+    std::copy(e_v, e_v + nv, a.e);
+    std::copy(e_c, e_c + nc, a.e + nv);
+    hipLaunchKernelGGL(energies_kernel, dim3(((int)n + 255) / 256), dim3(256), 0, s, a, (int)n, dev);
+    return hipGetLastError();
+  }
+  if (n <= (long long)ENERGY_ARG * ENERGY_LAUNCHES) {
+    const hipError_t e = upload_part(e_v, nv, dev, s);
+    return e != hipSuccess ? e : upload_part(e_c, nc, dev + nv, s);
+  }
+  const hipError_t e = hipMemcpyAsync(dev, e_v, (size_t)nv * sizeof(double), hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) return e;
+  return hipMemcpyAsync(dev + nv, e_c, (size_t)nc * sizeof(double), hipMemcpyHostToDevice, s);
 }
 
 hipError_t launch_scale_table(const double *e_v, int nv, const double *e_c, int nc, double prefactor, float *scale,
