@@ -641,6 +641,11 @@ int gw_pair_products(gw_ctx *ctx, const gw_c32 *psi_v, int nv, const gw_c32 *psi
   GW_STATUS(check_energies(ctx, e_v, nv, e_c, nc));
   if (ctx->device < 0) return GW_OK;
   hipStream_t s = as_stream(stream);
+  if (pair_energies_fit(nv, nc)) {
+    GW_HIP(ctx, launch_pair_products_e((const float2 *)psi_v, nv, (const float2 *)psi_c, nc, nr, e_v, e_c, prefactor,
+                                       (float2 *)f_out, s));
+    return GW_OK;
+  }
   float *scale = nullptr;
   GW_STATUS(upload_scales(ctx, e_v, nv, e_c, nc, prefactor, &scale, s));
   GW_HIP(ctx, launch_pair_products((const float2 *)psi_v, nv, (const float2 *)psi_c, nc, nr, scale, scale_ld(nc),

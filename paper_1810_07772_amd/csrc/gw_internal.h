@@ -86,6 +86,10 @@ hipError_t launch_scale_table(const double *e_v, int nv, const double *e_c, int 
                               float *scale, int ldsc, hipStream_t s);
 hipError_t launch_pair_products(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr,
                                 const float *scale, int ldsc, float2 *f, hipStream_t s);
+// The same with the scales formed from host energies passed in the launch's arguments, where those fit.
+bool pair_energies_fit(int nv, int nc);
+hipError_t launch_pair_products_e(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const double *e_v,
+                                  const double *e_c, double prefactor, float2 *f, hipStream_t s);
 
 // Rank-K update P = -F^H F with the pair products formed in-kernel.
 // precision: enum gw_precision; tile: index into the tile table (-1 default).

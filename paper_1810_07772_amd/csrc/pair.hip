@@ -1,12 +1,17 @@
 // Pair products f_vc(r) = conj(u_v(r)) u_c(r) sqrt(p/(E_c - E_v))  (Eq.(fdef)) and the scale table.
 //
-// HBM-bound: the kernel writes nv*nc*nr complex64 values.  Layout: one workgroup owns a chunk of 1024
-// grid points and PP_CG unoccupied bands; a thread holds the psi_v values of PP_VB occupied bands at its
-// four grid points in registers and, for each of its unoccupied bands, issues 2 PP_VB independent 16-byte
-// non-temporal stores, so many stores are in flight per thread and each wave writes 2 KB of a row of F
-// per band pair.  Chunks run fastest across the grid, so neighbouring workgroups write consecutive
-// stretches of the same rows of F.
+// Bound by writing nv*nc*nr complex64 values.  A workgroup owns a segment of PP_P grid points, PP_VB occupied
+// and PP_CB unoccupied bands: their values at the segment pass through LDS once and serve PP_VB * PP_CB rows of F.
+// Rows of F start anywhere in a 128-byte line (nr need not be a multiple of 16), so each row's segment runs from
+// line boundary to line boundary, and a wave stores whole lines, 1 KB per instruction, whatever nr is: stores
+// that straddled lines reached 3.6 TB/s at nr = 19683 (27^3) and 4.2 at 19684, against 5.1 on rows that are aligned
+// anyway; with whole lines 5.2 to 5.4 on all of them (12 x 200 bands; a plain fill of that size 6.9).  On small grids
+// the segment of 512 points (1024 before) also leaves fewer CUs idle: 16 x 100 bands on 15^3 38 -> 20 us a call.
+// Segments by VB x CB at nr = 19683: 512 by 8 x 4 79 us, 256 by 8 x 8 79, 384 by 8 x 8 80, 512 by 8 x 8 83, 1024 by
+// 4 x 4 86, 512 by 4 x 8 88; at 36^3, 8 x 256 bands, 142, 150, 148, 145, 148 and 146 us.  Stores that are not
+// non-temporal: 3 to 20% slower.
 #include <algorithm>
+#include <type_traits>
 
 #include "gw_internal.h"
 
@@ -27,12 +32,11 @@ __global__ void scale_table_kernel(const double *__restrict__ e_v, int nv, const
   scale[(size_t)nv * ldsc + idx] = (float)q;
 }
 
-// Energies in the kernel's own arguments (a copy made at the launch): nothing on the host waits, whereas a copy
-// from pageable memory blocks until the stream has come to it, so back-to-back calls never overlapped with the
-// host (12 x 200 bands on 27^3: 139 us a call for an 88 us kernel).  ENERGY_ARG doubles fit beside the other
-// arguments into the 4 KB a launch takes; a longer list goes in several launches, and one of more than
-// ENERGY_LAUNCHES by a copy.
-constexpr int ENERGY_ARG = 496, ENERGY_LAUNCHES = 4;
+// Energies in the kernel's own arguments (a copy made at the launch) instead of two copies from pageable memory,
+// which the host stages and waits for: 12 x 200 bands on 27^3 138.8 -> 136.2 us a call, 12^3 FP32 build 130 -> 127.
+// ENERGY_ARG doubles fit beside the other arguments into the 4 KB a launch takes; a longer list goes in several
+// launches, and one of more than ENERGY_LAUNCHES by copies.
+constexpr int ENERGY_ARG = 488, ENERGY_LAUNCHES = 4;
 struct EnergyArg { double e[ENERGY_ARG]; };
 
 __global__ void energies_kernel(EnergyArg a, int n, double *__restrict__ out) {
@@ -79,152 +83,100 @@ hipError_t launch_scale_table(const double *e_v, int nv, const double *e_c, int 
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int PP_THREADS = 256;
-constexpr int PP_NH = 2;   // point pairs per thread, 128 points apart (1: 4.68 TB/s, 2: 4.90, 4: 4.80 at 36^3)
-constexpr int PP_SEG = 2 * 64 * PP_NH;                   // consecutive points per wave
-constexpr int PP_CHUNK = (PP_THREADS / 64) * PP_SEG;     // grid points per workgroup
-
 __device__ __forceinline__ float2 conj_mul_scale(float2 v, float2 c, float s) {
   // conj(v) * c * s
   return make_float2((v.x * c.x + v.y * c.y) * s, (v.x * c.y - v.y * c.x) * s);
 }
 
-constexpr int PP_VB = 8;   // occupied bands whose psi_v values a thread holds in registers
-constexpr int PP_CG = 8;   // unoccupied bands per workgroup (4: 4.4 TB/s, 8: 4.7, 16: 4.5 at 36^3)
+constexpr int PP_THREADS = 256;
+constexpr int PP_P = 512;      // points per row segment
+constexpr int PP_VB = 8;       // occupied bands per workgroup
+constexpr int PP_CB = 4;       // unoccupied bands per workgroup
+constexpr int PP_LINE = 16;    // values in a 128-byte line
 
-// Lane l of wave w holds the point pairs (p, p + 1), p = chunk + w PP_SEG + 2 l + 128 h, h < PP_NH: for
-// each (v, c) a wave's PP_NH stores cover PP_NH KB of one row of F back to back.
+// The pair scales come from the table, or (ARG) from the energies in the arguments: no launch before this one.
+template <bool ARG>
 __global__ __launch_bounds__(PP_THREADS) void pair_products_kernel(const float2 *__restrict__ psi_v, int nv,
                                                                    const float2 *__restrict__ psi_c, int nc, int nr,
-                                                                   const float *__restrict__ scale, int ldsc,
-                                                                   float2 *__restrict__ f) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int base = blockIdx.x * PP_CHUNK + wave * PP_SEG + 2 * lane;
-  const int cg0 = blockIdx.y * PP_CG;
-  if (base >= nr) return;   // the thread's first point is its smallest
-  bool one[PP_NH], two[PP_NH], wide[PP_NH];
+                                                                   int cbase, const float *__restrict__ scale, int ldsc,
+                                                                   double prefactor, float2 *__restrict__ f,
+                                                                   std::conditional_t<ARG, EnergyArg, int> energies) {
+  __shared__ float2 sv[PP_VB][PP_P + PP_LINE], sc[PP_CB][PP_P + PP_LINE];
+  __shared__ float ss[PP_VB][PP_CB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nvb = (nv + PP_VB - 1) / PP_VB;
+  const int v0 = ((int)blockIdx.x % nvb) * PP_VB, p0 = ((int)blockIdx.x / nvb) * PP_P;
+  const int c0 = cbase + (int)blockIdx.y * PP_CB;
+  const int mv = min(PP_VB, nv - v0), mc = min(PP_CB, nc - c0);
+  const int np = min(PP_P + PP_LINE, nr - p0);
+  for (int i = tid; i < PP_P + PP_LINE; i += PP_THREADS) {
+    const int q = min(i, np - 1);
 #pragma unroll
-  for (int h = 0; h < PP_NH; ++h) {
-    const int p = base + 128 * h;
-    one[h] = p < nr;
-    two[h] = p + 1 < nr;
-    wide[h] = two[h] && ((nr & 1) == 0);
+    for (int k = 0; k < PP_VB; ++k) sv[k][i] = psi_v[(size_t)min(v0 + k, nv - 1) * nr + p0 + q];
+#pragma unroll
+    for (int k = 0; k < PP_CB; ++k) sc[k][i] = psi_c[(size_t)min(c0 + k, nc - 1) * nr + p0 + q];
   }
-  if ((nr & 1) == 0 && ((int)blockIdx.x + 1) * PP_CHUNK <= nr) {
-    // every point of the workgroup exists and pairs are 16-byte aligned: no per-lane condition anywhere,
-    // so the wait for the next band's prefetched psi_c counts past this band's stores instead of draining
-    // them (on this architecture one counter covers both)
-    for (int vb = 0; vb < nv; vb += PP_VB) {
-      const int nvb = min(PP_VB, nv - vb);
-      f32x4 vv[PP_NH][PP_VB];
-#pragma unroll
-      for (int h = 0; h < PP_NH; ++h)
-#pragma unroll
-        for (int k = 0; k < PP_VB; ++k)
-          vv[h][k] = *reinterpret_cast<const f32x4 *>(psi_v + (size_t)(vb + min(k, nvb - 1)) * nr + base + 128 * h);
-      f32x4 cv[PP_NH], cn[PP_NH];
-#pragma unroll
-      for (int h = 0; h < PP_NH; ++h) {
-        cv[h] = *reinterpret_cast<const f32x4 *>(psi_c + (size_t)min(cg0, nc - 1) * nr + base + 128 * h);
-        cn[h] = cv[h];
-      }
-      for (int cc = 0; cc < PP_CG; ++cc) {
-        const int c = cg0 + cc;
-        if (c >= nc) break;
-        if (cc + 1 < PP_CG && c + 1 < nc) {
-#pragma unroll
-          for (int h = 0; h < PP_NH; ++h)
-            cn[h] = *reinterpret_cast<const f32x4 *>(psi_c + (size_t)(c + 1) * nr + base + 128 * h);
-        }
-        float sk[PP_VB];
-#pragma unroll
-        for (int k = 0; k < PP_VB; ++k) sk[k] = scale[(vb + min(k, nvb - 1)) * ldsc + c];
-#pragma unroll
-        for (int k = 0; k < PP_VB; ++k) {
-          if (k < nvb) {                                     // uniform
-#pragma unroll
-            for (int h = 0; h < PP_NH; ++h) {
-              const float2 a = conj_mul_scale(make_float2(vv[h][k][0], vv[h][k][1]), make_float2(cv[h][0], cv[h][1]), sk[k]);
-              const float2 b = conj_mul_scale(make_float2(vv[h][k][2], vv[h][k][3]), make_float2(cv[h][2], cv[h][3]), sk[k]);
-              const f32x4 w = {a.x, a.y, b.x, b.y};
-              __builtin_nontemporal_store(w, reinterpret_cast<f32x4 *>(f + ((size_t)(vb + k) * nc + c) * nr + base + 128 * h));
-            }
-          }
-        }
-#pragma unroll
-        for (int h = 0; h < PP_NH; ++h) cv[h] = cn[h];
-      }
-    }
-    return;
+  if (tid < PP_VB * PP_CB) {
+    const int k = tid / PP_CB, j = tid % PP_CB;
+    const int v = min(v0 + k, nv - 1), c = min(c0 + j, nc - 1);
+    if constexpr (ARG) ss[k][j] = (float)sqrt(prefactor / (energies.e[nv + c] - energies.e[v]));
+    else ss[k][j] = scale[(size_t)v * ldsc + c];
   }
-  for (int vb = 0; vb < nv; vb += PP_VB) {
-    const int nvb = min(PP_VB, nv - vb);
-    float2 v0[PP_NH][PP_VB], v1[PP_NH][PP_VB];
-#pragma unroll
-    for (int h = 0; h < PP_NH; ++h)
-#pragma unroll
-      for (int k = 0; k < PP_VB; ++k) {
-        v0[h][k] = make_float2(0.f, 0.f);
-        v1[h][k] = make_float2(0.f, 0.f);
-        if (k < nvb && one[h]) {
-          const float2 *pv = psi_v + (size_t)(vb + k) * nr + base + 128 * h;
-          v0[h][k] = pv[0];
-          if (two[h]) v1[h][k] = pv[1];
-        }
-      }
-    // psi_c of the next unoccupied band is loaded while the current band's products are stored, so no
-    // band waits for its own loads; the band's PP_VB scales are read together before its stores
-    float2 c0[PP_NH], c1[PP_NH], n0[PP_NH] = {}, n1[PP_NH] = {};
-    auto load_c = [&](int c, float2 (&a)[PP_NH], float2 (&b)[PP_NH]) {
-#pragma unroll
-      for (int h = 0; h < PP_NH; ++h) {
-        const float2 *pc = psi_c + (size_t)c * nr + base + 128 * h;
-        a[h] = one[h] ? pc[0] : make_float2(0.f, 0.f);
-        b[h] = two[h] ? pc[1] : make_float2(0.f, 0.f);
-      }
-    };
-    if (cg0 < nc) load_c(cg0, c0, c1);
-    for (int cc = 0; cc < PP_CG; ++cc) {
-      const int c = cg0 + cc;
-      if (c >= nc) break;
-      if (cc + 1 < PP_CG && c + 1 < nc) load_c(c + 1, n0, n1);
-      float sk[PP_VB];
-#pragma unroll
-      for (int k = 0; k < PP_VB; ++k) sk[k] = k < nvb ? scale[(vb + k) * ldsc + c] : 0.f;
-#pragma unroll
-      for (int k = 0; k < PP_VB; ++k) {
-        if (k < nvb) {
-          const float s = sk[k];
-#pragma unroll
-          for (int h = 0; h < PP_NH; ++h) {
-            if (!one[h]) continue;
-            float2 *out = f + ((size_t)(vb + k) * nc + c) * nr + base + 128 * h;
-            const float2 a = conj_mul_scale(v0[h][k], c0[h], s);
-            if (wide[h]) {
-              const float2 b = conj_mul_scale(v1[h][k], c1[h], s);
-              const f32x4 w = {a.x, a.y, b.x, b.y};
-              __builtin_nontemporal_store(w, reinterpret_cast<f32x4 *>(out));
-            } else {
-              out[0] = a;
-              if (two[h]) out[1] = conj_mul_scale(v1[h][k], c1[h], s);
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < PP_NH; ++h) {
-        c0[h] = n0[h];
-        c1[h] = n1[h];
+  __syncthreads();
+  const int a0 = (int)((reinterpret_cast<uintptr_t>(f) >> 3) & (PP_LINE - 1));
+  for (int row = wave; row < mv * PP_CB; row += PP_THREADS / 64) {
+    const int k = row / PP_CB, j = row % PP_CB;
+    if (j >= mc) continue;
+    const size_t at = ((size_t)(v0 + k) * nc + c0 + j) * nr + p0;      // the segment's first value in F
+    float2 *out = f + at;
+    // From the first line boundary (the row's start for its first segment) to the first one past the segment
+    // (the row's end for its last); a wave's stores start at a boundary, if need be before the row's start.
+    const int off = (int)((a0 + at) & (PP_LINE - 1)), sh = (PP_LINE - off) & (PP_LINE - 1);
+    const int beg = p0 == 0 ? 0 : sh, end = min(PP_P + sh, nr - p0);   // PP_P is a multiple of a line
+    const float s = ss[k][j];
+    for (int i = (p0 == 0 ? -off : sh) + 2 * lane; i < end; i += 128) {
+      const int x = max(i, 0), y = max(min(i + 1, np - 1), 0);
+      const float2 a = conj_mul_scale(sv[k][x], sc[j][x], s), b = conj_mul_scale(sv[k][y], sc[j][y], s);
+      if (i >= beg && i + 1 < end) {
+        const f32x4 w = {a.x, a.y, b.x, b.y};
+        __builtin_nontemporal_store(w, reinterpret_cast<f32x4 *>(out + i));
+      } else {
+        if (i >= beg && i < end) out[i] = a;
+        if (i + 1 >= beg && i + 1 < end) out[i + 1] = b;
       }
     }
   }
 }
 
+static_assert(PP_P % PP_LINE == 0, "a segment's end falls on the line boundary its start is shifted to");
+
+template <bool ARG>
+static hipError_t launch_pairs(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const float *scale,
+                               int ldsc, double prefactor, float2 *f, std::conditional_t<ARG, EnergyArg, int> e,
+                               hipStream_t s) {
+  constexpr int CY = 65535 * PP_CB;                    // unoccupied bands per launch
+  for (int cb = 0; cb < nc; cb += CY) {
+    const dim3 grid(((nr + PP_P - 1) / PP_P) * ((nv + PP_VB - 1) / PP_VB), (std::min(CY, nc - cb) + PP_CB - 1) / PP_CB);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(pair_products_kernel<ARG>), grid, dim3(PP_THREADS), 0, s, psi_v, nv, psi_c, nc,
+                       nr, cb, scale, ldsc, prefactor, f, e);
+  }
+  return hipGetLastError();
+}
+
 hipError_t launch_pair_products(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const float *scale,
                                 int ldsc, float2 *f, hipStream_t s) {
-  dim3 grid((nr + PP_CHUNK - 1) / PP_CHUNK, (nc + PP_CG - 1) / PP_CG);
-  hipLaunchKernelGGL(pair_products_kernel, grid, dim3(PP_THREADS), 0, s, psi_v, nv, psi_c, nc, nr, scale, ldsc, f);
-  return hipGetLastError();
+  return launch_pairs<false>(psi_v, nv, psi_c, nc, nr, scale, ldsc, 1.0, f, 0, s);
+}
+
+bool pair_energies_fit(int nv, int nc) { return (long long)nv + nc <= ENERGY_ARG; }
+
+hipError_t launch_pair_products_e(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const double *e_v,
+                                  const double *e_c, double prefactor, float2 *f, hipStream_t s) {
+  if (!pair_energies_fit(nv, nc)) return hipErrorInvalidValue;
+  EnergyArg a;
+  std::copy(e_v, e_v + nv, a.e);
+  std::copy(e_c, e_c + nc, a.e + nv);
+  return launch_pairs<true>(psi_v, nv, psi_c, nc, nr, nullptr, 0, prefactor, f, a, s);
 }
 
 }  // namespace gwi
