@@ -19,22 +19,31 @@ namespace gwi {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int GT = 64;    // output tile
-constexpr int GK = 4;     // complex k per stage (8: 2% slower for the inverse at N = 4067, 16: 18% slower)
+// Two shapes of the product kernel: 64 x 64 tiles with 4 complex k per stage (16 KB of LDS, four workgroups per CU; 8
+// complex k per stage: 2% slower for the inverse at N = 4067, 16: 18% slower) for outputs that fill the chip, and
+// 32 x 32 tiles with 16 complex k per stage where they do not: four times the workgroups, and a stage long enough
+// to cover the next one's loads on a CU that holds a single workgroup.
+template <int GT> struct ZgShape;
+template <> struct ZgShape<64> { static constexpr int GK = 4, WGS = 4; };
+template <> struct ZgShape<32> { static constexpr int GK = 16, WGS = 3; };
 
-// The second product of a combined launch (lower_only == 3): same A, K, alpha, beta and leading
-// dimensions, its own B, C and column count, over a full grid of tiles numbered after the first
-// product's ntile1 lower tiles.
+// The second product of a combined launch (lower_only == 3): same A, K, alpha, beta and leading dimension of C, its
+// own B (leading dimension ldb), C and column count, over a full grid of tiles numbered after the first product's
+// ntile1 lower tiles.
 struct Zg2 {
   const double2 *B;
   double2 *C;
+  long long ldb;
   int transB, N, ntile1;
 };
 
-__global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, const double2 *__restrict__ A, long long lda,
-                                                    int transA, const double2 *__restrict__ B, long long ldb,
-                                                    int transB, double2 *__restrict__ C, long long ldc, double alpha,
-                                                    double beta, int lower_only, int tri_k, Zg2 z2) {
+template <int GT>
+__global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int N, int K, const double2 *__restrict__ A,
+                                                    long long lda, int transA, const double2 *__restrict__ B,
+                                                    long long ldb, int transB, double2 *__restrict__ C, long long ldc,
+                                                    double alpha, double beta, int lower_only, int tri_k, Zg2 z2) {
+  constexpr int GK = ZgShape<GT>::GK, RB = GT / 32;     // 16 x 16 blocks per wave and side
+  constexpr int LP = GT == 64 ? 64 : 36;                // LDS row stride
   // lower_only == 2: a square product over a one-dimensional grid of its lower tiles only, numbered row
   // by row (t = r (r + 1) / 2 + c), so consecutive workgroups, which the dispatcher deals out to the XCDs
   // in turn, carry equal work and no workgroup is launched for an upper tile
@@ -45,6 +54,7 @@ __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, cons
     col0 = (t % nct) * GT;
     B = z2.B;
     C = z2.C;
+    ldb = z2.ldb;
     transB = z2.transB;
     N = z2.N;
   } else if (lower_only >= 2) {
@@ -59,17 +69,16 @@ __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, cons
     col0 = blockIdx.x * GT;
   }
   const int kend = K;
-  if (lower_only == 1 && col0 >= row0 + GT) return;
   // two LDS stages: the global loads of stage k+1 are in flight in registers while stage k's MFMAs run
-  __shared__ double sA[2][GK][2][GT];
-  __shared__ double sX[2][GK][2][GT];   // [Re B; -Im B]; the [Im B; Re B] operand is read from it
+  __shared__ double sA[2][GK][2][LP];
+  __shared__ double sX[2][GK][3][LP];   // planes Re B, -Im B, Im B: [Re B; -Im B] is planes 0, 1, [Im B; Re B] 2, 0
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int wr = wave >> 1, wc = wave & 1;
-  f64x4 accR[2][2], accI[2][2];
+  f64x4 accR[RB][RB], accI[RB][RB];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < RB; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < RB; ++b)
 #pragma unroll
       for (int e = 0; e < 4; ++e) { accR[a][b][e] = 0.0; accI[a][b][e] = 0.0; }
 
@@ -132,6 +141,7 @@ __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, cons
       pb[it] += step_b;
     }
   };
+  const double sa = transA ? -1.0 : 1.0, sb = transB ? -1.0 : 1.0;
   auto lstore = [&](int buf) {
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
@@ -139,54 +149,76 @@ __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, cons
       int r, c, kk;
       a_coord(idx, r, kk);
       sA[buf][kk][0][r] = va[it].x;
-      sA[buf][kk][1][r] = transA ? -va[it].y : va[it].y;
+      sA[buf][kk][1][r] = sa * va[it].y;
       b_coord(idx, c, kk);
-      const double by = transB ? -vb[it].y : vb[it].y;
+      const double by = sb * vb[it].y;
       sX[buf][kk][0][c] = vb[it].x;
       sX[buf][kk][1][c] = -by;
+      sX[buf][kk][2][c] = by;
     }
   };
-  int buf = 0;
+  // operands of one step of two complex k
+  struct Ops { double a[RB], x[RB], y[RB]; };
+  const int comp = kl & 1, kh = kl >> 1, yp = comp ? 0 : 2;
+  const int ar = wr * 16 * RB + li, bc = wc * 16 * RB + li;
+  auto rd = [&](int buf, int s) {
+    const int kk = 2 * s + kh;
+    Ops o;
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      o.a[i] = sA[buf][kk][comp][ar + 16 * i];
+      o.x[i] = sX[buf][kk][comp][bc + 16 * i];
+      o.y[i] = sX[buf][kk][yp][bc + 16 * i];
+    }
+    return o;
+  };
+  auto mul = [&](const Ops &o) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int j = 0; j < RB; ++j) {
+        accR[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[i], o.x[j], accR[i][j], 0, 0, 0);
+        accI[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[i], o.y[j], accI[i][j], 0, 0, 0);
+      }
+  };
+  // Each step's operands are read from LDS during the step before, and the barrier stands before a stage's last
+  // step, so LDS latency and the wait for the other waves pass while MFMAs run.  Once a wave passes the
+  // barrier of stage k every wave has the stage's operands in registers, so stage k + 1 may refill its buffer.
   if (kbeg < kend) {
     gload(kbeg);
     lstore(0);
   }
   __syncthreads();
-  for (int k0 = kbeg; k0 < kend; k0 += GK) {
+  Ops cur = rd(0, 0);
+  auto stage = [&](int k0, auto bufc) {
+    constexpr int buf = decltype(bufc)::value;
     const bool more = k0 + GK < kend;
     if (more) gload(k0 + GK);
 #pragma unroll
-    for (int s = 0; s < GK / 2; ++s) {
-      const int kk = 2 * s + (kl >> 1), comp = kl & 1;
-      const double a0 = sA[buf][kk][comp][wr * 32 + li], a1 = sA[buf][kk][comp][wr * 32 + 16 + li];
-      const double x0 = sX[buf][kk][comp][wc * 32 + li], x1 = sX[buf][kk][comp][wc * 32 + 16 + li];
-      // Y = [Im B; Re B] = [-X_1; X_0]: the sign flip of the comp = 0 lanes as one xor of the high word
-      const double ys0 = sX[buf][kk][comp ^ 1][wc * 32 + li], ys1 = sX[buf][kk][comp ^ 1][wc * 32 + 16 + li];
-      const unsigned long long flip = comp ? 0ull : 0x8000000000000000ull;
-      const double y0 = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, ys0) ^ flip);
-      const double y1 = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, ys1) ^ flip);
-      accR[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, x0, accR[0][0], 0, 0, 0);
-      accI[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, y0, accI[0][0], 0, 0, 0);
-      accR[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, x1, accR[0][1], 0, 0, 0);
-      accI[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, y1, accI[0][1], 0, 0, 0);
-      accR[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, x0, accR[1][0], 0, 0, 0);
-      accI[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, y0, accI[1][0], 0, 0, 0);
-      accR[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, x1, accR[1][1], 0, 0, 0);
-      accI[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, y1, accI[1][1], 0, 0, 0);
+    for (int st = 0; st + 1 < GK / 2; ++st) {
+      const Ops next = rd(buf, st + 1);
+      mul(cur);
+      cur = next;
     }
     if (more) lstore(buf ^ 1);
     __syncthreads();
-    buf ^= 1;
+    const Ops last = cur;
+    if (more) cur = rd(buf ^ 1, 0);
+    mul(last);
+  };
+  for (int k0 = kbeg; k0 < kend; k0 += 2 * GK) {
+    stage(k0, std::integral_constant<int, 0>{});
+    if (k0 + GK < kend) stage(k0 + GK, std::integral_constant<int, 1>{});
   }
   // lane holds D[i][j] of each 16x16 block in register e with i = 4*e + (lane>>4), j = lane & 15
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
+  for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb)
+    for (int cb = 0; cb < RB; ++cb)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int row = row0 + wr * 32 + rb * 16 + 4 * e + kl;
-        const int col = col0 + wc * 32 + cb * 16 + li;
+        const int row = row0 + wr * 16 * RB + rb * 16 + 4 * e + kl;
+        const int col = col0 + wc * 16 * RB + cb * 16 + li;
         if (row < M && col < N) {
           double2 *d = C + (long long)row * ldc + col;
           double2 v = make_double2(alpha * accR[rb][cb][e], alpha * accI[rb][cb][e]);
@@ -196,32 +228,62 @@ __global__ __launch_bounds__(256, 4) void zgemm_kernel(int M, int N, int K, cons
       }
 }
 
+// Tile side for a product of `tiles` 64 x 64 tiles.  Small tiles win while four times as many still find a place at
+// once (three per CU), and further for short K, where a 64 x 64 tile's prologue and store are most of its time, and
+// for X^H X, whose tiles are of uneven length.  Inverse, us, 64 only -> this rule: N = 100 154 -> 140, 147 212 -> 181,
+// 410 523 -> 434, 925 1147 -> 961, 1500 1900 -> 1680, 2109 2916 -> 2734, 3071 5139 -> 5097; with small tiles for every
+// product below 1000 (all): 3071 5178 (5334), 4067 9768 against 8660 (all), and 925 x 925 products of the Newton
+// iteration (225 tiles, K = 925) 5.96 ms against 5.20.
+static int zg_tile(long long tiles, int K, int tri_k) {
+  return tiles < (tri_k ? 400 : K <= 256 ? 600 : 192) ? 32 : 64;
+}
+
+template <int GT>
+static hipError_t zgemm_t(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
+                          long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
+                          int lower_only, int tri_k, hipStream_t s) {
+  if (lower_only) {
+    const long long nt = (N + GT - 1) / GT;
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT>), dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, M, N, K,
+                       A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, 2, tri_k, Zg2{});
+    return hipGetLastError();
+  }
+  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT>), grid, dim3(256), 0, s, M, N, K, A, lda, transA, B, ldb, transB,
+                     C, ldc, alpha, beta, 0, tri_k, Zg2{});
+  return hipGetLastError();
+}
+
+// lower_only: a square product, its lower tiles only
 static hipError_t zgemm(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
                         long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
                         int lower_only, int tri_k, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (lower_only && M == N) {
-    const long long nt = (N + GT - 1) / GT;
-    hipLaunchKernelGGL(zgemm_kernel, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, M, N, K, A, lda, transA, B,
-                       ldb, transB, C, ldc, alpha, beta, 2, tri_k, Zg2{});
-    return hipGetLastError();
-  }
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
-  hipLaunchKernelGGL(zgemm_kernel, grid, dim3(256), 0, s, M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha,
-                     beta, lower_only, tri_k, Zg2{});
-  return hipGetLastError();
+  const long long mt = (M + 63) / 64, nt = (N + 63) / 64, tiles = lower_only ? nt * (nt + 1) / 2 : mt * nt;
+  return zg_tile(tiles, K, tri_k) == 32 ? zgemm_t<32>(M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, lower_only, tri_k, s)
+                              : zgemm_t<64>(M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, lower_only, tri_k, s);
 }
 
 // C1 = alpha A B1^H + beta C1 on the lower tiles of the square M x M C1, and C2 = alpha A B2 + beta C2 on
-// all tiles of the M x N2 C2, in one launch (both operands B row-major with leading dimension ldb)
-static hipError_t zgemm_lower_and_full(int M, int N2, int K, const double2 *A, long long lda, const double2 *B1,
-                                       double2 *C1, const double2 *B2, double2 *C2, long long ldb, long long ldc,
-                                       double alpha, double beta, hipStream_t s) {
-  if (M <= 0) return hipSuccess;
+// all tiles of the M x N2 C2, in one launch
+template <int GT>
+static hipError_t zgemm_lower_and_full_t(int M, int N2, int K, const double2 *A, long long lda, const double2 *B1,
+                                         long long ldb1, double2 *C1, const double2 *B2, long long ldb2, double2 *C2,
+                                         long long ldc, double alpha, double beta, hipStream_t s) {
   const long long nt = (M + GT - 1) / GT, nt1 = nt * (nt + 1) / 2, nt2 = N2 > 0 ? nt * ((N2 + GT - 1) / GT) : 0;
-  hipLaunchKernelGGL(zgemm_kernel, dim3((unsigned)(nt1 + nt2)), dim3(256), 0, s, M, M, K, A, lda, 0, B1, ldb, 1, C1,
-                     ldc, alpha, beta, 3, 0, Zg2{B2, C2, 0, N2, (int)nt1});
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT>), dim3((unsigned)(nt1 + nt2)), dim3(256), 0, s, M, M, K, A, lda, 0,
+                     B1, ldb1, 1, C1, ldc, alpha, beta, 3, 0, Zg2{B2, C2, ldb2, 0, N2, (int)nt1});
   return hipGetLastError();
+}
+
+static hipError_t zgemm_lower_and_full(int M, int N2, int K, const double2 *A, long long lda, const double2 *B1,
+                                       long long ldb1, double2 *C1, const double2 *B2, long long ldb2, double2 *C2,
+                                       long long ldc, double alpha, double beta, hipStream_t s) {
+  if (M <= 0) return hipSuccess;
+  const long long nt = (M + 63) / 64, tiles = nt * (nt + 1) / 2 + nt * ((N2 + 63) / 64);
+  return zg_tile(tiles, K, 0) == 32
+             ? zgemm_lower_and_full_t<32>(M, N2, K, A, lda, B1, ldb1, C1, B2, ldb2, C2, ldc, alpha, beta, s)
+             : zgemm_lower_and_full_t<64>(M, N2, K, A, lda, B1, ldb1, C1, B2, ldb2, C2, ldc, alpha, beta, s);
 }
 
 hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
@@ -257,8 +319,9 @@ __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, J..
   (f(std::integral_constant<int, J>{}), ...);
 }
 
+// L is the panel buffer: row i of the panel's columns at L + i ldl
 __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *__restrict__ A, int n, int p0,
-                                                                int k0, double2 *__restrict__ L,
+                                                                int k0, double2 *__restrict__ L, int ldl,
                                                                 double2 *__restrict__ linv, int *__restrict__ pivot) {
   __shared__ double2 a[NB][NB + 1];
   // L[k0 + i][p0 + k] (the block's rows, the panel's earlier columns) and the same columns of this
@@ -299,9 +362,9 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
     for (int q = 0; q < (CHOL_PW - NB) / NB; ++q) {
       if (NB * q < kp) {                                     // column k = pj + NB q; rows pib and pib + PR
         const int k = pj + NB * q;
-        const double2 u = pib < nb ? L[(size_t)(k0 + pib) * n + p0 + k] : make_double2(0.0, 0.0);
-        const double2 w = pib + PR < nb ? L[(size_t)(k0 + pib + PR) * n + p0 + k] : make_double2(0.0, 0.0);
-        const double2 v = r0 + pib < n ? L[(size_t)(r0 + pib) * n + p0 + k] : make_double2(0.0, 0.0);
+        const double2 u = pib < nb ? L[(size_t)(k0 + pib) * ldl + k] : make_double2(0.0, 0.0);
+        const double2 w = pib + PR < nb ? L[(size_t)(k0 + pib + PR) * ldl + k] : make_double2(0.0, 0.0);
+        const double2 v = r0 + pib < n ? L[(size_t)(r0 + pib) * ldl + k] : make_double2(0.0, 0.0);
         lbp[k][0][pib] = u.x;
         lbp[k][1][pib] = u.y;
         lbp[k][0][pib + PR] = w.x;
@@ -435,7 +498,7 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
   if (blockIdx.x == 0) {
     for (int idx = tid; idx < NB * NB; idx += PD_THREADS) {
       const int i = idx / NB, j = idx % NB;
-      if (i < nb && j < nb) L[(size_t)(k0 + i) * n + k0 + j] = (j <= i) ? a[i][j] : make_double2(0.0, 0.0);
+      if (i < nb && j < nb) L[(size_t)(k0 + i) * ldl + kp + j] = (j <= i) ? a[i][j] : make_double2(0.0, 0.0);
       linv[idx] = (i < nb && j < nb) ? x[i][j] : make_double2(0.0, 0.0);
     }
     if (tid == 0 && bad != 0 && *pivot == 0) *pivot = bad;
@@ -451,7 +514,7 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
     acc.x += av.x * v.x + av.y * v.y;
     acc.y += av.y * v.x - av.x * v.y;
   }
-  if (r0 + pib < n && pj < nb) L[(size_t)(r0 + pib) * n + k0 + pj] = acc;
+  if (r0 + pib < n && pj < nb) L[(size_t)(r0 + pib) * ldl + kp + pj] = acc;
 }
 
 __global__ void fill_identity_kernel(double2 *__restrict__ a, int n, double diag) {
@@ -496,7 +559,7 @@ constexpr int SUB_CW = 8;      // columns per workgroup
 constexpr int SUB_RS = 256 / SUB_CW;   // row stride of a thread's rows in a 32-row block
 
 __global__ __launch_bounds__(256) void subst_panel_kernel(const double2 *__restrict__ B, const double2 *__restrict__ L,
-                                                          const double2 *__restrict__ linv_all,
+                                                          int ldl, const double2 *__restrict__ linv_all,
                                                           double2 *__restrict__ X, int n, int p0, int p1) {
   __shared__ double2 sB[CHOL_PW][SUB_CW + 1];
   __shared__ double2 sM[NB][NB + 1];   // Linv_kk, then one L_ik block at a time
@@ -519,7 +582,7 @@ __global__ __launch_bounds__(256) void subst_panel_kernel(const double2 *__restr
       if (j0 < 0)
         pf[t] = linv_all[(size_t)(k0 / NB) * NB * NB + idx];
       else
-        pf[t] = (i < jn && m < nb) ? L[(size_t)(j0 + i) * n + k0 + m] : make_double2(0.0, 0.0);
+        pf[t] = (i < jn && m < nb) ? L[(size_t)(j0 + i) * ldl + k0 - p0 + m] : make_double2(0.0, 0.0);
     }
   };
   auto commit = [&]() {
@@ -597,6 +660,11 @@ __global__ __launch_bounds__(256) void subst_panel_kernel(const double2 *__restr
   }
 }
 
+// L is needed one panel of columns at a time: rows of CHOL_PW values, aligned to memory lines whatever n is.  (With
+// the n x n factor at n = 4067, whose rows of 65072 bytes start anywhere in a line, the products' 64-byte runs of
+// L touched half as many lines again.)
+size_t chol_panel_elems(int n) { return (size_t)n * std::min(n, CHOL_PW); }
+
 size_t chol_small_bytes(int n) {
   const int nblk = (n + NB - 1) / NB;
   return (size_t)nblk * NB * NB * sizeof(double2);
@@ -609,12 +677,8 @@ hipError_t hpd_inverse(double2 *a, int n, double2 *l, double2 *x, double2 *small
   const size_t nn = (size_t)n * n;
   const unsigned fill_blocks = (unsigned)((nn + 255) / 256);
   GW_TRY(launch_fill_int(pivot_dev, 0, s));
-  hipLaunchKernelGGL(fill_identity_kernel, dim3(fill_blocks), dim3(256), 0, s, l, n, 0.0);
-  GW_TRY(hipGetLastError());
   // the substitution's right-hand side B = I lives in out until X^H X overwrites it
   hipLaunchKernelGGL(fill_identity_kernel, dim3(fill_blocks), dim3(256), 0, s, out, n, 1.0);
-  GW_TRY(hipGetLastError());
-  hipLaunchKernelGGL(fill_identity_kernel, dim3(fill_blocks), dim3(256), 0, s, x, n, 0.0);
   GW_TRY(hipGetLastError());
   // Panels of PW columns, factorisation and substitution interleaved.  Inside a panel each NB-wide step of
   // the factorisation first applies the panel's earlier columns to its own (left-looking, inside the
@@ -626,6 +690,7 @@ hipError_t hpd_inverse(double2 *a, int n, double2 *l, double2 *x, double2 *small
   // (A look-ahead that moved each panel's trailing product to a second stream, so that the next panel's
   // chain could start at once, measured slower at N = 4067: the product's workgroups fill the CUs the
   // chain's small launches wait for.)
+  const int ldl = std::min(n, CHOL_PW);
   constexpr int PW = CHOL_PW;   // 128, 256 and 512 measured alike; 32 (no panels) 5% slower at N = 4067
   for (int p0 = 0; p0 < n; p0 += PW) {
     const int p1 = min(n, p0 + PW);
@@ -635,19 +700,20 @@ hipError_t hpd_inverse(double2 *a, int n, double2 *l, double2 *x, double2 *small
       double2 *linv = small + (size_t)kb * NB * NB;
       // the diagonal block and, in the same launch, the panel column L[k0+nb:, k0:k0+nb] = A Linv^H
       hipLaunchKernelGGL(potrf_diag_kernel, dim3(std::max(1, (rest + PR - 1) / PR)), dim3(PD_THREADS), 0, s, a, n, p0,
-                         k0, l, linv, pivot_dev);
+                         k0, l, ldl, linv, pivot_dev);
       GW_TRY(hipGetLastError());
     }
-    // 2. the panel's rows of X (columns < p1; X is zero beyond), all 32-row steps in one launch
-    hipLaunchKernelGGL(subst_panel_kernel, dim3((p1 + SUB_CW - 1) / SUB_CW), dim3(256), 0, s, out, l, small, x, n, p0,
+    // 2. the panel's rows of X (columns < p1; beyond them X is zero, never read and not written), all 32-row
+    // steps in one launch
+    hipLaunchKernelGGL(subst_panel_kernel, dim3((p1 + SUB_CW - 1) / SUB_CW), dim3(256), 0, s, out, l, ldl, small, x, n, p0,
                        p1);
     GW_TRY(hipGetLastError());
     // 3. A[p1:, p1:] -= Lp Lp^H (lower tiles) and B[p1:, :p1] -= Lp X[p0:p1, :p1], Lp = L[p1:, p0:p1]
     const int rest = n - p1;
     if (rest > 0) {
-      const double2 *lp = l + (size_t)p1 * n + p0;
-      GW_TRY(zgemm_lower_and_full(rest, p1, p1 - p0, lp, n, lp, a + (size_t)p1 * n + p1, x + (size_t)p0 * n,
-                                  out + (size_t)p1 * n, n, n, -1.0, 1.0, s));
+      const double2 *lp = l + (size_t)p1 * ldl;
+      GW_TRY(zgemm_lower_and_full(rest, p1, p1 - p0, lp, ldl, lp, ldl, a + (size_t)p1 * n + p1,
+                                  x + (size_t)p0 * n, n, out + (size_t)p1 * n, n, -1.0, 1.0, s));
     }
   }
   // 3. out = X^H X (lower tiles, k from max(row, col) since X is lower triangular), then mirror

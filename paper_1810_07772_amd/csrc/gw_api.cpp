@@ -513,7 +513,7 @@ int eps_build_impl(gw_ctx *ctx, const float2 *p_gg, int ng, gw_grid g, const dou
 
 int hpd_inverse_impl(gw_ctx *ctx, double2 *a, int n, double2 *out, hipStream_t s) {
   void *l, *x, *sm, *piv;
-  GW_STATUS(ws_get(ctx, WS_CHOL_L, (size_t)n * n * sizeof(double2), &l, s));
+  GW_STATUS(ws_get(ctx, WS_CHOL_L, chol_panel_elems(n) * sizeof(double2), &l, s));
   GW_STATUS(ws_get(ctx, WS_CHOL_X, (size_t)n * n * sizeof(double2), &x, s));
   GW_STATUS(ws_get(ctx, WS_CHOL_SMALL, chol_small_bytes(n) + 256, &sm, s));
   piv = (char *)sm + chol_small_bytes(n);

@@ -263,7 +263,7 @@ int gw_polarizability_batched(gw_ctx *ctx, const gw_c32 *psi_occ, int nv, const 
   else GWX_STATUS(api_ws_get(ctx, BS_PHT, ngmax * nr * sizeof(float2), &wpht, s));
   GWX_STATUS(api_ws_get(ctx, BS_Q, ngmax * ngmax * sizeof(float2), &wq, s));
   GWX_STATUS(api_ws_get(ctx, BS_EPS, ngmax * ngmax * sizeof(double2), &weps, s));
-  GWX_STATUS(api_ws_get(ctx, BS_L, ngmax * ngmax * sizeof(double2), &wl, s));
+  GWX_STATUS(api_ws_get(ctx, BS_L, chol_panel_elems((int)ngmax) * sizeof(double2), &wl, s));
   GWX_STATUS(api_ws_get(ctx, BS_X, ngmax * ngmax * sizeof(double2), &wx, s));
   GWX_STATUS(api_ws_get(ctx, BS_SMALL, chol_small_bytes((int)ngmax), &wsmall, s));
   GWX_STATUS(api_ws_get(ctx, BS_PIVOT, (size_t)nq * 64, &wpiv, s));

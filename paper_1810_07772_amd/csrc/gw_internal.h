@@ -56,7 +56,7 @@ enum SlotId {
   WS_MILLER,      // int [ng][3]
   WS_SQRTV,       // double [ng]
   WS_EPS,         // complex128 [n][n] eps / working matrix
-  WS_CHOL_L,      // complex128 [n][n] Cholesky factor
+  WS_CHOL_L,      // complex128 [n][min(n, 128)] a panel of the Cholesky factor
   WS_CHOL_X,      // complex128 [n][n] L^-1
   WS_CHOL_SMALL,  // diagonal-block inverses + pivot flag
   WS_BSCALE,      // per-band power-of-two exponents (FP16 path)
@@ -131,8 +131,9 @@ hipError_t launch_sqrtv(const int *miller, int ng, double q0, double q1, double 
 hipError_t launch_eps_build(const float2 *p_gg, int ng, const double *sv, double head, double2 *eps,
                             hipStream_t s);
 // Cholesky-based inverse of a Hermitian PD matrix (lower triangle of a read).  a is overwritten.
-// l, x: n*n workspaces; small: workspace of at least chol_small_bytes(n); pivot_dev: device int.
+// l: chol_panel_elems(n), x: n*n workspaces; small: workspace of at least chol_small_bytes(n); pivot_dev: device int.
 size_t chol_small_bytes(int n);
+size_t chol_panel_elems(int n);
 hipError_t hpd_inverse(double2 *a, int n, double2 *l, double2 *x, double2 *small, int *pivot_dev, double2 *out,
                        hipStream_t s);
 hipError_t launch_fill_int(int *p, int value, hipStream_t s);

@@ -1,0 +1,46 @@
+"""The complex FP64 product kernels (both tile sizes and the rule between them) through the inverse and the Newton
+iteration, against LAPACK: 1e-12 relative, as the condition numbers here are below 10."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def gw():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1810_07772_amd as gw
+    gw.load()
+    return gw
+
+
+def matrix(n):
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((n, 2 * n)) + 1j * rng.standard_normal((n, 2 * n))
+    return np.eye(n) + x @ x.conj().T / (4 * n)
+
+
+# One panel of 128 columns and the values beside it; several panels with a ragged last one; a size whose products take
+# small tiles throughout (640), one that takes both sizes (2000).  The workspace holds NaN from a call before.
+@pytest.mark.parametrize("n", [127, 128, 129, 163, 300, 640, 2000])
+def test_inverse(gw, n):
+    ctx = gw.Context(0)
+    bad = torch.full((n, n), float("nan"), dtype=torch.complex128, device="cuda:0")
+    with pytest.raises(gw.GwError):
+        gw.hpd_inverse(bad, ctx=ctx)
+    a = matrix(n)
+    print(f"[case] n={n}", flush=True)
+    got = gw.hpd_inverse(torch.from_numpy(a).cuda(), ctx=ctx).cpu().numpy()
+    ref = np.linalg.inv(a)
+    assert np.linalg.norm(got - ref) < 1e-12 * np.linalg.norm(ref)
+    assert np.array_equal(np.triu(got, 1), np.tril(got, -1).conj().T)     # the mirrored triangle
+
+
+@pytest.mark.parametrize("n", [33, 65, 500, 900])
+def test_newton(gw, n):
+    a = matrix(n)
+    got, its, _ = gw.newton_inverse(torch.from_numpy(a).cuda())
+    ref = np.linalg.inv(a)
+    assert np.linalg.norm(got.cpu().numpy() - ref) < 1e-12 * np.linalg.norm(ref)
