@@ -6,11 +6,12 @@
 // parallelises across distributed memory; on one GPU the factorisation costs about a
 // third of the flops and every large step below is still a matrix product (zgemm).
 //
-// zgemm: C = alpha * op(A) op(B) + beta * C for complex128, op = identity or conjugate
-// transpose, on v_mfma_f64_16x16x4f64.  Complex products use real MFMA with k' = (k, re/im):
+// zgemm: C = alpha * op(A) op(B) + beta * C for complex128 (B also complex64, widened on the way into LDS), op =
+// identity, transpose, conjugate or both, on v_mfma_f64_16x16x4f64.  Complex products use real MFMA with k' = (k, re/im):
 //   Re C += [Re A, Im A] . [Re B; -Im B],   Im C += [Re A, Im A] . [Im B; Re B].
 #include <algorithm>
 
+#include <type_traits>
 #include <utility>
 
 #include "gw_internal.h"
@@ -34,13 +35,13 @@ struct Zg2 {
   const double2 *B;
   double2 *C;
   long long ldb;
-  int transB, N, ntile1;
+  int opB, N, ntile1;
 };
 
-template <int GT>
+template <int GT, typename TB>
 __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int N, int K, const double2 *__restrict__ A,
-                                                    long long lda, int transA, const double2 *__restrict__ B,
-                                                    long long ldb, int transB, double2 *__restrict__ C, long long ldc,
+                                                    long long lda, int opA, const TB *__restrict__ B,
+                                                    long long ldb, int opB, double2 *__restrict__ C, long long ldc,
                                                     double alpha, double beta, int lower_only, int tri_k, Zg2 z2) {
   constexpr int GK = ZgShape<GT>::GK, RB = GT / 32;     // 16 x 16 blocks per wave and side
   constexpr int LP = GT == 64 ? 64 : 36;                // LDS row stride
@@ -52,10 +53,10 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
     const int t = (int)blockIdx.x - z2.ntile1, nct = (z2.N + GT - 1) / GT;
     row0 = (t / nct) * GT;
     col0 = (t % nct) * GT;
-    B = z2.B;
+    if constexpr (std::is_same_v<TB, double2>) B = z2.B;
     C = z2.C;
     ldb = z2.ldb;
-    transB = z2.transB;
+    opB = z2.opB;
     N = z2.N;
   } else if (lower_only >= 2) {
     const int t = blockIdx.x;
@@ -69,6 +70,7 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
     col0 = blockIdx.x * GT;
   }
   const int kend = K;
+  const bool transA = opA & Z_T, transB = opB & Z_T;
   // two LDS stages: the global loads of stage k+1 are in flight in registers while stage k's MFMAs run
   __shared__ double sA[2][GK][2][LP];
   __shared__ double sX[2][GK][3][LP];   // planes Re B, -Im B, Im B: [Re B; -Im B] is planes 0, 1, [Im B; Re B] 2, 0
@@ -86,7 +88,8 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
   if (tri_k) kbeg = (max(row0, col0) / GK) * GK;
   const int kl = lane >> 4, li = lane & 15;
   constexpr int PER = (GT * GK) / 256;   // elements of each operand per thread and stage
-  double2 va[PER], vb[PER];
+  double2 va[PER];
+  TB vb[PER];
   // element idx of a stage: A row r / B column c and its k offset kk, in the order that keeps the
   // global reads contiguous for either layout
   auto a_coord = [&](int idx, int &r, int &kk) {
@@ -99,7 +102,8 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
   // written to LDS, so no instruction waits on a load before the stage's MFMAs have been issued.
   // Each thread's elements advance by GK along k per stage: running pointers, and no bounds test in
   // the stages of a whole tile that lie inside [kbeg, kend).
-  const double2 *pa[PER], *pb[PER];
+  const double2 *pa[PER];
+  const TB *pb[PER];
   int ka[PER], kb[PER];
   bool ra[PER], cb_ok[PER];
 #pragma unroll
@@ -131,7 +135,7 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
       for (int it = 0; it < PER; ++it) {
         va[it] = make_double2(0.0, 0.0);
         if (ra[it] && k0 + ka[it] < kend) va[it] = *pa[it];
-        vb[it] = make_double2(0.0, 0.0);
+        vb[it] = TB{0, 0};
         if (cb_ok[it] && k0 + kb[it] < kend) vb[it] = *pb[it];
       }
     }
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
       pb[it] += step_b;
     }
   };
-  const double sa = transA ? -1.0 : 1.0, sb = transB ? -1.0 : 1.0;
+  const double sa = opA & Z_J ? -1.0 : 1.0, sb = opB & Z_J ? -1.0 : 1.0;
   auto lstore = [&](int buf) {
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
@@ -151,8 +155,8 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
       sA[buf][kk][0][r] = va[it].x;
       sA[buf][kk][1][r] = sa * va[it].y;
       b_coord(idx, c, kk);
-      const double by = sb * vb[it].y;
-      sX[buf][kk][0][c] = vb[it].x;
+      const double by = sb * (double)vb[it].y;
+      sX[buf][kk][0][c] = (double)vb[it].x;
       sX[buf][kk][1][c] = -by;
       sX[buf][kk][2][c] = by;
     }
@@ -238,30 +242,31 @@ static int zg_tile(long long tiles, int K, int tri_k) {
   return tiles < (tri_k ? 400 : K <= 256 ? 600 : 192) ? 32 : 64;
 }
 
-template <int GT>
-static hipError_t zgemm_t(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
-                          long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
+template <int GT, typename TB>
+static hipError_t zgemm_t(int M, int N, int K, const double2 *A, long long lda, int opA, const TB *B,
+                          long long ldb, int opB, double2 *C, long long ldc, double alpha, double beta,
                           int lower_only, int tri_k, hipStream_t s) {
   if (lower_only) {
     const long long nt = (N + GT - 1) / GT;
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT>), dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, M, N, K,
-                       A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, 2, tri_k, Zg2{});
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT, TB>), dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, s, M, N,
+                       K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, 2, tri_k, Zg2{});
     return hipGetLastError();
   }
   dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
-  hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT>), grid, dim3(256), 0, s, M, N, K, A, lda, transA, B, ldb, transB,
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT, TB>), grid, dim3(256), 0, s, M, N, K, A, lda, opA, B, ldb, opB,
                      C, ldc, alpha, beta, 0, tri_k, Zg2{});
   return hipGetLastError();
 }
 
 // lower_only: a square product, its lower tiles only
-static hipError_t zgemm(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
-                        long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
+template <typename TB>
+static hipError_t zgemm(int M, int N, int K, const double2 *A, long long lda, int opA, const TB *B,
+                        long long ldb, int opB, double2 *C, long long ldc, double alpha, double beta,
                         int lower_only, int tri_k, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const long long mt = (M + 63) / 64, nt = (N + 63) / 64, tiles = lower_only ? nt * (nt + 1) / 2 : mt * nt;
-  return zg_tile(tiles, K, tri_k) == 32 ? zgemm_t<32>(M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, lower_only, tri_k, s)
-                              : zgemm_t<64>(M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, lower_only, tri_k, s);
+  return zg_tile(tiles, K, tri_k) == 32 ? zgemm_t<32>(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, lower_only, tri_k, s)
+                              : zgemm_t<64>(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, lower_only, tri_k, s);
 }
 
 // C1 = alpha A B1^H + beta C1 on the lower tiles of the square M x M C1, and C2 = alpha A B2 + beta C2 on
@@ -271,8 +276,8 @@ static hipError_t zgemm_lower_and_full_t(int M, int N2, int K, const double2 *A,
                                          long long ldb1, double2 *C1, const double2 *B2, long long ldb2, double2 *C2,
                                          long long ldc, double alpha, double beta, hipStream_t s) {
   const long long nt = (M + GT - 1) / GT, nt1 = nt * (nt + 1) / 2, nt2 = N2 > 0 ? nt * ((N2 + GT - 1) / GT) : 0;
-  hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT>), dim3((unsigned)(nt1 + nt2)), dim3(256), 0, s, M, M, K, A, lda, 0,
-                     B1, ldb1, 1, C1, ldc, alpha, beta, 3, 0, Zg2{B2, C2, ldb2, 0, N2, (int)nt1});
+  hipLaunchKernelGGL(HIP_KERNEL_NAME(zgemm_kernel<GT, double2>), dim3((unsigned)(nt1 + nt2)), dim3(256), 0, s, M, M, K,
+                     A, lda, Z_N, B1, ldb1, Z_H, C1, ldc, alpha, beta, 3, 0, Zg2{B2, C2, ldb2, Z_N, N2, (int)nt1});
   return hipGetLastError();
 }
 
@@ -286,10 +291,14 @@ static hipError_t zgemm_lower_and_full(int M, int N2, int K, const double2 *A, l
              : zgemm_lower_and_full_t<64>(M, N2, K, A, lda, B1, ldb1, C1, B2, ldb2, C2, ldc, alpha, beta, s);
 }
 
-hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
-                        long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
-                        hipStream_t s) {
-  return zgemm(M, N, K, A, lda, transA, B, ldb, transB, C, ldc, alpha, beta, 0, 0, s);
+hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int opA, const double2 *B, long long ldb,
+                        int opB, double2 *C, long long ldc, double alpha, double beta, hipStream_t s) {
+  return zgemm(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, 0, 0, s);
+}
+
+hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int opA, const float2 *B, long long ldb,
+                        int opB, double2 *C, long long ldc, double alpha, double beta, hipStream_t s) {
+  return zgemm(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, 0, 0, s);
 }
 
 // ---- diagonal block L_kk = chol(A_kk), Linv_kk = L_kk^-1, and the panel column below it -------------
@@ -717,7 +726,7 @@ hipError_t hpd_inverse(double2 *a, int n, double2 *l, double2 *x, double2 *small
     }
   }
   // 3. out = X^H X (lower tiles, k from max(row, col) since X is lower triangular), then mirror
-  GW_TRY(zgemm(n, n, n, x, n, 1, x, n, 0, out, n, 1.0, 0.0, 1, 1, s));
+  GW_TRY(zgemm(n, n, n, x, n, Z_H, x, n, Z_N, out, n, 1.0, 0.0, 1, 1, s));
   dim3 mg((n + 31) / 32, (n + 31) / 32);
   hipLaunchKernelGGL(mirror_lower_kernel, mg, dim3(256), 0, s, out, n);
   return hipGetLastError();
@@ -805,7 +814,7 @@ size_t newton_ws_bytes(int n) { return 3 * (size_t)n * n * sizeof(double2) + ((s
 
 hipError_t newton_start(const double2 *a, int n, double2 *x, double2 *t, double *scratch, hipStream_t s) {
   // t = A A^H, alpha = 1 / max_i sum_j |t_ij|, x = alpha A^H
-  GW_TRY(zgemm(n, n, n, a, n, 0, a, n, 1, t, n, 1.0, 0.0, 0, 0, s));
+  GW_TRY(zgemm(n, n, n, a, n, Z_N, a, n, Z_H, t, n, 1.0, 0.0, 0, 0, s));
   hipLaunchKernelGGL(row_abs_sum_kernel, dim3(n), dim3(256), 0, s, t, n, scratch + 64);
   GW_TRY(hipGetLastError());
   hipLaunchKernelGGL(max_reduce_kernel, dim3(1), dim3(256), 0, s, scratch + 64, n, scratch, 1);
@@ -821,8 +830,8 @@ hipError_t newton_step(const double2 *a, int n, const double2 *x, double2 *t, do
   const size_t nn = (size_t)n * n;
   hipLaunchKernelGGL(fill_identity_kernel, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, t, n, 2.0);
   GW_TRY(hipGetLastError());
-  GW_TRY(zgemm(n, n, n, a, n, 0, x, n, 0, t, n, -1.0, 1.0, 0, 0, s));
-  GW_TRY(zgemm(n, n, n, x, n, 0, t, n, 0, xn, n, 1.0, 0.0, 0, 0, s));
+  GW_TRY(zgemm(n, n, n, a, n, Z_N, x, n, Z_N, t, n, -1.0, 1.0, 0, 0, s));
+  GW_TRY(zgemm(n, n, n, x, n, Z_N, t, n, Z_N, xn, n, 1.0, 0.0, 0, 0, s));
   hipLaunchKernelGGL(row_max_diff_kernel, dim3(n), dim3(256), 0, s, xn, x, n, scratch + 64);
   GW_TRY(hipGetLastError());
   hipLaunchKernelGGL(max_reduce_kernel, dim3(1), dim3(256), 0, s, scratch + 64, n, scratch + 1, 0);

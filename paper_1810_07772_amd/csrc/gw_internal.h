@@ -122,6 +122,11 @@ hipError_t launch_fft_gather_pass_t(int n, int sign, const float2 *in, float2 *o
                                     long long ld_out, const int *map, float scale, hipStream_t s);
 hipError_t launch_fft_gather_pass(int n, int sign, const float2 *in, float2 *out, int O, int U, int B, long long ld_in,
                                   long long ld_out, const int *map, float scale, hipStream_t s);
+// The first pass (axis of length n, exp(-i..), U = 1) of the pair transforms: its input, element (o n + i, b), is
+// conj(pn[.][b / nv]) pv[.][b % nv] with b = b0 + column, formed from the grid-major orbitals pn [n1 n2 n3][nn] and
+// pv [n1 n2 n3][nv].
+hipError_t launch_fft_pair_pass(int n, const float2 *pn, int nn, const float2 *pv, int nv, int b0, float2 *out, int O,
+                                int B, long long ld_out, const int *map, hipStream_t s);
 hipError_t launch_transpose_c64(const float2 *in, float2 *out, int rows, int cols, long long ld_in,
                                 long long ld_out, hipStream_t s);
 
@@ -137,14 +142,17 @@ size_t chol_panel_elems(int n);
 hipError_t hpd_inverse(double2 *a, int n, double2 *l, double2 *x, double2 *small, int *pivot_dev, double2 *out,
                        hipStream_t s);
 hipError_t launch_fill_int(int *p, int value, hipStream_t s);
-// C = alpha op(A) op(B) + beta C, complex128, op = identity (0) or conjugate transpose (1); row-major.
-hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int transA, const double2 *B,
-                        long long ldb, int transB, double2 *C, long long ldc, double alpha, double beta,
-                        hipStream_t s);
+// C = alpha op(A) op(B) + beta C, complex128 (B also complex64), row-major.
+enum ZOp { Z_N = 0, Z_T = 1, Z_J = 2, Z_H = 3 };   // identity, transpose, conjugate, conjugate transpose
+hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int opA, const double2 *B, long long ldb,
+                        int opB, double2 *C, long long ldc, double alpha, double beta, hipStream_t s);
+hipError_t launch_zgemm(int M, int N, int K, const double2 *A, long long lda, int opA, const float2 *B, long long ldb,
+                        int opB, double2 *C, long long ldc, double alpha, double beta, hipStream_t s);
 // Plasmon-pole kernels (pp.hip)
 hipError_t launch_density(const float2 *psi, int nv, int nr, double occ, double2 *rho, hipStream_t s);
 hipError_t launch_density_transform(double2 *rho, double2 *tmp, int n1, int n2, int n3, hipStream_t s);
-hipError_t launch_screening(const double2 *ei, const double *sv, int ng, double2 *out, hipStream_t s);
+// s = sv_g (eps_inv - delta) sv_g', rows of lds values
+hipError_t launch_screening(const double2 *ei, const double *sv, int ng, long long lds, double2 *out, hipStream_t s);
 hipError_t launch_sum_rule(const int *miller, int ng, const double *q, double a_bohr, const double *sv,
                            const double2 *rho_g, int n1, int n2, int n3, double2 *m, hipStream_t s);
 hipError_t launch_start_block(double2 *x, int ng, int b, unsigned long long seed, hipStream_t s);
@@ -175,14 +183,15 @@ hipError_t launch_pp_weight(const double2 *modes, int ng, int nm, const double *
 hipError_t launch_pp_finish(double2 *e, const double2 *ei_static, const double *sv, int ng, hipStream_t s);
 hipError_t launch_sqrtv(const int *miller, int ng, double q0, double q1, double q2, double a_bohr, double *sv,
                         hipStream_t s);
-// Static self-energy kernels (sigma.hip)
-hipError_t launch_fill_f32(float *p, int n, float v, hipStream_t s);
-hipError_t launch_conj_upcast(const float2 *in, size_t n, double2 *out, hipStream_t s);
-hipError_t launch_contract_conj(const float2 *a, const float2 *b, int ng, int nv, long long ld, const double *sv,
-                                double scale, int nn, double2 *out, hipStream_t s);
-hipError_t launch_contract_t(const float2 *a, const double2 *t, int ng, int nv, long long ld, double scale, int nn,
+// Static self-energy kernels (sigma.hip).  f: f~ as rows [g][n nv + v].
+size_t contract_part_elems(int nn, int nv, int ng);
+// out[n][n'] = scale sum_g V_g sum_v f[g][n nv + v] conj(f[g][n' nv + v]), V_g = sv_g^2
+hipError_t launch_contract_x(const float2 *f, int nn, int nv, int ng, const double *sv, double scale, double2 *part,
                              double2 *out, hipStream_t s);
-hipError_t launch_zeta(const float2 *f, int ng, int npair, const double2 *modes, int nm, double2 *zeta, hipStream_t s);
+// out[n][n'] = scale sum_g sum_v f[g][n nv + v] t[g][n' nv + v]
+hipError_t launch_contract_t(const float2 *f, const double2 *t, int nn, int nv, int ng, double scale, double2 *part,
+                             double2 *out, hipStream_t s);
+// out[n][n'] = -sum_a sigma_a sum_v zeta[a][n nv + v] conj(zeta[a][n' nv + v])
 hipError_t launch_contract_modes(const double2 *zeta, int nm, int nv, int nn, const double *sigma, double2 *out,
                                  hipStream_t s);
 // Newton iteration for the inverse: workspace of newton_ws_bytes(n) holds x, t, xn and the scalars.

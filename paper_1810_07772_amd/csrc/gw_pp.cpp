@@ -93,7 +93,7 @@ int gw_plasmon_pole(gw_ctx *ctx, const gw_c64 *eps_inv, int ng, gw_grid grid, co
   GWX_HIP(ctx, launch_density((const float2 *)psi_v, nv, nr, occupation, (double2 *)rho, s));
   GWX_HIP(ctx, launch_density_transform((double2 *)rho, (double2 *)rho_t, grid.n1, grid.n2, grid.n3, s));
   double2 *S = (double2 *)sp, *M = (double2 *)mp;
-  GWX_HIP(ctx, launch_screening((const double2 *)eps_inv, sv, ng, S, s));
+  GWX_HIP(ctx, launch_screening((const double2 *)eps_inv, sv, ng, ng, S, s));
   // block buffers
   void *xp, *yp, *wp, *tp, *smp;
   const size_t blk = (size_t)ng * b * sizeof(double2);
@@ -181,7 +181,7 @@ int gw_pp_eps_inverse(gw_ctx *ctx, const gw_c64 *eps_inv_static, int ng, gw_grid
   for (int f = 0; f < nf; ++f) {
     double2 *e = (double2 *)out + (size_t)f * ng * ng;
     GWX_HIP(ctx, launch_pp_weight((const double2 *)modes, ng, n_modes, sigma, omega, freqs[f], (double2 *)bp, s));
-    GWX_HIP(ctx, launch_zgemm(ng, ng, n_modes, (const double2 *)bp, n_modes, 0, (const double2 *)modes, n_modes, 1, e,
+    GWX_HIP(ctx, launch_zgemm(ng, ng, n_modes, (const double2 *)bp, n_modes, Z_N, (const double2 *)modes, n_modes, Z_H, e,
                               ng, 1.0, 0.0, s));
     GWX_HIP(ctx, launch_pp_finish(e, (const double2 *)eps_inv_static, sv, ng, s));
   }

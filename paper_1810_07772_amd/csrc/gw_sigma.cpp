@@ -13,7 +13,7 @@ namespace {
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
 // workspace slots of this file (after those of the batched path)
-enum { SG_ONES = 512, SG_F, SG_FT, SG_FG, SG_MAP, SG_A1, SG_A2, SG_MILLER, SG_SQRTV, SG_S, SG_FC, SG_T, SG_Z };
+enum { SG_F = 512, SG_FG, SG_MAP, SG_A1, SG_A2, SG_MILLER, SG_SQRTV, SG_S, SG_T, SG_Z };
 
 int check_common(gw_ctx *ctx, const void *psi_n, int nn, const void *psi_v, int nv, gw_grid grid, const int *miller,
                  int ng) {
@@ -29,30 +29,34 @@ int check_common(gw_ctx *ctx, const void *psi_n, int nn, const void *psi_v, int 
   return GW_OK;
 }
 
-// f~ [ng][nn*nv] (complex64, pair index n*nv + v fastest) for the bands and occupied set given
+// f~ [ng][nn*nv] (complex64, pair index n*nv + v fastest) for the bands and occupied set given.  *part: room for the
+// contractions' partial sums (over the transposed orbitals, which the transform is done with).
 int pair_transform(gw_ctx *ctx, const float2 *psi_n, int nn, const float2 *psi_v, int nv, gw_grid grid,
-                   const int *miller, int ng, float2 **ft, hipStream_t s) {
+                   const int *miller, int ng, float2 **ft, double2 **part, hipStream_t s) {
   const int nr = grid.n1 * grid.n2 * grid.n3, B = nn * nv;
-  const int ldsc = scale_ld(nv);
-  void *ones, *f, *fr, *fg;
-  GWX_STATUS(api_ws_get(ctx, SG_ONES, (size_t)nn * ldsc * sizeof(float), &ones, s));
-  GWX_HIP(ctx, launch_fill_f32((float *)ones, nn * ldsc, 1.0f, s));
-  GWX_STATUS(api_ws_get(ctx, SG_F, (size_t)B * nr * sizeof(float2), &f, s));
-  GWX_STATUS(api_ws_get(ctx, SG_FT, (size_t)B * nr * sizeof(float2), &fr, s));
+  void *ot, *fg, *a1, *a2;
+  GWX_STATUS(api_ws_get(ctx, SG_F, std::max((size_t)(nn + nv) * nr * sizeof(float2),
+                                            contract_part_elems(nn, nv, ng) * sizeof(double2)), &ot, s));
   GWX_STATUS(api_ws_get(ctx, SG_FG, (size_t)B * ng * sizeof(float2), &fg, s));
-  // conj(u_n) u_v as rows [n*nv + v][r] (the pair-product kernel with unit scales), then grid-major
-  GWX_HIP(ctx, launch_pair_products(psi_n, nn, psi_v, nv, nr, (const float *)ones, ldsc, (float2 *)f, s));
-  GWX_HIP(ctx, launch_transpose_c64((const float2 *)f, (float2 *)fr, B, nr, nr, B, s));
+  // the orbitals grid-major; the first pass forms the products conj(u_n) u_v from them
+  float2 *pn = (float2 *)ot, *pv = pn + (size_t)nn * nr;
+  GWX_HIP(ctx, launch_transpose_c64(psi_n, pn, nn, nr, nr, nn, s));
+  GWX_HIP(ctx, launch_transpose_c64(psi_v, pv, nv, nr, nr, nv, s));
   SpherePlan p;
   int *dA, *dB, *dC;
   GWX_STATUS(upload_plan(ctx, grid, miller, ng, SG_MAP, p, &dA, &dB, &dC, s));
   const int bc = std::max(1, std::min(p.bc, B));
-  void *a1, *a2;
   GWX_STATUS(api_ws_get(ctx, SG_A1, (size_t)grid.n1 * grid.n2 * p.m3count * bc * sizeof(float2), &a1, s));
   GWX_STATUS(api_ws_get(ctx, SG_A2, (size_t)grid.n1 * p.npair * bc * sizeof(float2), &a2, s));
-  GWX_HIP(ctx, transform_rows(p, -1, (const float2 *)fr, B, B, (float2 *)fg, B, (float2 *)a1, (float2 *)a2, bc, dA,
-                              dB, dC, s));
-  *ft = (float2 *)fg;
+  float2 *x1 = (float2 *)a1, *x2 = (float2 *)a2, *out = (float2 *)fg;
+  for (int b0 = 0; b0 < B; b0 += bc) {
+    const int w = std::min(bc, B - b0);
+    GWX_HIP(ctx, launch_fft_pair_pass(grid.n3, pn, nn, pv, nv, b0, x1, grid.n1 * grid.n2, w, w, dA, s));
+    GWX_HIP(ctx, launch_fft_pass(grid.n2, -1, x1, x2, grid.n1, p.m3count, w, w, w, dB, s));
+    GWX_HIP(ctx, launch_fft_pass(grid.n1, -1, x2, out + b0, 1, p.npair, w, w, B, dC, s));
+  }
+  *ft = out;
+  *part = (double2 *)ot;
   return GW_OK;
 }
 
@@ -83,22 +87,22 @@ int gw_sigma_static(gw_ctx *ctx, const gw_c32 *psi_n, int nn, const gw_c32 *psi_
   if (api_device(ctx) < 0) return GW_OK;
   hipStream_t s = as_stream(stream);
   float2 *ft;
-  GWX_STATUS(pair_transform(ctx, (const float2 *)psi_n, nn, (const float2 *)psi_v, nv, grid, g_miller, ng, &ft, s));
+  double2 *part;
+  GWX_STATUS(pair_transform(ctx, (const float2 *)psi_n, nn, (const float2 *)psi_v, nv, grid, g_miller, ng, &ft, &part, s));
   double *sv;
   GWX_STATUS(sqrtv_on_device(ctx, g_miller, ng, q, grid.a_bohr, &sv, s));
   const int B = nn * nv;
-  if (sigma_x) GWX_HIP(ctx, launch_contract_conj(ft, ft, ng, nv, B, sv, -1.0, nn, (double2 *)sigma_x, s));
+  if (sigma_x) GWX_HIP(ctx, launch_contract_x(ft, nn, nv, ng, sv, -1.0, part, (double2 *)sigma_x, s));
   if (sigma_sex) {
-    void *sp, *fc, *tp;
-    GWX_STATUS(api_ws_get(ctx, SG_S, (size_t)ng * ng * sizeof(double2), &sp, s));
-    GWX_STATUS(api_ws_get(ctx, SG_FC, (size_t)ng * B * sizeof(double2), &fc, s));
+    // rows of S start on memory lines: the product's 64-byte runs along k would straddle them otherwise
+    const long long lds = (ng + 7) / 8 * 8;
+    void *sp, *tp;
+    GWX_STATUS(api_ws_get(ctx, SG_S, (size_t)ng * lds * sizeof(double2), &sp, s));
     GWX_STATUS(api_ws_get(ctx, SG_T, (size_t)ng * B * sizeof(double2), &tp, s));
-    GWX_HIP(ctx, launch_screening((const double2 *)eps_inv, sv, ng, (double2 *)sp, s));
-    GWX_HIP(ctx, launch_conj_upcast(ft, (size_t)ng * B, (double2 *)fc, s));
+    GWX_HIP(ctx, launch_screening((const double2 *)eps_inv, sv, ng, lds, (double2 *)sp, s));
     // T = -S conj(f~)
-    GWX_HIP(ctx, launch_zgemm(ng, B, ng, (const double2 *)sp, ng, 0, (const double2 *)fc, B, 0, (double2 *)tp, B, -1.0,
-                              0.0, s));
-    GWX_HIP(ctx, launch_contract_t(ft, (const double2 *)tp, ng, nv, B, 1.0, nn, (double2 *)sigma_sex, s));
+    GWX_HIP(ctx, launch_zgemm(ng, B, ng, (const double2 *)sp, lds, Z_N, ft, B, Z_J, (double2 *)tp, B, -1.0, 0.0, s));
+    GWX_HIP(ctx, launch_contract_t(ft, (const double2 *)tp, nn, nv, ng, 1.0, part, (double2 *)sigma_sex, s));
   }
   return GW_OK;
 }
@@ -113,11 +117,14 @@ int gw_sigma_sex_modes(gw_ctx *ctx, const gw_c32 *psi_n, int nn, const gw_c32 *p
   if (api_device(ctx) < 0) return GW_OK;
   hipStream_t s = as_stream(stream);
   float2 *ft;
-  GWX_STATUS(pair_transform(ctx, (const float2 *)psi_n, nn, (const float2 *)psi_v, nv, grid, g_miller, ng, &ft, s));
+  double2 *part;
+  GWX_STATUS(pair_transform(ctx, (const float2 *)psi_n, nn, (const float2 *)psi_v, nv, grid, g_miller, ng, &ft, &part, s));
   const int B = nn * nv;
   void *z;
   GWX_STATUS(api_ws_get(ctx, SG_Z, (size_t)B * n_modes * sizeof(double2), &z, s));
-  GWX_HIP(ctx, launch_zeta(ft, ng, B, (const double2 *)modes, n_modes, (double2 *)z, s));
+  // zeta[a][pair] = sum_g A(g, a) f~_g
+  GWX_HIP(ctx, launch_zgemm(n_modes, B, ng, (const double2 *)modes, n_modes, Z_T, ft, B, Z_N, (double2 *)z, B, 1.0, 0.0,
+                            s));
   GWX_HIP(ctx, launch_contract_modes((const double2 *)z, n_modes, nv, nn, sigma, (double2 *)sigma_sex, s));
   return GW_OK;
 }

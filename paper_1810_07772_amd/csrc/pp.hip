@@ -48,7 +48,7 @@ __global__ void dft_axis_f64_kernel(const double2 *__restrict__ in, double2 *__r
 }
 
 // s = sv_g (eps_inv - delta) sv_g'
-__global__ void screening_kernel(const double2 *__restrict__ ei, const double *__restrict__ sv, int ng,
+__global__ void screening_kernel(const double2 *__restrict__ ei, const double *__restrict__ sv, int ng, long long lds,
                                  double2 *__restrict__ s) {
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (size_t)ng * ng) return;
@@ -56,7 +56,7 @@ __global__ void screening_kernel(const double2 *__restrict__ ei, const double *_
   double2 e = ei[idx];
   if (g == h) e.x -= 1.0;
   const double f = sv[g] * sv[h];
-  s[idx] = make_double2(f * e.x, f * e.y);
+  s[g * lds + h] = make_double2(f * e.x, f * e.y);
 }
 
 // m = V_g V_h (2pi/a)^2 [(q+m_g).(q+m_h)] rho[(m_g - m_h) mod n]
@@ -815,8 +815,8 @@ hipError_t launch_density_transform(double2 *rho, double2 *tmp, int n1, int n2, 
   return hipGetLastError();
 }
 
-hipError_t launch_screening(const double2 *ei, const double *sv, int ng, double2 *out, hipStream_t s) {
-  hipLaunchKernelGGL(screening_kernel, dim3(blocks_for((size_t)ng * ng)), dim3(256), 0, s, ei, sv, ng, out);
+hipError_t launch_screening(const double2 *ei, const double *sv, int ng, long long lds, double2 *out, hipStream_t s) {
+  hipLaunchKernelGGL(screening_kernel, dim3(blocks_for((size_t)ng * ng)), dim3(256), 0, s, ei, sv, ng, lds, out);
   return hipGetLastError();
 }
 

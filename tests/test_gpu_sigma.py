@@ -92,3 +92,29 @@ def test_plane_wave_fock_closed_form_non_cubic(gw):
                 ref -= 4 * np.pi / (a ** 3 * k @ k)
         assert abs(sx[i, i] - ref) < 1e-6 * abs(ref)
     assert np.max(np.abs(sx - np.diag(np.diag(sx)))) < 1e-6 * np.max(np.abs(sx))
+
+
+# The contractions' tiles of 16 x 16 bands and units of 16 occupied bands at their edges, on a cubic grid and on one
+# with three different sides; tolerances as above (FP32 transforms of orbitals: 2e-6 of the matrix norm).
+@pytest.mark.parametrize("n,nn,nv,ng", [((8, 8, 8), 1, 1, 40), ((8, 8, 8), 16, 16, 60), ((8, 8, 8), 17, 15, 33),
+                                        ((6, 5, 8), 33, 5, 50), ((6, 5, 8), 3, 18, 21)])
+def test_band_counts(gw, n, nn, nv, ng):
+    rng = np.random.default_rng(nn)
+    nr, q = n[0] * n[1] * n[2], np.array([0.2, 0.1, 0.3])
+    psi = (rng.standard_normal((nn + nv, nr)) + 1j * rng.standard_normal((nn + nv, nr)))
+    psi = (psi / np.sqrt((np.abs(psi) ** 2).sum(1))[:, None]).astype(np.complex64)
+    mill = gs.sphere(n, count=ng, q=q)
+    x = rng.standard_normal((ng, 2 * ng)) + 1j * rng.standard_normal((ng, 2 * ng))
+    ei = np.linalg.inv(np.eye(ng) + x @ x.conj().T / (4 * ng)) + 0.05 * x[:, :ng]          # not Hermitian
+    print(f"[case] n={n} nn={nn} nv={nv} ng={ng}", flush=True)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda:0")
+    sx, ss = gw.sigma_static(dev(psi[:nn]), dev(psi[nn:]), n, 7.0, q, mill, dev(ei))
+    sv = orc.coulomb_sqrt(n, 7.0, q, mill)
+    idx = tuple((mill % np.array(n)).T)
+    f = np.array([[np.fft.fftn((u.conj() * w).reshape(n))[idx] for w in psi[nn:].astype(np.complex128)]
+                  for u in psi[:nn].astype(np.complex128)])
+    rx = -np.einsum("nvg,mvg,g->nm", f, f.conj(), sv ** 2)
+    s = sv[:, None] * (ei - np.eye(ng)) * sv[None, :]
+    rs = -np.einsum("nvg,gh,mvh->nm", f, s, f.conj(), optimize=True)
+    assert np.linalg.norm(sx.cpu().numpy() - rx) < 2e-6 * np.linalg.norm(rx)
+    assert np.linalg.norm(ss.cpu().numpy() - rs) < 2e-6 * np.linalg.norm(rs)
