@@ -322,6 +322,15 @@ __device__ __forceinline__ double recip(double d) {
   return r;
 }
 
+// v of lane K of each row of 16 lanes, in all its lanes (DPP row_newbcast)
+template <int K>
+__device__ __forceinline__ double row_bcast(double v) {
+  const int2 u = __builtin_bit_cast(int2, v);
+  const int2 b = make_int2(__builtin_amdgcn_update_dpp(0, u.x, 0x150 + K, 0xf, 0xf, true),
+                           __builtin_amdgcn_update_dpp(0, u.y, 0x150 + K, 0xf, 0xf, true));
+  return __builtin_bit_cast(double, b);
+}
+
 // f(integral_constant<int, J>) for J = 0, 1, ...: loop bodies whose index must be a constant
 template <typename F, int... J>
 __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, J...>) {
@@ -342,188 +351,240 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
   __shared__ int bad;
   const int tid = threadIdx.x;
   const int nb = min(NB, n - k0);
-  // this workgroup's PR panel rows below the block, loaded now so that their latency overlaps the
-  // factorisation: thread (pib, pj) holds A[r0 + pib][k0 + pj]
+  const int kp = k0 - p0;                                   // a multiple of NB
+  // Every load is issued before the first use, so that one memory latency covers them all: this workgroup's PR
+  // panel rows below the block (thread (pib, pj) holds A[r0 + pib][k0 + pj]), the block's lower triangle
+  // (rows pib and pib + PR), and the panel's earlier columns of both.
   const int r0 = k0 + nb + (int)blockIdx.x * PR;
   const int pj = tid % NB, pib = tid / NB;
   static_assert(PR * NB == PD_THREADS, "one panel entry per thread");
-  double2 pv = (r0 + pib < n && pj < nb) ? A[(size_t)(r0 + pib) * n + k0 + pj] : make_double2(0.0, 0.0);
-  if (tid == 0) bad = 0;
-  for (int idx = tid; idx < NB * NB; idx += PD_THREADS) {
-    const int i = idx / NB, j = idx % NB;
-    double2 v = make_double2(0.0, 0.0);
-    if (i < nb && j < nb && j <= i) v = A[(size_t)(k0 + i) * n + k0 + j];
-    if (i >= nb && i == j) v = make_double2(1.0, 0.0);      // pad with identity
-    a[i][j] = v;
-    x[i][j] = make_double2(i == j ? 1.0 : 0.0, 0.0);
-  }
-  pa[pib][pj] = pv;
-  // Left-looking inside the panel: the kp = k0 - p0 columns of this panel factored by the earlier steps
-  // are applied here, A[k0:, k0:k0+nb] -= L[k0:, p0:k0] L[k0:k0+nb, p0:k0]^H, to this workgroup's copy of
-  // the diagonal block and to its panel rows, instead of by a separate product after every step.  Five
-  // waves each form one 16 x 16 tile on the FP64 MFMA, with k' = (k, re/im) as in zgemm_kernel:
-  // Re C += [Re A, Im A] . [Re B; Im B] and Im C += [Re A, Im A] . [-Im B; Re B] for C = A B^H.  Waves 0
-  // and 1 take the panel rows' two column halves, waves 2 to 4 the block's lower tiles (0,0), (1,0), (1,1).
-  const int kp = k0 - p0;                                   // a multiple of NB
   static_assert(2 * PR == NB, "rows pib and pib + PR cover the block");
+  const double2 zero2 = make_double2(0.0, 0.0);
+  const double2 pv = (r0 + pib < n && pj < nb) ? A[(size_t)(r0 + pib) * n + k0 + pj] : zero2;
+  double2 bv[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int i = pib + PR * h;
+    bv[h] = i >= nb && i == pj ? make_double2(1.0, 0.0) : zero2;      // padded with the identity
+    if (i < nb && pj <= i) bv[h] = A[(size_t)(k0 + i) * n + k0 + pj];
+  }
+  constexpr int Q = (CHOL_PW - NB) / NB;
+  double2 lu[Q], lw[Q], lv[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    lu[q] = lw[q] = lv[q] = zero2;
+    if (NB * q < kp) {                                       // column k = pj + NB q; rows pib and pib + PR
+      const int k = pj + NB * q;
+      if (pib < nb) lu[q] = L[(size_t)(k0 + pib) * ldl + k];
+      if (pib + PR < nb) lw[q] = L[(size_t)(k0 + pib + PR) * ldl + k];
+      if (r0 + pib < n) lv[q] = L[(size_t)(r0 + pib) * ldl + k];
+    }
+  }
+  a[pib][pj] = bv[0];
+  a[pib + PR][pj] = bv[1];
+  pa[pib][pj] = pv;
+  // Left-looking inside the panel: the kp columns of this panel factored by the earlier steps are applied
+  // here, A[k0:, k0:k0+nb] -= L[k0:, p0:k0] L[k0:k0+nb, p0:k0]^H, to this workgroup's copy of the diagonal
+  // block and to its panel rows, instead of by a separate product after every step.  The FP64 MFMA forms five
+  // 16 x 16 tiles, with k' = (k, re/im) as in zgemm_kernel: Re C += [Re A, Im A] . [Re B; Im B] and
+  // Im C += [Re A, Im A] . [-Im B; Re B] for C = A B^H.  Waves 0 and 1 take the panel rows' two column
+  // halves, waves 2 and 3 the block's tiles (0,0) and (1,0), and waves 4 to 7 a quarter of the columns each of tile
+  // (1,1), so that the four SIMDs carry the same number of MFMAs (five whole tiles on five waves leave
+  // one SIMD with two); the quarters are added where the block is next read.
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, kl = lane >> 4, li = lane & 15;
+  const int comp = kl & 1;
+  const unsigned long long flip = comp ? 0ull : 0x8000000000000000ull;   // Y = [-Im B; Re B]
+  double2 (*quarter)[16][16] = reinterpret_cast<double2 (*)[16][16]>(&x[0][0]);   // x is free until the factor is done
+  static_assert(4 * 16 * 16 <= NB * (NB + 1), "the quarters fit in x");
   if (kp > 0) {
 #pragma unroll
-    for (int q = 0; q < (CHOL_PW - NB) / NB; ++q) {
-      if (NB * q < kp) {                                     // column k = pj + NB q; rows pib and pib + PR
+    for (int q = 0; q < Q; ++q) {
+      if (NB * q < kp) {
         const int k = pj + NB * q;
-        const double2 u = pib < nb ? L[(size_t)(k0 + pib) * ldl + k] : make_double2(0.0, 0.0);
-        const double2 w = pib + PR < nb ? L[(size_t)(k0 + pib + PR) * ldl + k] : make_double2(0.0, 0.0);
-        const double2 v = r0 + pib < n ? L[(size_t)(r0 + pib) * ldl + k] : make_double2(0.0, 0.0);
-        lbp[k][0][pib] = u.x;
-        lbp[k][1][pib] = u.y;
-        lbp[k][0][pib + PR] = w.x;
-        lbp[k][1][pib + PR] = w.y;
-        lrp[k][0][pib] = v.x;
-        lrp[k][1][pib] = v.y;
+        lbp[k][0][pib] = lu[q].x;
+        lbp[k][1][pib] = lu[q].y;
+        lbp[k][0][pib + PR] = lw[q].x;
+        lbp[k][1][pib + PR] = lw[q].y;
+        lrp[k][0][pib] = lv[q].x;
+        lrp[k][1][pib] = lv[q].y;
       }
     }
     __syncthreads();
-    const int wave = tid >> 6, lane = tid & 63, kl = lane >> 4, li = lane & 15;
-    if (wave < 5) {                                          // wave-uniform
-      const bool rows = wave < 2;
-      const int ra = rows ? 0 : (wave == 2 ? 0 : 16);        // first row of the tile (panel rows or block)
-      const int cb = rows ? 16 * wave : (wave == 4 ? 16 : 0);  // first column (block row of B)
-      f64x4 accR = {0.0, 0.0, 0.0, 0.0}, accI = {0.0, 0.0, 0.0, 0.0};
-      const int comp = kl & 1;
-      const unsigned long long flip = comp ? 0ull : 0x8000000000000000ull;   // Y = [-Im B; Re B]
-      for (int s2 = 0; s2 < kp; s2 += 2) {
-        const int kk = s2 + (kl >> 1);
-        const double av = rows ? lrp[kk][comp][li] : lbp[kk][comp][ra + li];
-        const double xv = lbp[kk][comp][cb + li];
-        const double ys = lbp[kk][comp ^ 1][cb + li];
-        const double yv = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, ys) ^ flip);
-        accR = __builtin_amdgcn_mfma_f64_16x16x4f64(av, xv, accR, 0, 0, 0);
-        accI = __builtin_amdgcn_mfma_f64_16x16x4f64(av, yv, accI, 0, 0, 0);
-      }
-      // lane holds tile entry (4 e + kl, li) in register e
+    const bool rows = wave < 2;                              // wave-uniform
+    const int ra = wave < 3 ? 0 : 16;                        // first row of the tile (panel rows or block)
+    const int cb = wave == 1 || wave >= 4 ? 16 : 0;          // first column (block row of B)
+    const int kb = wave < 4 ? 0 : (wave - 4) * (kp / 4), ke = wave < 4 ? kp : kb + kp / 4;   // multiples of 8
+    f64x4 accR = {0.0, 0.0, 0.0, 0.0}, accI = {0.0, 0.0, 0.0, 0.0};
+    // groups of eight columns, the next group's operands read while one is multiplied, in two register sets
+    struct Group {
+      double a[4], x[4], y[4];
+    } g0, g1;
+    const double *ap = rows ? &lrp[kl >> 1][comp][li] : &lbp[kl >> 1][comp][ra + li];
+    const int as = rows ? 2 * (PR + 1) : 2 * (NB + 1);       // doubles per column
+    auto fetch = [&](Group &g, int s8) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = 4 * e + kl;
-        if (rows) {
-          pa[i][cb + li].x -= accR[e];
-          pa[i][cb + li].y -= accI[e];
-        } else if (ra + i >= cb + li) {                      // lower entries of the block only
-          a[ra + i][cb + li].x -= accR[e];
-          a[ra + i][cb + li].y -= accI[e];
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int kk = s8 + 2 * u;
+        g.a[u] = ap[kk * as];
+        g.x[u] = lbp[kk + (kl >> 1)][comp][cb + li];
+        g.y[u] = lbp[kk + (kl >> 1)][comp ^ 1][cb + li];
+      }
+    };
+    auto multiply = [&](Group &g) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        g.y[u] = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, g.y[u]) ^ flip);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        accR = __builtin_amdgcn_mfma_f64_16x16x4f64(g.a[u], g.x[u], accR, 0, 0, 0);
+        accI = __builtin_amdgcn_mfma_f64_16x16x4f64(g.a[u], g.y[u], accI, 0, 0, 0);
+      }
+    };
+    fetch(g0, kb);
+    for (int s8 = kb; s8 < ke; s8 += 16) {
+      if (s8 + 8 < ke) fetch(g1, s8 + 8);
+      multiply(g0);
+      if (s8 + 8 < ke) {
+        if (s8 + 16 < ke) fetch(g0, s8 + 16);
+        multiply(g1);
+      }
+    }
+    // lane holds tile entry (4 e + kl, li) in register e
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = 4 * e + kl;
+      if (rows) {
+        pa[i][cb + li].x -= accR[e];
+        pa[i][cb + li].y -= accI[e];
+      } else if (wave >= 4) {
+        quarter[wave - 4][i][li] = make_double2(accR[e], accI[e]);
+      } else if (ra + i >= li) {                             // lower entries of the block only
+        a[ra + i][li].x -= accR[e];
+        a[ra + i][li].y -= accI[e];
       }
     }
   }
-  // Unblocked right-looking Cholesky on the lower triangle, with unscaled columns: step j subtracts
-  // s_j s_j^H / d_j (d_j the pivot, s_j column j) from the trailing lower triangle.  In elimination form
-  // A = Lu D Lu^H with Lu = I + sum_j (s_j / d_j) e_j^T below the diagonal, so the same step also applies
-  // Lu's j-th elimination to X (started as I): row i > j loses (s_j(i) / d_j) times row j, on the columns
-  // m <= j where row j is non-zero.  After the last step X = Lu^-1, and L = Lu D^1/2, L^-1 = D^-1/2 X
-  // follow by scaling.
+  // Unblocked right-looking elimination of the whole Hermitian block, A = Lu D Lu^H with Lu unit lower: step j
+  // subtracts p_j(i) row_j(m) / d_j from every entry (i, m) below it, with p_j column j, row_j = p_j^H and d_j
+  // the pivot.  The same step applies Lu's j-th elimination to X (started as I): row i > j loses p_j(i) / d_j
+  // times row j of X, on the columns m <= j where that row is non-zero.  After the last step X = Lu^-1, and
+  // L = Lu D^1/2, L^-1 = D^-1/2 X follow by scaling.  Column m of A changes only in the steps j < m and
+  // column m of X only in the steps j >= m, so A and X share the registers: X's column takes the place of
+  // A's in step m, and row j of both together is one row of 32 entries.
   //
-  // The 32 steps form the kernel's latency chain.  The block lives in registers, spread over the first
-  // four waves (the other four only take part in the barriers): lane (m, c) = (tid % 32, tid / 32) keeps
-  // one column on the rows i = 8t + c, so each lane updates four rows per step.  Column m of A changes
-  // only in the steps j < m and column m of X only in the steps j >= m (X is I on it until then), so the
-  // lanes of column m hold A's column until step m, where they pass it on and take X's identity column
-  // in its place.  Step j's column of the factor and row of X go to LDS rows of their own (colj[j],
-  // xrowj[j]), so one barrier per step orders the writes before the reads and no step overwrites what
-  // another still reads.  Every lane then subtracts s_j(i) w on its rows i > j, with w = conj(s_j(m)) / d_j
-  // while it holds A (m > j) and X[j][m] / d_j once it holds X.  On A's columns this also writes rows
-  // j < i < m above the diagonal; those rows are never read, and X's column is zeroed above its diagonal
-  // when it is stored.
-  __shared__ double2 colj[NB][NB + 1], xrowj[NB][NB + 1];
+  // The 32 steps form the kernel's latency chain, so they are laid out for few instructions and little LDS
+  // traffic per step: lane (c, m) = (tid / 16, tid % 16) holds the entries (c, m) and (c, 16 + m).  A row of the
+  // block is then one row of 16 lanes, in which p_j(c) is a register broadcast (DPP) from lane j % 16; the
+  // row of the pivot, divided by it, goes through LDS (w[j], a row of its own for every step, so one
+  // barrier per step orders the writes before the reads), written by the wave that holds it and read as two
+  // words of 16 bytes per lane by the waves that still have rows below it.  Pivots that are not positive
+  // go on as they are (the result is not used) and are found afterwards.
+  // (Four waves with four rows each, the column and the row both through LDS, the pivot checked and the row
+  // bounds tested in every step: 20.4 us per call on average at N = 410 against 13.3 us.)
+  __shared__ double2 w[NB][NB];
+  __shared__ double dv[NB];
+  const int m = tid % 16, c = tid / 16;
+  static_assert(PD_THREADS == 16 * NB && NB == 32, "one row per 16 lanes, two columns per lane");
   {
-    constexpr int C = 8, T = NB / C;                        // row classes, rows per lane
-    const int m = tid % NB, c = tid / NB;
-    const bool fw = c < C;                                  // wave-uniform: one of the factoring waves
-    double2 z[T];
+    double2 z[2], p;                                         // p = p_j(c); the wave's rows are 4 wave ... 4 wave + 3
     __syncthreads();
-    if (fw) {
 #pragma unroll
-      for (int t = 0; t < T; ++t) z[t] = a[C * t + c][m];
-    }
-    int badj = 0;
-    auto step = [&](auto jc) {                                 // step j, a compile-time index
-      constexpr int j = decltype(jc)::value, jt = j / C, jr = j % C;
-      if (fw) {
-        if (m == j) {
+    for (int h = 0; h < 2; ++h) {                            // the upper triangle from the lower one
+      const int k = 16 * h + m;
+      z[h] = a[max(c, k)][min(c, k)];
+      if (kp > 0 && min(c, k) >= 16) {
 #pragma unroll
-          for (int t = jt; t < T; ++t) colj[j][C * t + c] = z[t];     // column j, final from here on
-#pragma unroll
-          for (int t = jt; t < T; ++t) z[t] = make_double2(C * t + c == m ? 1.0 : 0.0, 0.0);   // X's column
+        for (int g = 0; g < 4; ++g) {
+          const double2 v = quarter[g][max(c, k) - 16][min(c, k) - 16];
+          z[h].x -= v.x;
+          z[h].y -= v.y;
         }
-        if (c == jr) xrowj[j][m] = z[jt];                        // row j of X (read only where m <= j)
       }
-      __syncthreads();
-      if (fw) {
-        const double d0 = colj[j][j].x;
-        const double2 q = colj[j][m], xq = xrowj[j][m];
-        double2 pj[T];
-#pragma unroll
-        for (int t = jt; t < T; ++t) pj[t] = colj[j][C * t + c];
-        const bool okd = d0 > 0.0 && isfinite(d0);
-        badj = (!okd && j < nb && badj == 0) ? k0 + j + 1 : badj;
-        const double dinv = recip(okd ? d0 : 1.0);
-        const bool fac = m > j;
-        const double wx = (fac ? q.x : xq.x) * dinv;
-        const double wy = (fac ? -q.y : xq.y) * dinv;
-#pragma unroll
-        for (int t = jt; t < T; ++t) {
-          if (t > jt || c > jr) {                                // rows i > j
-            z[t].x -= pj[t].x * wx - pj[t].y * wy;
-            z[t].y -= pj[t].x * wy + pj[t].y * wx;
-          }
+      if (k > c) z[h].y = -z[h].y;
+    }
+    // p of step j, X's column in place of A's, and row j of w by the wave that holds it
+    auto pivot_row = [&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      p = make_double2(row_bcast<j % 16>(z[j / 16].x), row_bcast<j % 16>(z[j / 16].y));
+      if (m == j % 16) z[j / 16] = make_double2(c == j ? 1.0 : 0.0, 0.0);
+      if (wave == j / 4) {
+        if (c == j) {
+          const double dinv = recip(p.x);
+          w[j][m] = make_double2(z[0].x * dinv, z[0].y * dinv);
+          w[j][16 + m] = make_double2(z[1].x * dinv, z[1].y * dinv);
+          if (m == 0) dv[j] = p.x;
         }
       }
     };
-    static_for(step, std::make_integer_sequence<int, NB>{});
-    if (fw) {
+    auto step = [&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      __syncthreads();
+      if (wave >= (j + 1) / 4) {                               // this wave has rows below j
+        if (wave == (j + 1) / 4) __builtin_amdgcn_s_setprio(3);      // every wave waits for the next pivot row
+        const double2 q0 = w[j][m], q1 = w[j][16 + m];
+        z[0].x = fma(-p.x, q0.x, fma(p.y, q0.y, z[0].x));
+        z[0].y = fma(-p.x, q0.y, fma(-p.y, q0.x, z[0].y));
+        z[1].x = fma(-p.x, q1.x, fma(p.y, q1.y, z[1].x));
+        z[1].y = fma(-p.x, q1.y, fma(-p.y, q1.x, z[1].y));
+        if constexpr (j + 1 < NB) pivot_row(std::integral_constant<int, j + 1>{});
+      }
+    };
+    pivot_row(std::integral_constant<int, 0>{});
+    static_for(step, std::make_integer_sequence<int, NB - 1>{});
+  }
+  __syncthreads();
+  // With r_j = sqrt(d_j): row j of L^-1 is r_j w[j] up to the diagonal, column j of L is r_j conj(w[j]) from it
+  // on.  The first pivot that is not positive and finite (1-based, over the whole matrix) is flagged; it
+  // scales by 1.
+  if (wave == 0) {
+    const bool wrong = tid < nb && !(dv[tid % NB] > 0.0 && isfinite(dv[tid % NB]));
+    const unsigned long long first = __ballot(wrong);
+    if (tid == 0) bad = first ? k0 + __ffsll(first) : 0;
+  }
+  {
+    const double d = dv[c], r = d > 0.0 && isfinite(d) ? sqrt(d) : 1.0;
 #pragma unroll
-      for (int t = 0; t < T; ++t) x[C * t + c][m] = C * t + c >= m ? z[t] : make_double2(0.0, 0.0);
+    for (int h = 0; h < 2; ++h) {
+      const int k = 16 * h + m;
+      const double2 v = w[c][k];
+      x[c][k] = k <= c ? make_double2(v.x * r, v.y * r) : make_double2(0.0, 0.0);
+      if (k >= c) a[k][c] = k == c ? make_double2(r, 0.0) : make_double2(v.x * r, -v.y * r);
     }
-    if (tid == 0) bad = badj;
   }
   __syncthreads();
-  // r_j = sqrt(d_j) (bad pivots were replaced by 1 and flagged); L = column j over r_j, L^-1 = row i of X
-  // over r_i
-  __shared__ double rs[NB];
-  if (tid < NB) {
-    double d = colj[tid][tid].x;
-    if (!(d > 0.0) || !isfinite(d)) d = 1.0;
-    rs[tid] = sqrt(d);
-  }
-  __syncthreads();
-  for (int idx = tid; idx < NB * NB; idx += PD_THREADS) {
-    const int i = idx / NB, j = idx % NB;
-    if (j <= i) {
-      const double r = rs[j];
-      a[i][j] = (i == j) ? make_double2(r, 0.0) : make_double2(colj[j][i].x / r, colj[j][i].y / r);
-    }
-    const double ri = rs[i];
-    x[i][j] = make_double2(x[i][j].x / ri, x[i][j].y / ri);
-  }
-  __syncthreads();
-  if (blockIdx.x == 0) {
-    for (int idx = tid; idx < NB * NB; idx += PD_THREADS) {
+  // Waves 4 to 7 of workgroup 0 store the block while waves 0 to 3 form the panel below it.
+  if (wave >= 4) {
+    if (blockIdx.x != 0) return;
+    for (int idx = tid - 256; idx < NB * NB; idx += PD_THREADS - 256) {
       const int i = idx / NB, j = idx % NB;
       if (i < nb && j < nb) L[(size_t)(k0 + i) * ldl + kp + j] = (j <= i) ? a[i][j] : make_double2(0.0, 0.0);
       linv[idx] = (i < nb && j < nb) ? x[i][j] : make_double2(0.0, 0.0);
     }
-    if (tid == 0 && bad != 0 && *pivot == 0) *pivot = bad;
+    if (tid == 256 && bad != 0 && *pivot == 0) *pivot = bad;
+    return;
   }
-  // panel below the block, one entry per thread (every workgroup factored the block above for itself):
-  // L[r][k0 + j] = sum_{k <= j} A[r][k0 + k] conj(Linv[j][k]).  Linv is lower triangular with its upper
-  // part stored as zeros, so the k loop runs to NB for every thread: no divergence.
+  // L[r][k0 + j] = sum_{k <= j} A[r][k0 + k] conj(Linv[j][k]) (every workgroup factored the block for itself),
+  // the tiles of columns 0-15 and 16-31 on the MFMA: waves 0 and 1 form the first tile's real and imaginary
+  // part (k < 16: Linv is lower triangular, its upper part zeros), waves 2 and 3 the second's.
   if (r0 >= n) return;
-  double2 acc = make_double2(0.0, 0.0);
-#pragma unroll 8
-  for (int k = 0; k < NB; ++k) {
-    const double2 v = x[pj][k], av = pa[pib][k];
-    acc.x += av.x * v.x + av.y * v.y;
-    acc.y += av.y * v.x - av.x * v.y;
+  const int cb = 16 * (wave >> 1), im = wave & 1;
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};
+  for (int s16 = 0; s16 <= cb; s16 += 16) {
+#pragma unroll
+    for (int s2 = 0; s2 < 16; s2 += 2) {
+      const int kk = s16 + s2 + (kl >> 1);
+      const double2 av = pa[li][kk], xv = x[cb + li][kk];
+      const double left = comp ? av.y : av.x;
+      const double right = im ? (comp ? xv.x : -xv.y) : (comp ? xv.y : xv.x);
+      f64x4 &to = s2 & 2 ? acc2 : acc;
+      to = __builtin_amdgcn_mfma_f64_16x16x4f64(left, right, to, 0, 0, 0);
+    }
   }
-  if (r0 + pib < n && pj < nb) L[(size_t)(r0 + pib) * ldl + kp + pj] = acc;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int i = r0 + 4 * e + kl, j = cb + li;
+    if (i < n && j < nb) reinterpret_cast<double *>(&L[(size_t)i * ldl + kp + j])[im] = acc[e] + acc2[e];
+  }
 }
 
 __global__ void fill_identity_kernel(double2 *__restrict__ a, int n, double diag) {

@@ -38,6 +38,27 @@ def test_inverse(gw, n):
     assert np.array_equal(np.triu(got, 1), np.tril(got, -1).conj().T)     # the mirrored triangle
 
 
+# The factorisation of one 32-wide block: a single entry, part of one 16-column half, a block short of or beyond its
+# edge, and blocks after one to three earlier ones of the same panel.  Turning one pivot negative names that one,
+# also in the last (padded) block.  A = Lu D Lu^H with Lu unit lower, so the pivots are D.
+@pytest.mark.parametrize("n", [1, 2, 16, 17, 31, 33, 50, 80, 111])
+def test_diagonal_blocks(gw, n):
+    ctx = gw.Context(0)
+    a = matrix(n)
+    print(f"[case] n={n}", flush=True)
+    got = gw.hpd_inverse(torch.from_numpy(a).cuda(), ctx=ctx).cpu().numpy()
+    ref = np.linalg.inv(a)
+    assert np.linalg.norm(got - ref) < 1e-12 * np.linalg.norm(ref)
+    c = np.linalg.cholesky(a)
+    lu = c / np.diag(c)
+    for bad in sorted({1, n // 2 + 1, n}):
+        d = np.diag(c).real ** 2
+        d[bad - 1] *= -1
+        with pytest.raises(gw.GwError) as e:
+            gw.hpd_inverse(torch.from_numpy(lu * d @ lu.conj().T).cuda(), ctx=ctx)
+        assert e.value.status == 4 and f"pivot {bad} " in str(e.value)
+
+
 @pytest.mark.parametrize("n", [33, 65, 500, 900])
 def test_newton(gw, n):
     a = matrix(n)
