@@ -20,13 +20,15 @@ namespace gwi {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// Two shapes of the product kernel: 64 x 64 tiles with 4 complex k per stage (16 KB of LDS, four workgroups per CU; 8
+// Two shapes of the product kernel: 64 x 64 tiles with 4 complex k per stage (20 KB of LDS, four workgroups per CU; 8
 // complex k per stage: 2% slower for the inverse at N = 4067, 16: 18% slower) for outputs that fill the chip, and
-// 32 x 32 tiles with 16 complex k per stage where they do not: four times the workgroups, and a stage long enough
-// to cover the next one's loads on a CU that holds a single workgroup.
+// 32 x 32 tiles with 16 complex k per stage where they do not: four times the workgroups, and stages long enough
+// to cover the loads of the stage after the next on a CU that holds a single workgroup.  GK: complex k per
+// stage; WGS: workgroups per CU; SETS: stages whose global loads are in registers; AHEAD: steps of two complex k
+// between reading an operand from LDS and multiplying it.
 template <int GT> struct ZgShape;
-template <> struct ZgShape<64> { static constexpr int GK = 4, WGS = 4; };
-template <> struct ZgShape<32> { static constexpr int GK = 16, WGS = 3; };
+template <> struct ZgShape<64> { static constexpr int GK = 4, WGS = 4, SETS = 1, AHEAD = 1; };
+template <> struct ZgShape<32> { static constexpr int GK = 16, WGS = 3, SETS = 2, AHEAD = 4; };
 
 // The second product of a combined launch (lower_only == 3): same A, K, alpha, beta and leading dimension of C, its
 // own B (leading dimension ldb), C and column count, over a full grid of tiles numbered after the first product's
@@ -88,8 +90,9 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
   if (tri_k) kbeg = (max(row0, col0) / GK) * GK;
   const int kl = lane >> 4, li = lane & 15;
   constexpr int PER = (GT * GK) / 256;   // elements of each operand per thread and stage
-  double2 va[PER];
-  TB vb[PER];
+  constexpr int SETS = ZgShape<GT>::SETS;
+  double2 va[SETS][PER];
+  TB vb[SETS][PER];
   // element idx of a stage: A row r / B column c and its k offset kk, in the order that keeps the
   // global reads contiguous for either layout
   auto a_coord = [&](int idx, int &r, int &kk) {
@@ -100,8 +103,13 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
   };
   // Loads keep the raw values; the conjugation of a transposed operand is applied when they are
   // written to LDS, so no instruction waits on a load before the stage's MFMAs have been issued.
-  // Each thread's elements advance by GK along k per stage: running pointers, and no bounds test in
-  // the stages of a whole tile that lie inside [kbeg, kend).
+  // Each thread's elements advance by GK along k per stage: running pointers.  With one set of registers the loads of
+  // stage k + 1 are issued in stage k, without a bounds test in the stages of a whole tile that lie inside
+  // [kbeg, kend).  With two sets they are issued two stages ahead, and without a branch, behind which the
+  // compiler would wait for all outstanding loads, not for the stage's own: an element outside the tile or past
+  // kend reads an address inside its operand, and zero takes its place on the way to LDS.
+  // (N = 410, K = 128, 32 x 32 tiles: 15.2 us with one set, 12.6 us with two; 64 x 64 tiles, where four waves
+  // per SIMD hide the loads: 67.8 TFLOP/s with one set at N = 4067, 66 without the branches.)
   const double2 *pa[PER];
   const TB *pb[PER];
   int ka[PER], kb[PER];
@@ -113,30 +121,41 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
     a_coord(idx, r, kk);
     ka[it] = kk;
     ra[it] = row0 + r < M;
-    const int rr = min(row0 + r, M - 1);   // an address inside A for rows past M (never read)
-    pa[it] = transA ? A + (long long)(kbeg + kk) * lda + rr : A + (long long)rr * lda + kbeg + kk;
+    const int rr = min(row0 + r, M - 1), kr = min(kbeg + kk, kend - 1);
+    pa[it] = transA ? A + (long long)kr * lda + rr : A + (long long)rr * lda + kr;
     b_coord(idx, c, kk);
     kb[it] = kk;
     cb_ok[it] = col0 + c < N;
-    const int cc = min(col0 + c, N - 1);
-    pb[it] = transB ? B + (long long)cc * ldb + kbeg + kk : B + (long long)(kbeg + kk) * ldb + cc;
+    const int cc = min(col0 + c, N - 1), kc = min(kbeg + kk, kend - 1);
+    pb[it] = transB ? B + (long long)cc * ldb + kc : B + (long long)kc * ldb + cc;
   }
   const long long step_a = transA ? (long long)GK * lda : GK, step_b = transB ? GK : (long long)GK * ldb;
   const bool whole = row0 + GT <= M && col0 + GT <= N;
-  auto gload = [&](int k0) {
-    if (whole && k0 + GK <= kend) {        // uniform
+  auto gload = [&](int k0, auto setc) {      // the stage from k0 on, and the pointers to the next
+    constexpr int set = decltype(setc)::value % SETS;
+    if constexpr (SETS == 2) {
 #pragma unroll
       for (int it = 0; it < PER; ++it) {
-        va[it] = *pa[it];
-        vb[it] = *pb[it];
+        va[set][it] = *pa[it];
+        vb[set][it] = *pb[it];
+        pa[it] += k0 + GK + ka[it] < kend ? step_a : 0;
+        pb[it] += k0 + GK + kb[it] < kend ? step_b : 0;
+      }
+      return;
+    }
+    if (whole && k0 + GK <= kend) {          // uniform
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        va[set][it] = *pa[it];
+        vb[set][it] = *pb[it];
       }
     } else {
 #pragma unroll
       for (int it = 0; it < PER; ++it) {
-        va[it] = make_double2(0.0, 0.0);
-        if (ra[it] && k0 + ka[it] < kend) va[it] = *pa[it];
-        vb[it] = TB{0, 0};
-        if (cb_ok[it] && k0 + kb[it] < kend) vb[it] = *pb[it];
+        va[set][it] = make_double2(0.0, 0.0);
+        if (ra[it] && k0 + ka[it] < kend) va[set][it] = *pa[it];
+        vb[set][it] = TB{0, 0};
+        if (cb_ok[it] && k0 + kb[it] < kend) vb[set][it] = *pb[it];
       }
     }
 #pragma unroll
@@ -146,17 +165,25 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
     }
   };
   const double sa = opA & Z_J ? -1.0 : 1.0, sb = opB & Z_J ? -1.0 : 1.0;
-  auto lstore = [&](int buf) {
+  auto lstore = [&](int k0, auto bufc) {
+    constexpr int buf = decltype(bufc)::value, set = buf % SETS;
+    if (SETS == 2 && !(whole && k0 + GK <= kend)) {       // uniform
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        if (!(ra[it] && k0 + ka[it] < kend)) va[set][it] = make_double2(0.0, 0.0);
+        if (!(cb_ok[it] && k0 + kb[it] < kend)) vb[set][it] = TB{0, 0};
+      }
+    }
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
       const int idx = tid + it * 256;
       int r, c, kk;
       a_coord(idx, r, kk);
-      sA[buf][kk][0][r] = va[it].x;
-      sA[buf][kk][1][r] = sa * va[it].y;
+      sA[buf][kk][0][r] = va[set][it].x;
+      sA[buf][kk][1][r] = sa * va[set][it].y;
       b_coord(idx, c, kk);
-      const double by = sb * (double)vb[it].y;
-      sX[buf][kk][0][c] = (double)vb[it].x;
+      const double by = sb * (double)vb[set][it].y;
+      sX[buf][kk][0][c] = (double)vb[set][it].x;
       sX[buf][kk][1][c] = -by;
       sX[buf][kk][2][c] = by;
     }
@@ -185,30 +212,36 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
         accI[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a[i], o.y[j], accI[i][j], 0, 0, 0);
       }
   };
-  // Each step's operands are read from LDS during the step before, and the barrier stands before a stage's last
-  // step, so LDS latency and the wait for the other waves pass while MFMAs run.  Once a wave passes the
-  // barrier of stage k every wave has the stage's operands in registers, so stage k + 1 may refill its buffer.
+  // Each step's operands are read from LDS AHEAD steps before they are multiplied, and the barrier stands before
+  // a stage's last AHEAD steps, so LDS latency and the wait for the other waves pass while MFMAs run.  Once a wave
+  // passes the barrier of stage k every wave has the stage's operands in registers, so stage k + 1 may refill
+  // its buffer.  The reads past the last stage return whatever the buffer holds, unused: with a test around them
+  // the MFMAs behind it waited for all reads (4096^3: 67.7 TFLOP/s with the test, 70.4 without).
+  constexpr int AHEAD = ZgShape<GT>::AHEAD, ST = GK / 2;   // steps per stage
+  static_assert(ST % AHEAD == 0, "a step's slot is its index modulo AHEAD");
   if (kbeg < kend) {
-    gload(kbeg);
-    lstore(0);
+    gload(kbeg, std::integral_constant<int, 0>{});
+    if constexpr (SETS == 2) gload(kbeg + GK, std::integral_constant<int, 1>{});
+    lstore(kbeg, std::integral_constant<int, 0>{});
   }
   __syncthreads();
-  Ops cur = rd(0, 0);
+  Ops q[AHEAD];
+#pragma unroll
+  for (int st = 0; st < AHEAD; ++st) q[st] = rd(0, st);
   auto stage = [&](int k0, auto bufc) {
     constexpr int buf = decltype(bufc)::value;
     const bool more = k0 + GK < kend;
-    if (more) gload(k0 + GK);
+    if (SETS == 2 || more) gload(k0 + SETS * GK, bufc);
 #pragma unroll
-    for (int st = 0; st + 1 < GK / 2; ++st) {
-      const Ops next = rd(buf, st + 1);
+    for (int st = 0; st < ST; ++st) {
+      if (st == ST - AHEAD) {
+        if (more) lstore(k0 + GK, std::integral_constant<int, buf ^ 1>{});
+        __syncthreads();
+      }
+      const Ops cur = q[st % AHEAD];
+      q[st % AHEAD] = st + AHEAD < ST ? rd(buf, st + AHEAD) : rd(buf ^ 1, st + AHEAD - ST);
       mul(cur);
-      cur = next;
     }
-    if (more) lstore(buf ^ 1);
-    __syncthreads();
-    const Ops last = cur;
-    if (more) cur = rd(buf ^ 1, 0);
-    mul(last);
   };
   for (int k0 = kbeg; k0 < kend; k0 += 2 * GK) {
     stage(k0, std::integral_constant<int, 0>{});
@@ -234,12 +267,11 @@ __global__ __launch_bounds__(256, ZgShape<GT>::WGS) void zgemm_kernel(int M, int
 
 // Tile side for a product of `tiles` 64 x 64 tiles.  Small tiles win while four times as many still find a place at
 // once (three per CU), and further for short K, where a 64 x 64 tile's prologue and store are most of its time, and
-// for X^H X, whose tiles are of uneven length.  Inverse, us, 64 only -> this rule: N = 100 154 -> 140, 147 212 -> 181,
-// 410 523 -> 434, 925 1147 -> 961, 1500 1900 -> 1680, 2109 2916 -> 2734, 3071 5139 -> 5097; with small tiles for every
-// product below 1000 (all): 3071 5178 (5334), 4067 9768 against 8660 (all), and 925 x 925 products of the Newton
-// iteration (225 tiles, K = 925) 5.96 ms against 5.20.
+// for X^H X, whose tiles are of uneven length.  Inverse, us, the limits 400, 600, 192 -> these: N = 1800 1870 -> 1723,
+// 2109 2367 -> 2221, 2500 3065 -> 2936, 3071 4325 -> 4280; 2200 in place of 600 takes 4617 at 3071 and 900 takes 4366;
+// 925 x 925 products of the Newton iteration (225 tiles, K = 925) take 4.99 ms, and 5.11 with a limit of 256.
 static int zg_tile(long long tiles, int K, int tri_k) {
-  return tiles < (tri_k ? 400 : K <= 256 ? 600 : 192) ? 32 : 64;
+  return tiles < (tri_k ? 1200 : K <= 256 ? 600 : 192) ? 32 : 64;
 }
 
 template <int GT, typename TB>
@@ -442,10 +474,10 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
     };
     fetch(g0, kb);
     for (int s8 = kb; s8 < ke; s8 += 16) {
-      if (s8 + 8 < ke) fetch(g1, s8 + 8);
+      fetch(g1, min(s8 + 8, ke - 8));                        // unconditional: a branch would make the MFMAs wait for it
       multiply(g0);
       if (s8 + 8 < ke) {
-        if (s8 + 16 < ke) fetch(g0, s8 + 16);
+        fetch(g0, min(s8 + 16, ke - 8));
         multiply(g1);
       }
     }
