@@ -14,6 +14,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "elim32.h"
 #include "gw_internal.h"
 
 namespace gwi {
@@ -344,31 +345,6 @@ constexpr int PR = 16;    // panel rows per workgroup of the diagonal-block kern
 constexpr int CHOL_PW = 128;   // panel width of the factorisation and the substitution
 constexpr int PD_THREADS = PR * NB;   // diagonal-block kernel: eight waves, one panel entry per thread
 
-// 1 / d for a positive finite d: the hardware estimate refined by two Newton steps r <- r + r (1 - d r),
-// each of which squares the relative error (within an ulp or two of the rounded quotient); three
-// dependent operations fewer than the correctly rounded division on the factorisation's latency chain
-__device__ __forceinline__ double recip(double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  r = fma(r, fma(-d, r, 1.0), r);
-  r = fma(r, fma(-d, r, 1.0), r);
-  return r;
-}
-
-// v of lane K of each row of 16 lanes, in all its lanes (DPP row_newbcast)
-template <int K>
-__device__ __forceinline__ double row_bcast(double v) {
-  const int2 u = __builtin_bit_cast(int2, v);
-  const int2 b = make_int2(__builtin_amdgcn_update_dpp(0, u.x, 0x150 + K, 0xf, 0xf, true),
-                           __builtin_amdgcn_update_dpp(0, u.y, 0x150 + K, 0xf, 0xf, true));
-  return __builtin_bit_cast(double, b);
-}
-
-// f(integral_constant<int, J>) for J = 0, 1, ...: loop bodies whose index must be a constant
-template <typename F, int... J>
-__device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, J...>) {
-  (f(std::integral_constant<int, J>{}), ...);
-}
-
 // L is the panel buffer: row i of the panel's columns at L + i ldl
 __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *__restrict__ A, int n, int p0,
                                                                 int k0, double2 *__restrict__ L, int ldl,
@@ -496,21 +472,7 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
       }
     }
   }
-  // Unblocked right-looking elimination of the whole Hermitian block, A = Lu D Lu^H with Lu unit lower: step j
-  // subtracts p_j(i) row_j(m) / d_j from every entry (i, m) below it, with p_j column j, row_j = p_j^H and d_j
-  // the pivot.  The same step applies Lu's j-th elimination to X (started as I): row i > j loses p_j(i) / d_j
-  // times row j of X, on the columns m <= j where that row is non-zero.  After the last step X = Lu^-1, and
-  // L = Lu D^1/2, L^-1 = D^-1/2 X follow by scaling.  Column m of A changes only in the steps j < m and
-  // column m of X only in the steps j >= m, so A and X share the registers: X's column takes the place of
-  // A's in step m, and row j of both together is one row of 32 entries.
-  //
-  // The 32 steps form the kernel's latency chain, so they are laid out for few instructions and little LDS
-  // traffic per step: lane (c, m) = (tid / 16, tid % 16) holds the entries (c, m) and (c, 16 + m).  A row of the
-  // block is then one row of 16 lanes, in which p_j(c) is a register broadcast (DPP) from lane j % 16; the
-  // row of the pivot, divided by it, goes through LDS (w[j], a row of its own for every step, so one
-  // barrier per step orders the writes before the reads), written by the wave that holds it and read as two
-  // words of 16 bytes per lane by the waves that still have rows below it.  Pivots that are not positive
-  // go on as they are (the result is not used) and are found afterwards.
+  // Elimination of the whole block: the kernel's latency chain.
   // (Four waves with four rows each, the column and the row both through LDS, the pivot checked and the row
   // bounds tested in every step: 20.4 us per call on average at N = 410 against 13.3 us.)
   __shared__ double2 w[NB][NB];
@@ -518,7 +480,7 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
   const int m = tid % 16, c = tid / 16;
   static_assert(PD_THREADS == 16 * NB && NB == 32, "one row per 16 lanes, two columns per lane");
   {
-    double2 z[2], p;                                         // p = p_j(c); the wave's rows are 4 wave ... 4 wave + 3
+    double2 z[2];
     __syncthreads();
 #pragma unroll
     for (int h = 0; h < 2; ++h) {                            // the upper triangle from the lower one
@@ -534,35 +496,7 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
       }
       if (k > c) z[h].y = -z[h].y;
     }
-    // p of step j, X's column in place of A's, and row j of w by the wave that holds it
-    auto pivot_row = [&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      p = make_double2(row_bcast<j % 16>(z[j / 16].x), row_bcast<j % 16>(z[j / 16].y));
-      if (m == j % 16) z[j / 16] = make_double2(c == j ? 1.0 : 0.0, 0.0);
-      if (wave == j / 4) {
-        if (c == j) {
-          const double dinv = recip(p.x);
-          w[j][m] = make_double2(z[0].x * dinv, z[0].y * dinv);
-          w[j][16 + m] = make_double2(z[1].x * dinv, z[1].y * dinv);
-          if (m == 0) dv[j] = p.x;
-        }
-      }
-    };
-    auto step = [&](auto jc) {
-      constexpr int j = decltype(jc)::value;
-      __syncthreads();
-      if (wave >= (j + 1) / 4) {                               // this wave has rows below j
-        if (wave == (j + 1) / 4) __builtin_amdgcn_s_setprio(3);      // every wave waits for the next pivot row
-        const double2 q0 = w[j][m], q1 = w[j][16 + m];
-        z[0].x = fma(-p.x, q0.x, fma(p.y, q0.y, z[0].x));
-        z[0].y = fma(-p.x, q0.y, fma(-p.y, q0.x, z[0].y));
-        z[1].x = fma(-p.x, q1.x, fma(p.y, q1.y, z[1].x));
-        z[1].y = fma(-p.x, q1.y, fma(-p.y, q1.x, z[1].y));
-        if constexpr (j + 1 < NB) pivot_row(std::integral_constant<int, j + 1>{});
-      }
-    };
-    pivot_row(std::integral_constant<int, 0>{});
-    static_for(step, std::make_integer_sequence<int, NB - 1>{});
+    eliminate32(z, w, dv, wave, NB, [](double d) { return rcp_nr(d); });
   }
   __syncthreads();
   // With r_j = sqrt(d_j): row j of L^-1 is r_j w[j] up to the diagonal, column j of L is r_j conj(w[j]) from it

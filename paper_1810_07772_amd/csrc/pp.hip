@@ -8,6 +8,7 @@
 // FP64 MFMA GEMM).
 #include <algorithm>
 
+#include "elim32.h"
 #include "gw_internal.h"
 
 namespace gwi {
@@ -304,13 +305,7 @@ __device__ __forceinline__ void gram_sum(const double2 *__restrict__ gpart, int 
 // each (two per iteration) to 102 us (one).  The matrix is the Hermitian part of the sum of nblk partial ones, [b][b] each.
 // Eigenvalues are returned in descending order with their vectors as columns of z (row-major, leading dimension b).
 
-// 1 / x and 1 / sqrt(x), x > 0 normal: the hardware estimate refined by two Newton steps
-__device__ __forceinline__ double rcp_nr(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) r = fma(r, fma(-x, r, 1.0), r);
-  return r;
-}
+// 1 / sqrt(x), x > 0 normal: the hardware estimate refined by two Newton steps
 __device__ __forceinline__ double rsqrt_nr(double x) {
   double r = __builtin_amdgcn_rsq(x);
 #pragma unroll
@@ -493,72 +488,44 @@ __global__ __launch_bounds__(512) void herm_jacobi_kernel(const double2 *__restr
 // are close to orthogonal once the iteration settles, so W u stays close to them and the next Rayleigh-Ritz
 // problem close to diagonal, which saves its Jacobi sweeps.  A direction whose squared length falls below
 // 1e-14 of its column's once the earlier columns are projected out is dropped (u gets a zero column), as is a zero
-// column.  One workgroup; lane (m, c) of 32 x 8 keeps column m's rows 8 t + c, one barrier per pivot (the
-// elimination form of the Cholesky panels' diagonal blocks: a lane holds column m of G until pivot m and then
-// that column of L's inverse).
-__global__ __launch_bounds__(256) void block_chol_kernel(const double2 *__restrict__ gpart, int nblk, int b,
+// column.  One workgroup; the pivots are its time.
+// (b = 24 from 64 partial matrices: 28.2 us with a column per lane, one pivot's column and row through LDS; 24.4 us in
+// this form, 12 us of it the sum.)
+__global__ __launch_bounds__(512) void block_chol_kernel(const double2 *__restrict__ gpart, int nblk, int b,
                                                          double2 *__restrict__ u) {
   __shared__ double2 g[JMAX][JMAX + 1];
-  __shared__ double2 colj[JMAX][JMAX + 1], rowj[JMAX][JMAX + 1];
-  __shared__ double dinv[JMAX];
-  const int tid = threadIdx.x, m = tid % JMAX, c = tid / JMAX;
-  constexpr int T = JMAX / 8;
-  gram_sum<256>(gpart, nblk, b, g);
+  __shared__ double2 w[JMAX][JMAX];
+  __shared__ double dinv[JMAX], dv[JMAX];
+  const int tid = threadIdx.x, m = tid % 16, c = tid / 16;
+  static_assert(JMAX == 32, "eliminate32");
+  gram_sum<512>(gpart, nblk, b, g);
   __syncthreads();
   if (tid < JMAX) {
     const double d = g[tid][tid].x;
     dinv[tid] = d > 0.0 && isfinite(d) ? 1.0 / sqrt(d) : 0.0;
   }
   __syncthreads();
-  double2 v[T];
+  double2 z[2];
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const int i = 8 * t + c;
-    const double2 a = g[i][m], h = g[m][i];
-    const double f = 0.5 * dinv[i] * dinv[m];
-    v[t] = make_double2(f * (a.x + h.x), f * (a.y - h.y));
+  for (int h = 0; h < 2; ++h) {
+    const int k = 16 * h + m;
+    const double2 a = g[c][k], t = g[k][c];
+    const double f = 0.5 * dinv[c] * dinv[k];
+    z[h] = make_double2(f * (a.x + t.x), f * (a.y - t.y));
   }
-  for (int j = 0; j < b; ++j) {
-    if (m == j) {
-#pragma unroll
-      for (int t = 0; t < T; ++t) {
-        const int i = 8 * t + c;
-        colj[j][i] = v[t];
-        v[t] = make_double2(i == m ? 1.0 : 0.0, 0.0);
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < T; ++t)
-      if (8 * t + c == j) rowj[j][m] = v[t];           // row j of L's inverse (used where m <= j)
-    __syncthreads();
-    const double d = colj[j][j].x;
-    const bool ok = d > 1e-14;
-    const double di = ok ? rcp_nr(d) : 0.0;
-    const double2 q = m > j ? colj[j][m] : rowj[j][m];
-    const double wx = q.x * di, wy = (m > j ? -q.y : q.y) * di;
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int i = 8 * t + c;
-      if (i > j) {
-        const double2 s = colj[j][i];
-        v[t].x -= s.x * wx - s.y * wy;
-        v[t].y -= s.x * wy + s.y * wx;
-      }
-    }
-  }
-  // row i of the inverse times D^-1/2 of pivot i; u[m][i] = dinv[m] conj(Linv[i][m])
-  __shared__ double piv[JMAX];
-  if (tid < b) {
-    const double d = colj[tid][tid].x;
-    piv[tid] = d > 1e-14 ? 1.0 / sqrt(d) : 0.0;
-  }
+  eliminate32(z, w, dv, __builtin_amdgcn_readfirstlane(tid >> 6), b, [](double d) { return d > 1e-14 ? rcp_nr(d) : 0.0; });
   __syncthreads();
+  // row c of the inverse of L is sqrt(d_c) w[c]; u[k][c] = dinv[k] conj(Linv[c][k])
+  if (c < b) {
+    const double d = dv[c], r = d > 1e-14 ? sqrt(d) : 0.0;
 #pragma unroll
-  for (int t = 0; t < T; ++t) {
-    const int i = 8 * t + c;
-    if (i < b && m < b) {
-      const double f = i >= m ? dinv[m] * piv[i] : 0.0;
-      u[m * b + i] = make_double2(f * v[t].x, -f * v[t].y);
+    for (int h = 0; h < 2; ++h) {
+      const int k = 16 * h + m;
+      if (k < b) {
+        const double f = c >= k ? dinv[k] * r : 0.0;
+        const double2 v = w[c][k];
+        u[k * b + c] = make_double2(f * v.x, -f * v.y);
+      }
     }
   }
 }
@@ -863,7 +830,7 @@ hipError_t launch_herm_jacobi(const double2 *gpart, int ng, int b, double *evals
 
 hipError_t launch_block_chol(const double2 *gpart, int ng, int b, double2 *u, hipStream_t s) {
   if (b < 1 || b > JMAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(block_chol_kernel, dim3(1), dim3(256), 0, s, gpart, gram_blocks(ng), b, u);
+  hipLaunchKernelGGL(block_chol_kernel, dim3(1), dim3(512), 0, s, gpart, gram_blocks(ng), b, u);
   return hipGetLastError();
 }
 
