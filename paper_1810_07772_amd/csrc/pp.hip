@@ -194,52 +194,70 @@ static int thin_splits(int M, int K) {
 }
 size_t thin_part_elems(int M, int N, int K) { return (size_t)thin_splits(M, K) * M * N; }
 
-// The share of X^H Y of the rows [blockIdx.x chunk, +chunk) into gpart[block].  Thread (i, j0) of 32 x 8 forms the
-// entries (i, j0 + 8 q); 16 rows at a time in LDS.
-constexpr int GRAM_ROWS = 16;
-constexpr int GRAM_BLOCKS = 64;  // partial Gram matrices that their consumer, one workgroup, adds
-__global__ __launch_bounds__(256) void block_gram_kernel(const double2 *__restrict__ x, const double2 *__restrict__ y,
+// The share of X^H Y of the rows [blockIdx.x chunk, +chunk) into gpart[block].  Up to GRAM_ROWS rows of both at a
+// time in LDS, all their loads in flight together; each of eight waves forms the real or imaginary part of one
+// 16 x 16 tile on the FP64 MFMA, with k' = (row, re/im): Re = [Re X; Im X]^T [Re Y; Im Y],
+// Im = [Re X; Im X]^T [Im Y; -Re Y].  Bound by latency, and so is its consumer, one workgroup that reads every
+// partial matrix: the split is the one that keeps their sum shortest.  3071 rows, b = 24: 64 blocks of
+// 48 rows on the vector units took 8.6 us, their sum 12 us of the consumer's; 32 of 96 rows 6.6 us and 7 (48 blocks
+// 5.5 and 10, 24 blocks 8.7 and 6).
+constexpr int GRAM_ROWS = 96;
+constexpr int GRAM_BLOCKS = 32;
+__global__ __launch_bounds__(512) void block_gram_kernel(const double2 *__restrict__ x, const double2 *__restrict__ y,
                                                          int ng, int b, int chunk, double2 *__restrict__ gpart) {
   __shared__ double2 sx[GRAM_ROWS][JMAX + 1], sy[GRAM_ROWS][JMAX + 1];
-  const int tid = threadIdx.x, i = tid % JMAX, j0 = tid / JMAX;
+  static_assert(JMAX == 32, "two tiles a side");
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int kl = lane >> 4, li = lane & 15, comp = kl & 1, kh = kl >> 1;
+  const int ti = 16 * (wave & 1), tj = 16 * ((wave >> 1) & 1), im = wave >> 2;
+  const unsigned long long flip = comp && im ? 0x8000000000000000ull : 0ull;
   const int r_beg = blockIdx.x * chunk, r_end = min(ng, r_beg + chunk);
-  double2 acc[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) acc[q] = make_double2(0.0, 0.0);
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
   for (int r0 = r_beg; r0 < r_end; r0 += GRAM_ROWS) {
     if (r0 != r_beg) __syncthreads();
+    const int i = tid % JMAX;
+    double2 xv[GRAM_ROWS / 16], yv[GRAM_ROWS / 16];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int rr = j0 + 8 * h, r = r0 + rr;
-      double2 xv = make_double2(0.0, 0.0), yv = xv;
+    for (int h = 0; h < GRAM_ROWS / 16; ++h) {
+      const int r = r0 + tid / JMAX + 16 * h;
+      xv[h] = yv[h] = make_double2(0.0, 0.0);
       if (r < r_end && i < b) {
         const size_t at = (size_t)r * b + i;
-        xv = x[at];
-        yv = y[at];
+        xv[h] = x[at];
+        yv[h] = y[at];
       }
-      sx[rr][i] = xv;
-      sy[rr][i] = yv;
+    }
+#pragma unroll
+    for (int h = 0; h < GRAM_ROWS / 16; ++h) {
+      sx[tid / JMAX + 16 * h][i] = xv[h];
+      sy[tid / JMAX + 16 * h][i] = yv[h];
     }
     __syncthreads();
-#pragma unroll 4
-    for (int rr = 0; rr < GRAM_ROWS; ++rr) {
-      const double2 u = sx[rr][i];
+    if (ti < b && tj < b) {                              // uniform over the wave
+      const double *px = &reinterpret_cast<const double *>(&sx[kh][ti + li])[comp];
+      const double *py = &reinterpret_cast<const double *>(&sy[kh][tj + li])[comp ^ im];
+      const int groups = (min(GRAM_ROWS, r_end - r0) + 15) / 16;
+      for (int g = 0; g < groups; ++g) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const double2 v = sy[rr][j0 + 8 * q];        // conj(u) v
-        acc[q].x += u.x * v.x + u.y * v.y;
-        acc[q].y += u.x * v.y - u.y * v.x;
+        for (int t = 0; t < 8; ++t) {                    // two rows each
+          const int at = (16 * g + 2 * t) * 2 * (JMAX + 1);
+          const double yy = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, py[at]) ^ flip);
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(px[at], yy, acc, 0, 0, 0);
+        }
       }
     }
   }
+  // lane holds tile entry (4 e + kl, li) in register e
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (i < b && j0 + 8 * q < b) gpart[(size_t)blockIdx.x * b * b + i * b + j0 + 8 * q] = acc[q];
+  for (int e = 0; e < 4; ++e) {
+    const int i = ti + 4 * e + kl, j = tj + li;
+    if (i < b && j < b) reinterpret_cast<double *>(gpart + (size_t)blockIdx.x * b * b + i * b + j)[im] = acc[e];
+  }
 }
 
 static int gram_chunk(int ng) {
-  const int c = std::max(3 * GRAM_ROWS, (ng + GRAM_BLOCKS - 1) / GRAM_BLOCKS);
-  return (c + GRAM_ROWS - 1) / GRAM_ROWS * GRAM_ROWS;
+  const int c = std::max(48, (ng + GRAM_BLOCKS - 1) / GRAM_BLOCKS);
+  return (c + 15) / 16 * 16;
 }
 static int gram_blocks(int ng) { return (ng + gram_chunk(ng) - 1) / gram_chunk(ng); }
 size_t gram_part_elems(int ng, int b) { return (size_t)gram_blocks(ng) * b * b; }
@@ -490,7 +508,7 @@ __global__ __launch_bounds__(512) void herm_jacobi_kernel(const double2 *__restr
 // 1e-14 of its column's once the earlier columns are projected out is dropped (u gets a zero column), as is a zero
 // column.  One workgroup; the pivots are its time.
 // (b = 24 from 64 partial matrices: 28.2 us with a column per lane, one pivot's column and row through LDS; 24.4 us in
-// this form, 12 us of it the sum.)
+// this form, 12 us of it the sum, and 16.7 us from 32.)
 __global__ __launch_bounds__(512) void block_chol_kernel(const double2 *__restrict__ gpart, int nblk, int b,
                                                          double2 *__restrict__ u) {
   __shared__ double2 g[JMAX][JMAX + 1];
@@ -818,7 +836,7 @@ hipError_t launch_thin_sum(const double2 *part, int M, int N, int K, double alph
 }
 
 hipError_t launch_block_gram(const double2 *x, const double2 *y, int ng, int b, double2 *gpart, hipStream_t s) {
-  hipLaunchKernelGGL(block_gram_kernel, dim3(gram_blocks(ng)), dim3(256), 0, s, x, y, ng, b, gram_chunk(ng), gpart);
+  hipLaunchKernelGGL(block_gram_kernel, dim3(gram_blocks(ng)), dim3(512), 0, s, x, y, ng, b, gram_chunk(ng), gpart);
   return hipGetLastError();
 }
 

@@ -148,3 +148,27 @@ def test_block_sizes(gw, ng, nm, rank):
         gap = np.min(np.abs(np.delete(w, j) - w[j])) if ng > 1 else 1.0
         assert abs(abs(np.vdot(v[:, j], modes[:, j])) - 1.0) < max(1e-9, (1e-9 * abs(w[0]) / gap) ** 2)
     assert np.all(om.cpu().numpy() > 0) and res <= 1e-10
+
+
+# More rows than one pass of the Gram kernel's workgroups holds (96 each, 32 workgroups): a matrix of known
+# eigenvectors and values, tolerances as above.
+@pytest.mark.parametrize("ng", [3071, 3100])
+def test_long_blocks(gw, ng):
+    rng = np.random.default_rng(ng)
+    n, q, nm, rank = (20, 20, 20), np.array([0.1, 0.2, 0.3]), 8, 40
+    mill = gs.sphere(n, count=ng, q=q)
+    a = gs.cell_side(20)
+    sv = orc.coulomb_sqrt(n, a, q, mill)
+    u = np.linalg.qr(rng.standard_normal((ng, rank)) + 1j * rng.standard_normal((ng, rank)))[0]
+    w = -1.0 / (0.2 + np.arange(rank)) ** 1.5
+    eps_inv = np.eye(ng) + (u * w) @ u.conj().T / (sv[:, None] * sv[None, :])
+    psi = rng.standard_normal((3, 20 ** 3)) + 1j * rng.standard_normal((3, 20 ** 3))
+    psi = (psi / np.sqrt((np.abs(psi) ** 2).sum(1))[:, None]).astype(np.complex64)
+    print(f"[case] ng={ng}", flush=True)
+    dev = lambda v: torch.from_numpy(np.ascontiguousarray(v)).to("cuda:0")
+    sig, _, modes, _, res = gw.plasmon_pole(dev(eps_inv), n, a, q, mill, dev(psi), n_modes=nm)
+    modes = modes.cpu().numpy()
+    assert np.max(np.abs(sig.cpu().numpy() - w[:nm])) < 1e-12 * abs(w[0]) and res <= 1e-10
+    for j in range(nm):
+        gap = np.min(np.abs(np.delete(w, j) - w[j]))
+        assert abs(abs(np.vdot(u[:, j], modes[:, j])) - 1.0) < max(1e-9, (1e-9 * abs(w[0]) / gap) ** 2)
