@@ -102,8 +102,9 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // 64 rows per workgroup, 16 complex k per stage, so a workgroup has 16 KB of A in flight in registers while the
 // FP64 MFMAs of the stage before run (k' = (k, re/im) as in zgemm_kernel: Re C += [Re A, Im A] . [Re B; -Im B],
 // Im C += [Re A, Im A] . [Im B; Re B]); wave w owns rows 16 w .. +15 and all 32 columns.  Bound by memory and the
-// matrix cores alike (16 bytes and 256 flop per entry of A).  The 64 x 64 tiles of zgemm_kernel, half of whose
-// columns are padding here, took 103 us for 3071 x 3071 by 32 columns; 59 us.
+// matrix cores alike (16 bytes and 256 flop per entry of A).  3071 x 3071 by 24 columns: 103 us in the 64 x 64 tiles
+// of zgemm_kernel, half of whose columns are padding here, 59 us so with one stage of loads in flight, 50 us with two
+// and no branch between a load and its use.
 constexpr int TPM = 64, TPK = 16;
 __global__ __launch_bounds__(256) void thin_product_kernel(int M, int N, int K, const double2 *__restrict__ A,
                                                            long long lda, const double2 *__restrict__ B, int ldb,
@@ -113,35 +114,37 @@ __global__ __launch_bounds__(256) void thin_product_kernel(int M, int N, int K, 
   __shared__ double sB[2][TPK][2][LB];            // [Re B; -Im B]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, kl = lane >> 4, li = lane & 15;
   const int row0 = blockIdx.x * TPM, k_beg = blockIdx.y * kchunk, k_end = min(K, k_beg + kchunk);
-  double2 va[4], vb[2];
+  double2 va[2][4], vb[2][2];                     // the loads of two stages
   const int ar = tid / TPK, ak = tid % TPK;       // A: rows ar + 16 i, offset ak
   const int bc = tid % JMAX, bk = tid / JMAX;     // B: k offsets bk + 8 i, column bc
-  auto gload = [&](int k0) {
+  // Every stage loads, without a branch (behind one the compiler waits for all outstanding loads): elements outside
+  // the operands read an address inside, and zero takes their place on the way to LDS.
+  auto gload = [&](int k0, auto setc) {
+    constexpr int set = decltype(setc)::value;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = row0 + ar + 16 * i, k = k0 + ak;
-      const bool in = r < M && k < k_end;
-      va[i] = A[(long long)min(r, M - 1) * lda + min(k, K - 1)];
-      if (!in) va[i] = make_double2(0.0, 0.0);
-    }
+    for (int i = 0; i < 4; ++i) va[set][i] = A[(long long)min(row0 + ar + 16 * i, M - 1) * lda + min(k0 + ak, k_end - 1)];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int k = k0 + bk + 8 * i;
-      const bool in = bc < N && k < k_end;
-      vb[i] = B[(long long)min(k, K - 1) * ldb + min(bc, N - 1)];
-      if (!in) vb[i] = make_double2(0.0, 0.0);
-    }
+    for (int i = 0; i < 2; ++i) vb[set][i] = B[(long long)min(k0 + bk + 8 * i, k_end - 1) * ldb + min(bc, N - 1)];
   };
-  auto lstore = [&](int buf) {
+  auto lstore = [&](int k0, auto bufc) {
+    constexpr int buf = decltype(bufc)::value;
+    if (k0 + TPK > k_end || N < JMAX) {           // uniform; rows past M are not stored
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (k0 + ak >= k_end) va[buf][i] = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        if (bc >= N || k0 + bk + 8 * i >= k_end) vb[buf][i] = make_double2(0.0, 0.0);
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      sA[buf][ak][0][ar + 16 * i] = va[i].x;
-      sA[buf][ak][1][ar + 16 * i] = va[i].y;
+      sA[buf][ak][0][ar + 16 * i] = va[buf][i].x;
+      sA[buf][ak][1][ar + 16 * i] = va[buf][i].y;
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      sB[buf][bk + 8 * i][0][bc] = vb[i].x;
-      sB[buf][bk + 8 * i][1][bc] = -vb[i].y;
+      sB[buf][bk + 8 * i][0][bc] = vb[buf][i].x;
+      sB[buf][bk + 8 * i][1][bc] = -vb[buf][i].y;
     }
   };
   f64x4 accR[2], accI[2];
@@ -149,32 +152,54 @@ __global__ __launch_bounds__(256) void thin_product_kernel(int M, int N, int K, 
   for (int c = 0; c < 2; ++c)
 #pragma unroll
     for (int e = 0; e < 4; ++e) { accR[c][e] = 0.0; accI[c][e] = 0.0; }
-  const int comp = kl & 1;
+  const int comp = kl & 1, kh = kl >> 1;
   const unsigned long long flip = comp ? 0ull : 0x8000000000000000ull;   // [Im B; Re B] = [-X_1; X_0]
-  int buf = 0;
-  if (k_beg < k_end) {
-    gload(k_beg);
-    lstore(0);
-  }
-  __syncthreads();
-  for (int k0 = k_beg; k0 < k_end; k0 += TPK) {
-    const bool more = k0 + TPK < k_end;
-    if (more) gload(k0 + TPK);
+  // Operands are read AHEAD steps of two k before they are multiplied, the barrier stands before a stage's last AHEAD
+  // steps, and the reads past the last stage are unused, as in zgemm_kernel.
+  struct Ops { double a, x[2], y[2]; };
+  constexpr int AHEAD = 2, ST = TPK / 2;
+  auto rd = [&](int buf, int s) {
+    const int kk = 2 * s + kh;
+    Ops o;
+    o.a = sA[buf][kk][comp][16 * wave + li];
 #pragma unroll
-    for (int s = 0; s < TPK / 2; ++s) {
-      const int kk = 2 * s + (kl >> 1);
-      const double av = sA[buf][kk][comp][16 * wave + li];
+    for (int c = 0; c < 2; ++c) {
+      o.x[c] = sB[buf][kk][comp][16 * c + li];
+      o.y[c] = sB[buf][kk][comp ^ 1][16 * c + li];
+    }
+    return o;
+  };
+  Ops q[AHEAD];
+  auto stage = [&](int k0, auto bufc) {
+    constexpr int buf = decltype(bufc)::value;
+    gload(k0 + 2 * TPK, bufc);
+#pragma unroll
+    for (int s = 0; s < ST; ++s) {
+      if (s == ST - AHEAD) {
+        if (k0 + TPK < k_end) lstore(k0 + TPK, std::integral_constant<int, buf ^ 1>{});
+        __syncthreads();
+      }
+      const Ops o = q[s % AHEAD];
+      q[s % AHEAD] = s + AHEAD < ST ? rd(buf, s + AHEAD) : rd(buf ^ 1, s + AHEAD - ST);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        const double xv = sB[buf][kk][comp][16 * c + li], ys = sB[buf][kk][comp ^ 1][16 * c + li];
-        const double yv = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, ys) ^ flip);
-        accR[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, xv, accR[c], 0, 0, 0);
-        accI[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, yv, accI[c], 0, 0, 0);
+        const double yv = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, o.y[c]) ^ flip);
+        accR[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a, o.x[c], accR[c], 0, 0, 0);
+        accI[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(o.a, yv, accI[c], 0, 0, 0);
       }
     }
-    if (more) lstore(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
+  };
+  if (k_beg < k_end) {
+    gload(k_beg, std::integral_constant<int, 0>{});
+    gload(k_beg + TPK, std::integral_constant<int, 1>{});
+    lstore(k_beg, std::integral_constant<int, 0>{});
+  }
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < AHEAD; ++s) q[s] = rd(0, s);
+  for (int k0 = k_beg; k0 < k_end; k0 += 2 * TPK) {
+    stage(k0, std::integral_constant<int, 0>{});
+    if (k0 + TPK < k_end) stage(k0 + TPK, std::integral_constant<int, 1>{});
   }
   double2 *out = part + (size_t)blockIdx.y * M * N;
 #pragma unroll
@@ -186,8 +211,8 @@ __global__ __launch_bounds__(256) void thin_product_kernel(int M, int N, int K, 
     }
 }
 
-// Splits of K: three workgroups per CU (their LDS fits; at 3071 rows 58.6 us against 67.9 with two and 77.6 with one and
-// a half), at least four stages each.
+// Splits of K: three workgroups per CU (their LDS fits; at 3071 rows, before the second stage of loads, 58.6 us against 67.9 with two
+// and 77.6 with one and a half), at least four stages each.
 static int thin_splits(int M, int K) {
   const int tiles = (M + TPM - 1) / TPM;
   return std::max(1, std::min(768 / tiles, K / (4 * TPK)));
