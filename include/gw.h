@@ -154,7 +154,9 @@ int gw_polarizability_r(gw_ctx *ctx, const gw_c32 *psi_v, int nv, const gw_c32 *
  * cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc).  Inputs, output, options and results
  * are those of gw_polarizability_r, except that opts->tile = -1 means the default
- * tile of the precision (no autotuner lookup).  The energies, the pair-scale table
+ * tile of the precision (no autotuner lookup, and every tile in one piece: where
+ * gw_polarizability_r cuts tiles along K to fill the device, the two agree to
+ * rounding, not bit for bit).  The energies, the pair-scale table
  * and the FP16 band exponents go to a fixed 8 MiB device array that each GPU holds
  * for the life of the process (its address is resolved once per device by
  * gw_create): calls needing more than 8 MiB, i.e. about
