@@ -298,8 +298,9 @@ static hipError_t zgemm(int M, int N, int K, const double2 *A, long long lda, in
                         int lower_only, int tri_k, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const long long mt = (M + 63) / 64, nt = (N + 63) / 64, tiles = lower_only ? nt * (nt + 1) / 2 : mt * nt;
-  return zg_tile(tiles, K, tri_k) == 32 ? zgemm_t<32>(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, lower_only, tri_k, s)
-                              : zgemm_t<64>(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, lower_only, tri_k, s);
+  return zg_tile(tiles, K, tri_k) == 32
+             ? zgemm_t<32>(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, lower_only, tri_k, s)
+             : zgemm_t<64>(M, N, K, A, lda, opA, B, ldb, opB, C, ldc, alpha, beta, lower_only, tri_k, s);
 }
 
 // C1 = alpha A B1^H + beta C1 on the lower tiles of the square M x M C1, and C2 = alpha A B2 + beta C2 on

@@ -52,8 +52,8 @@ __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, J..
 // Out: w[j][m] = row_j(m) inv(d_j), A's entries right of the diagonal, X's on it (X_jj = 1) and left of it; dv[j] = d_j;
 // for j < n, complete after the caller's next barrier.  wave is the uniform tid / 64.
 template <typename Inv>
-__device__ __forceinline__ void eliminate32(double2 (&z)[2], double2 (*__restrict__ w)[32], double *__restrict__ dv, int wave,
-                                            int n, Inv inv) {
+__device__ __forceinline__ void eliminate32(double2 (&z)[2], double2 (*__restrict__ w)[32],
+                                            double *__restrict__ dv, int wave, int n, Inv inv) {
   const int m = threadIdx.x % 16, c = threadIdx.x / 16;    // the wave's rows are 4 wave ... 4 wave + 3
   double2 p;                                               // p_j(c)
   // p of step j, X's column in place of A's, and row j of w by the wave that holds it

@@ -211,8 +211,8 @@ __global__ __launch_bounds__(256) void thin_product_kernel(int M, int N, int K, 
     }
 }
 
-// Splits of K: three workgroups per CU (their LDS fits; at 3071 rows, before the second stage of loads, 58.6 us against 67.9 with two
-// and 77.6 with one and a half), at least four stages each.
+// Splits of K: three workgroups per CU (their LDS fits; at 3071 rows, before the second stage of loads, 58.6 us against
+// 67.9 with two and 77.6 with one and a half), at least four stages each.
 static int thin_splits(int M, int K) {
   const int tiles = (M + TPM - 1) / TPM;
   return std::max(1, std::min(768 / tiles, K / (4 * TPK)));
