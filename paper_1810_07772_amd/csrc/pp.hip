@@ -342,21 +342,21 @@ __device__ __forceinline__ void gram_sum(const double2 *__restrict__ gpart, int 
 // A round's time is its serial chain, so it has one barrier: thread (k, l) of the first four waves computes
 // the rotation of pair l from A, takes that of pair k from the lane that holds it (its own row of 16 lanes
 // has all 16 pairs), and applies both sides to the 2 x 2 block (pair k, pair l) in registers, from one
-// copy of A in LDS to the other.  The other four waves apply the previous round's rotations to V meanwhile.
+// copy of A in LDS to the other.  The other four waves apply the previous round's rotations to V meanwhile, at a
+// lower wave priority, since they share the SIMDs.
 // (With the rotations passed through LDS and one barrier each for them, the columns and the rows, a round took
-// 2.4 us; about 0.6 us.)  At 3071 G and 16 modes the solves of the iteration went from 522 us
-// each (two per iteration) to 102 us (one).  The matrix is the Hermitian part of the sum of nblk partial ones, [b][b] each.
+// 2.4 us; about 0.55 us.)  At 3071 G and 16 modes the solves of the iteration went from 522 us each (two per
+// iteration) to 102 us (one), 95 us with fewer partial matrices to add, and 91 us with the priority and the
+// shorter square roots.  The matrix is the Hermitian part of the sum of nblk partial ones, [b][b] each.
 // Eigenvalues are returned in descending order with their vectors as columns of z (row-major, leading dimension b).
 
-// 1 / sqrt(x), x > 0 normal: the hardware estimate refined by two Newton steps
+// 1 / sqrt(x), x > 0 normal: the hardware estimate r (5e-8 relative) refined by r (1 + e / 2 + 3 e^2 / 8),
+// e = 1 - x r^2, the binomial series to third order: 1.4e-16 at most over 2^20 values, as with two Newton
+// steps, and two dependent operations fewer
 __device__ __forceinline__ double rsqrt_nr(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const double e = fma(-x * r, r, 1.0);
-    r = fma(0.5 * r, e, r);
-  }
-  return r;
+  const double r = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * r, r, 1.0);
+  return fma(r * e, fma(0.375, e, 0.5), r);
 }
 
 // Sum of v over the 64 lanes of a wave.
@@ -407,6 +407,7 @@ __global__ __launch_bounds__(512) void herm_jacobi_kernel(const double2 *__restr
   }
   __syncthreads();
   int cur = 0, done = 0;               // A's current copy; rounds done
+  if (wave < 4) __builtin_amdgcn_s_setprio(3);     // V's waves share their SIMDs and have time to spare
   const int l = lane & 15;             // this lane's pair of columns, and of rows (first four waves) k
   const int k = (wave & 3) * 4 + (lane >> 4), i0 = (wave & 3) * 8 + (lane >> 4) * 2;
   JacobiPair cols(l < half ? l : 0, m), rows(k < half ? k : 0, m);
