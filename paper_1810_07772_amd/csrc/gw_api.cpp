@@ -392,8 +392,6 @@ int upload_plan(gw_ctx *ctx, gw_grid g, const int *miller, int ng, int map_slot,
 
 int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, hipStream_t s) {
   const size_t nm = (size_t)ng * 3;
-  void *d;
-  GW_STATUS(ws_get(ctx, slot, nm * sizeof(int), &d, s));
   std::unique_ptr<MillerCacheEntry> &e = ctx->millers[slot];
   if (!e) {
     e.reset(new (std::nothrow) MillerCacheEntry());
@@ -402,11 +400,15 @@ int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, h
       return GW_E_NOMEM;
     }
   }
+  // Not valid from here until the copy is queued: a slot that has to grow for the list is freed first, and where the
+  // larger one does not fit the next buffer may have the freed one's address.
+  if (e->stream != (void *)s || e->miller.size() != nm || !std::equal(miller, miller + nm, e->miller.begin()))
+    e->dev = nullptr;
+  void *d;
+  GW_STATUS(ws_get(ctx, slot, nm * sizeof(int), &d, s));
   *dev = (int *)d;
-  if (e->dev == d && e->stream == (void *)s && e->miller.size() == nm &&
-      std::equal(miller, miller + nm, e->miller.begin()))
-    return GW_OK;
-  e->dev = nullptr;                       // not valid until the copy is queued
+  if (e->dev == d) return GW_OK;
+  e->dev = nullptr;
   e->miller.assign(miller, miller + nm);
   GW_HIP(ctx, hipMemcpyAsync(d, e->miller.data(), nm * sizeof(int), hipMemcpyHostToDevice, s));
   e->dev = d;

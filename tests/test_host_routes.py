@@ -1,0 +1,88 @@
+"""The library's host side without a GPU: workspace, uploads, the choice of kernels and what a stream capture records,
+with tests/fake_hip.cpp in the place of the HIP runtime.  Each test runs in a process of its own, into which neither
+torch nor the real runtime's calls come."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+LIB = os.path.join(os.path.dirname(HERE), "paper_1810_07772_amd", "libgw.so")
+
+PRELUDE = """
+import ctypes as C, importlib.util, os, sys
+import numpy as np
+sys.path.insert(0, %(root)r)
+import gwsynth as gs
+fake = C.CDLL(%(fake)r, mode=C.RTLD_GLOBAL)
+for f, r in (("fake_recorded_src", C.c_void_p), ("fake_recorded_dst", C.c_void_p), ("fake_launch_name", C.c_char_p),
+             ("fake_recorded_bytes", C.c_size_t)):
+    getattr(fake, f).restype = r
+spec = importlib.util.spec_from_file_location("gw_lib", os.path.join(%(root)r, "paper_1810_07772_amd", "_lib.py"))
+L = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(L)
+lib = L.load()
+S = C.c_void_p(4096)                       # a stream of the caller's
+
+def ctx(cap=0):
+    h = C.c_void_p()
+    assert lib.gw_create(C.byref(h), 0, cap) == 0
+    return h
+
+def ptr(a):
+    return a.ctypes.data_as(C.c_void_p)
+
+def buf(n):                                # "device" memory of the caller's
+    return np.zeros(n, np.uint8)
+
+def launches(sub=""):
+    names = [fake.fake_launch_name(i).decode() for i in range(fake.fake_launches())]
+    return [n for n in names if sub in n]
+
+def capture(on):
+    fake.fake_capture(S, int(on))
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not os.path.exists(LIB):
+        pytest.fail("libgw.so is not built (run __graft_entry__.build())")
+    out = tmp_path_factory.mktemp("fake") / "libfake_hip.so"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", os.path.join(HERE, "fake_hip.cpp"), "-o", str(out)],
+                   check=True)
+    prelude = PRELUDE % {"root": os.path.dirname(HERE), "fake": str(out)}
+
+    script = out.with_name("case.py")
+
+    def go(code):
+        script.write_text(prelude + code)
+        r = subprocess.run([sys.executable, str(script)], capture_output=True, text=True, timeout=100)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return go
+
+
+MILLER = """
+a = np.ascontiguousarray(gs.sphere((12, 12, 12), count=20), np.int32)
+b = np.ascontiguousarray(gs.sphere((12, 12, 12), count=300), np.int32)
+grid, q = L.Grid(12, 12, 12, 10.0), np.array([0.1, 0.2, 0.3])
+p, e = buf(8 * 300 * 300), buf(16 * 300 * 300)
+def epsilon(h, m):
+    return lib.gw_epsilon(h, ptr(p), len(m), grid, ptr(q), ptr(m), 1.0, ptr(e), S)
+"""
+
+
+def test_miller_list_after_a_slot_that_could_not_grow(run):
+    """The longer list's buffer does not fit on the device once; the first list is copied again, although the next
+    buffer has the freed one's address."""
+    run(MILLER + """
+h = ctx()
+assert epsilon(h, a) == 0
+fake.fake_clear()
+fake.fake_limit(3000)
+assert epsilon(h, b) == 2                  # 3600 bytes
+fake.fake_limit(0)
+assert epsilon(h, a) == 0 and fake.fake_copies() == 1
+assert epsilon(h, a) == 0 and fake.fake_copies() == 1
+""")
