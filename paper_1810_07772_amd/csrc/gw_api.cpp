@@ -390,6 +390,16 @@ int upload_plan(gw_ctx *ctx, gw_grid g, const int *miller, int ng, int map_slot,
   return GW_OK;
 }
 
+// Whether work on s is being recorded into a graph (or cannot be known not to be).
+bool stream_capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
 int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, hipStream_t s) {
   const size_t nm = (size_t)ng * 3;
   std::unique_ptr<MillerCacheEntry> &e = ctx->millers[slot];
@@ -407,7 +417,13 @@ int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, h
   void *d;
   GW_STATUS(ws_get(ctx, slot, nm * sizeof(int), &d, s));
   *dev = (int *)d;
-  if (e->dev == d) return GW_OK;
+  if (stream_capturing(s)) {
+    e->in_graph = true;
+    e->dev = nullptr;
+    GW_HIP(ctx, hipMemcpyAsync(d, miller, nm * sizeof(int), hipMemcpyHostToDevice, s));
+    return GW_OK;
+  }
+  if (e->dev == d && !e->in_graph) return GW_OK;
   e->dev = nullptr;
   e->miller.assign(miller, miller + nm);
   GW_HIP(ctx, hipMemcpyAsync(d, e->miller.data(), nm * sizeof(int), hipMemcpyHostToDevice, s));

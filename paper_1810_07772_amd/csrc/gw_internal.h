@@ -255,10 +255,12 @@ struct PlanCacheEntry {
 struct MillerCacheEntry {
   std::vector<int> miller;
   void *stream = nullptr, *dev = nullptr;
+  bool in_graph = false;     // a captured graph copies its own list into the slot at every replay
 };
 // The device copy of a Miller list in workspace slot `slot`, which nothing else writes: a call with the list and
 // stream of the slot's last upload reuses it (a copy from pageable memory would block the host until the stream
-// has come to it).
+// has come to it).  A call that a stream captures records a copy of the caller's list, as its replays may follow calls
+// with another one; from then on every call copies.
 int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, hipStream_t s);
 struct SphereBuffers {
   float2 *a1, *a2, *ph, *pht, *q;  // pass intermediates, P^ [ng][nr], its transpose, Q [ng][ng]
@@ -300,6 +302,7 @@ int upload_plan(gw_ctx *ctx, gw_grid g, const int *miller, int ng, int map_slot,
 // ---- shared host helpers of gw_api.cpp used by the batched path ---------------------------------
 int api_ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s);
 void *api_ws_try(gw_ctx *ctx, int slot, size_t bytes, hipStream_t s);
+bool stream_capturing(hipStream_t s);
 int api_check_energies(gw_ctx *ctx, const double *e_v, int nv, const double *e_c, int nc);
 int api_check_sphere(gw_ctx *ctx, gw_grid g, const int *m, int ng);
 int api_check_opts(gw_ctx *ctx, const gw_opts *o);

@@ -86,3 +86,30 @@ fake.fake_limit(0)
 assert epsilon(h, a) == 0 and fake.fake_copies() == 1
 assert epsilon(h, a) == 0 and fake.fake_copies() == 1
 """)
+
+
+def test_miller_list_under_capture(run):
+    """A captured call records its list's copy whatever lies in the slot; as the graph may rewrite the slot at any time
+    from then on, later calls copy theirs."""
+    run(MILLER + """
+c = a[::-1].copy()
+h = ctx()
+assert epsilon(h, a) == 0
+capture(True)
+fake.fake_clear()
+assert epsilon(h, a) == 0 and fake.fake_recorded() == 1
+assert fake.fake_recorded_src(0) == a.ctypes.data and fake.fake_recorded_bytes(0) == a.nbytes
+capture(False)
+slot = fake.fake_recorded_dst(0)
+held = lambda: np.ctypeslib.as_array((C.c_int * a.size).from_address(slot)).reshape(a.shape)
+assert epsilon(h, c) == 0 and np.array_equal(held(), c)
+fake.fake_replay()
+assert epsilon(h, c) == 0 and np.array_equal(held(), c)
+h = ctx()                                  # the first use of a list is a captured one
+assert epsilon(h, c) == 0
+capture(True)
+assert epsilon(h, a) == 0
+capture(False)
+fake.fake_clear()
+assert epsilon(h, a) == 0 and fake.fake_copies() == 1 and fake.fake_violations() == 0
+""")
