@@ -28,7 +28,10 @@
  *   the caller's `head` value (the wings become 0).
  * - Ownership: the caller owns every buffer it passes and the library never
  *   frees them.  The context owns its device workspace, bounded by the cap
- *   given at creation.  Host arrays are read during the call only.
+ *   given at creation.  Host arrays are read during the call only, except by a
+ *   call that its stream captures: the graph then holds copies from e_v, e_c and
+ *   (where the Coulomb factor or the tail's features are formed) g_miller, and
+ *   reads those arrays at every replay.
  * - Streams: `stream` is a hipStream_t (NULL = the default stream).  Calls are
  *   asynchronous on that stream unless stated otherwise.
  * - Errors: every call returns a gw_status; no exception crosses the ABI.  All

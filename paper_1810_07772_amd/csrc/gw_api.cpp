@@ -115,8 +115,8 @@ int ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
   return st;
 }
 
-// A buffer of kOptionalSlots, or NULL where it does not fit under the cap or on the device.  The next ws_get
-// may free it, so it is asked for right before the launches that use it.
+// A buffer that the call can do without, or NULL where it does not fit under the cap or on the device.  The next
+// ws_get may free one of kOptionalSlots, so it is asked for right before the launches that use it.
 void *ws_try(gw_ctx *ctx, int slot, size_t bytes, hipStream_t s) {
   void *p = nullptr;
   if (ws_alloc(ctx, slot, bytes, &p, s) == GW_OK) return p;
@@ -659,7 +659,10 @@ int gw_pair_products(gw_ctx *ctx, const gw_c32 *psi_v, int nv, const gw_c32 *psi
   GW_STATUS(check_energies(ctx, e_v, nv, e_c, nc));
   if (ctx->device < 0) return GW_OK;
   hipStream_t s = as_stream(stream);
-  if (pair_energies_fit(nv, nc)) {
+  if (pair_energies_fit(nv, nc) && !stream_capturing(s)) {
+    // room for the scale table, which the call forms when it is captured and can then not allocate
+    (void)ws_try(ctx, WS_ENERGY, (size_t)(nv + nc) * sizeof(double), s);
+    (void)ws_try(ctx, WS_SCALE, scale_table_floats(nv, nc) * sizeof(float), s);
     GW_HIP(ctx, launch_pair_products_e((const float2 *)psi_v, nv, (const float2 *)psi_c, nc, nr, e_v, e_c, prefactor,
                                        (float2 *)f_out, s));
     return GW_OK;

@@ -35,7 +35,8 @@ __global__ void scale_table_kernel(const double *__restrict__ e_v, int nv, const
 // Energies in the kernel's own arguments (a copy made at the launch) instead of two copies from pageable memory,
 // which the host stages and waits for: 12 x 200 bands on 27^3 138.8 -> 136.2 us a call, 12^3 FP32 build 130 -> 127.
 // ENERGY_ARG doubles fit beside the other arguments into the 4 KB a launch takes; a longer list goes in several
-// launches, and one of more than ENERGY_LAUNCHES by copies.
+// launches, and one of more than ENERGY_LAUNCHES by copies.  Under capture any list goes by copies: a graph whose
+// launches held the energies would replay those of the capture, copies read the caller's arrays at every replay.
 constexpr int ENERGY_ARG = 488, ENERGY_LAUNCHES = 4;
 struct EnergyArg { double e[ENERGY_ARG]; };
 
@@ -54,17 +55,18 @@ static hipError_t upload_part(const double *e, int n, double *dst, hipStream_t s
   return hipGetLastError();
 }
 
-// dev[0 .. nv) = e_v, dev[nv .. nv + nc) = e_c (host arrays, read before the call returns)
+// dev[0 .. nv) = e_v, dev[nv .. nv + nc) = e_c (host arrays, read before the call returns unless it is captured)
 hipError_t upload_energies(const double *e_v, int nv, const double *e_c, int nc, double *dev, hipStream_t s) {
   const long long n = (long long)nv + nc;
-  if (n <= ENERGY_ARG) {
+  const bool by_args = n <= (long long)ENERGY_ARG * ENERGY_LAUNCHES && !stream_capturing(s);
+  if (by_args && n <= ENERGY_ARG) {
     EnergyArg a;
     std::copy(e_v, e_v + nv, a.e);
     std::copy(e_c, e_c + nc, a.e + nv);
     hipLaunchKernelGGL(energies_kernel, dim3(((int)n + 255) / 256), dim3(256), 0, s, a, (int)n, dev);
     return hipGetLastError();
   }
-  if (n <= (long long)ENERGY_ARG * ENERGY_LAUNCHES) {
+  if (by_args) {
     const hipError_t e = upload_part(e_v, nv, dev, s);
     return e != hipSuccess ? e : upload_part(e_c, nc, dev + nv, s);
   }

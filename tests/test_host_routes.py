@@ -113,3 +113,27 @@ capture(False)
 fake.fake_clear()
 assert epsilon(h, a) == 0 and fake.fake_copies() == 1 and fake.fake_violations() == 0
 """)
+
+
+def test_energies_under_capture(run):
+    """However many energies there are, a captured call records copies of the caller's arrays, which its replays read;
+    an eager call has made the room that it needs."""
+    run("""
+opts = L._opts("fp32")
+for nv, nc in ((3, 20), (40, 600), (100, 2000)):
+    ev, ec = np.linspace(-0.5, -0.1, nv), np.linspace(0.1, 1.0, nc)
+    args = (ptr(buf(8)), nv, ptr(buf(8)), nc, 64, ptr(ev), ptr(ec))
+    for call in (lambda h: lib.gw_polarizability_r_noalloc(h, *args, C.byref(opts), ptr(buf(8)), S),
+                 lambda h: lib.gw_polarizability_r(h, *args, C.byref(opts), ptr(buf(8)), S),
+                 lambda h: lib.gw_pair_products(h, *args, 1.0, ptr(buf(8)), S)):
+        h = ctx()
+        assert call(h) == 0
+        fake.fake_clear()
+        capture(True)
+        assert call(h) == 0
+        capture(False)
+        got = {(fake.fake_recorded_src(i), fake.fake_recorded_bytes(i)) for i in range(fake.fake_recorded())}
+        assert got == {(ev.ctypes.data, ev.nbytes), (ec.ctypes.data, ec.nbytes)}, (nv, nc, got)
+        assert not launches("energies_kernel") and launches("scale_table_kernel")
+        assert fake.fake_violations() == 0
+""")
