@@ -236,14 +236,25 @@ def _orbitals(psi_v, psi_c, e_v, e_c, nr=None):
     return nv, nc, nrv
 
 
+# Converted host arrays of captured calls: a graph reads them at every replay, and nothing else holds them.
+_captured: list = []
+
+
+def _host(a, dtype):
+    out = np.ascontiguousarray(np.asarray(a, dtype=dtype))
+    if out is not a:
+        import torch
+        if torch.cuda.is_initialized() and torch.cuda.is_current_stream_capturing():
+            _captured.append(out)
+    return out, out.ctypes.data_as(C.c_void_p)
+
+
 def _host_f64(a, name):
-    a = np.ascontiguousarray(np.asarray(a, dtype=np.float64))
-    return a, a.ctypes.data_as(C.c_void_p)
+    return _host(a, np.float64)
 
 
 def _host_i32(a, name):
-    a = np.ascontiguousarray(np.asarray(a, dtype=np.int32))
-    return a, a.ctypes.data_as(C.c_void_p)
+    return _host(a, np.int32)
 
 
 def _stream(t):

@@ -113,3 +113,18 @@ def test_other_entry_point_shapes():
     raises_value(lambda: gw.sigma_static(c64(2, NR), c64(3, NR - 1), N, 5.0, Q, MILLER), "grid points")
     raises_value(lambda: gw.sigma_static(c64(2, NR), c64(3, NR), N, 5.0, Q, MILLER, eps_inv=c128(2, 2)), "eps_inv")
     raises_value(lambda: gw.sigma_sex_modes(c64(2, NR), c64(3, NR), N, MILLER, modes, torch.zeros(3)), "sigma")
+
+
+def test_converted_host_arrays_of_captured_calls_are_kept(monkeypatch):
+    """A captured graph reads the call's host arrays at every replay: the binding holds what it converted itself, and
+    leaves the caller's own arrays to the caller."""
+    L = gw._lib
+    monkeypatch.setattr(L, "_captured", [], raising=False)
+    own, _ = L._host_f64(np.linspace(0.0, 1.0, 4), "e_v")
+    L._host_f64([0.0, 1.0], "e_v")
+    assert L._captured == []
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
+    assert L._host_f64(own, "e_v")[0] is own and L._captured == []
+    kept = [L._host_f64([0.0, 1.0], "e_v")[0], L._host_i32(np.zeros((4, 3), np.int64), "g_miller")[0]]
+    assert len(L._captured) == 2 and all(x is y for x, y in zip(kept, L._captured))
