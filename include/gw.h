@@ -147,6 +147,11 @@ int gw_pair_products(gw_ctx *ctx, const gw_c32 *psi_v, int nv, const gw_c32 *psi
  * update, K = nv*nc):  P(r,r') = -sum_vc conj(f_vc(r)) f_vc(r')  (+ P if accumulate).
  *   p_rr [nr][nr] complex64, both triangles written (P is Hermitian).
  *   The pair products are formed inside the update kernel and never stored.
+ *   With opts->tile = -1, tiles that would leave most of the device idle may be
+ *   cut along K, which needs a workspace buffer for their parts: where that does
+ *   not fit under the cap or on the device, and in a call that its stream
+ *   captures, every tile runs in one piece, and P agrees to rounding with that of
+ *   a call that cut them, not bit for bit.
  * ------------------------------------------------------------------------- */
 int gw_polarizability_r(gw_ctx *ctx, const gw_c32 *psi_v, int nv, const gw_c32 *psi_c, int nc, int nr,
                         const double *e_v, const double *e_c, const gw_opts *opts, gw_c32 *p_rr,
@@ -406,7 +411,9 @@ int gw_tail_forward(gw_ctx *ctx, const gw_mlp *w, const float *feat, int ng, flo
 
 /* One training step on one system: forward, loss (written to the device float *loss_out),
  * gradient (opt->grad), Adam update of opt->master and refresh of w->w, w->b; opt->step += 1.
- * target [ng][ng] must be Hermitian (as gw_tail_target makes it). */
+ * target [ng][ng] must be Hermitian (as gw_tail_target makes it).
+ * The gradient is the sum of partial ones, fewer of them where their workspace buffer does not fit
+ * under the cap or on the device or where the stream captures the call: equal to rounding. */
 int gw_tail_train_step(gw_ctx *ctx, gw_mlp *w, gw_adam *opt, const float *feat, const gw_c32 *target, int ng,
                        float *loss_out, void *stream);
 

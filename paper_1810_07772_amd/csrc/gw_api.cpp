@@ -57,6 +57,20 @@ void set_err(gw_ctx *ctx, const char *fmt, ...) {
 
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
+}  // namespace
+
+// Whether work on s is being recorded into a graph (or cannot be known not to be).
+bool gwi::stream_capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+namespace {
+
 // grow-only workspace slot
 int ws_alloc(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
   if (bytes == 0) bytes = 256;
@@ -108,7 +122,7 @@ bool ws_release_optional(gw_ctx *ctx) {
 // A buffer that the call needs: where it does not fit, the optional buffers make room for it.
 int ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
   int st = ws_alloc(ctx, slot, bytes, out, s);
-  if (st == GW_E_NOMEM && ws_release_optional(ctx)) {
+  if (st == GW_E_NOMEM && !stream_capturing(s) && ws_release_optional(ctx)) {
     ctx->err.clear();
     st = ws_alloc(ctx, slot, bytes, out, s);
   }
@@ -116,9 +130,11 @@ int ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
 }
 
 // A buffer that the call can do without, or NULL where it does not fit under the cap or on the device.  The next
-// ws_get may free one of kOptionalSlots, so it is asked for right before the launches that use it.
+// ws_get may free one of kOptionalSlots, so it is asked for right before the launches that use it.  A captured
+// call gets none: an allocation would end the capture, and a graph would go on using what a later call frees.
 void *ws_try(gw_ctx *ctx, int slot, size_t bytes, hipStream_t s) {
   void *p = nullptr;
+  if (stream_capturing(s)) return nullptr;
   if (ws_alloc(ctx, slot, bytes, &p, s) == GW_OK) return p;
   ctx->err.clear();
   return nullptr;
@@ -388,16 +404,6 @@ int upload_plan(gw_ctx *ctx, gw_grid g, const int *miller, int ng, int map_slot,
   p.bc = pl.bc; p.a1_elems = pl.a1_elems; p.a2_elems = pl.a2_elems;
   p.plane = pl.plane; p.nk2 = pl.nk2; p.y1_elems = pl.y1_elems;
   return GW_OK;
-}
-
-// Whether work on s is being recorded into a graph (or cannot be known not to be).
-bool stream_capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return true;
-  }
-  return st != hipStreamCaptureStatusNone;
 }
 
 int upload_miller(gw_ctx *ctx, const int *miller, int ng, int slot, int **dev, hipStream_t s) {

@@ -137,3 +137,40 @@ for nv, nc in ((3, 20), (40, 600), (100, 2000)):
         assert not launches("energies_kernel") and launches("scale_table_kernel")
         assert fake.fake_violations() == 0
 """)
+
+
+OPTIONAL = """
+opts = L._opts("fp32")
+ev, ec = np.linspace(-0.5, -0.1, 8), np.linspace(0.1, 1.0, 64)
+def update(h, o=opts):                     # 105 tiles, which are cut
+    return lib.gw_polarizability_r(h, ptr(buf(8)), 8, ptr(buf(8)), 64, 1728, ptr(ev), ptr(ec), C.byref(o), ptr(buf(8)), S)
+u = C.c_void_p(256)
+def train(h, n=600):
+    w, o = L.Mlp(256, 256, 256, 5), L.Adam(256, 256, 256, 256, 0, 1e-3, 0.9, 0.999, 1e-8)
+    return lib.gw_tail_train_step(h, C.byref(w), C.byref(o), u, u, n, u, S)
+def backward():
+    return [fake.fake_launch_grid(i) for i in range(fake.fake_launches())
+            if b"tail_backward" in fake.fake_launch_name(i)]
+"""
+
+
+def test_optional_buffers_under_capture(run):
+    """A captured call neither allocates a buffer that it can do without nor uses one, which later calls may free."""
+    run(OPTIONAL + """
+h = ctx()
+assert update(h) == 0 and launches("part_sum") and train(h) == 0 and backward() == [38]
+capture(True)
+fake.fake_clear()
+assert update(h) == 0 and launches("herk_fp32") and not launches("part_sum")
+assert train(h) == 0 and backward() == [7]
+capture(False)
+h = ctx()                                  # the buffers that the calls need are there, the others not
+assert update(h, L._opts("fp32", tile=4)) == 0
+fake.fake_limit(3 << 20)
+assert train(h) == 0
+fake.fake_limit(0)
+capture(True)
+assert update(h) == 0 and train(h) == 0
+capture(False)
+assert fake.fake_violations() == 0
+""")
