@@ -1532,10 +1532,14 @@ int herk_default_tile(int precision, int nr) {
 // that round as it is with `rounds` rounds of shorter parts, each of which stores its sums (tile_us), plus the
 // pass that adds them: its launch, its reads, and the chain of a tile's parts.  Measured, update alone (us,
 // uncut -> cut): FP32 12^3, 8 x 64 bands 170 -> 113 (105 tiles, S = 2); FP32 10^3, 20 x 100 669 -> 134 (36 tiles,
-// S = 7); BF16 16^3, 32 x 128 982 -> 678 (272 blocks, the last 16 with S = 16); BF16 18^3, 16 x 160 992 -> 832
+// S = 7); BF16 16^3, 32 x 128 982 -> 678 (272 blocks, the last 16 with S = 13); BF16 18^3, 16 x 160 992 -> 832
 // (552 blocks, the last 40 with S = 6).  Cutting loses where a tile has few stages or the last round is nearly
 // full: BF16 15^3, 10 x 60 (196 blocks of 40 stages) 110 -> 140, FP32 24^3, 4 x 20 1214 -> 1249.  Over 15 shapes
-// and three precisions the rule's choice is within 7% of the best S.
+// and three precisions the rule's choice is within 7% of the best S.  Memory: a cut has to win 1% of the whole
+// update (without that, 209 of the 33489 blocks of BF16 36^3, 128 x 1024 took 603 MB for 0.1%), and the parts hold at
+// most PART_BYTES (132 blocks with 8192 stages each, 14^3 with 128 x 1024 bands, would take 865 MB with S = 25 for
+// 45% of the update by the rule's estimate, and get 242 MB with S = 7 for 42%).
+constexpr long long PART_BYTES = 256ll << 20;
 struct HerkPlan { int whole, count, S; };
 static HerkPlan herk_plan(int precision, int nr, int nv, int nc) {
   constexpr int CUS = 256;
@@ -1549,8 +1553,10 @@ static HerkPlan herk_plan(int precision, int nr, int nv, int nc) {
   if (rem == 0) return p;
   const double stage_us = wide ? 1.55 : 5.3;             // one stage of a tile
   const double tile_us = wide ? 12.0 : 6.0;              // every CU storing one part
-  double best = 0.95 * (nch * stage_us + tile_us);
-  for (int S = 2; S <= 32 && 2 * S <= nch; ++S) {
+  const double round_us = nch * stage_us + tile_us;
+  double best = round_us - std::max(0.05, 0.01 * ((tiles + CUS - 1) / CUS)) * round_us;
+  const long long tile_bytes = (wide ? 8ll : 4ll) * QPART * (long long)sizeof(f32x4);
+  for (int S = 2; S <= 32 && 2 * S <= nch && rem * S * tile_bytes <= PART_BYTES; ++S) {
     const int rounds = (rem * S + CUS - 1) / CUS;
     const double sum_us = 6.0 + tile_us * rem * S / CUS + 1.5 * S;
     const double cost = rounds * ((nch + S - 1) / S * stage_us + tile_us) + sum_us;

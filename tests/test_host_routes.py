@@ -174,3 +174,28 @@ assert update(h) == 0 and train(h) == 0
 capture(False)
 assert fake.fake_violations() == 0
 """)
+
+
+def test_parts_of_cut_tiles_are_worth_their_memory(run):
+    """Tiles are cut where that wins 1% of the update, with parts of at most 256 MiB; the shapes that the GPU tests of
+    cut tiles use are, as their comment says."""
+    run("""
+def shape(prec, nr, nv, nc):
+    h, ev, ec = ctx(), np.linspace(-0.5, -0.1, nv), np.linspace(0.1, 1.0, nc)
+    fake.fake_clear()
+    o = L._opts(prec)
+    assert lib.gw_polarizability_r(h, ptr(buf(8)), nv, ptr(buf(8)), nc, nr, ptr(ev), ptr(ec), C.byref(o), ptr(buf(8)),
+                                   S) == 0
+    n = [fake.fake_launch_grid(i) for i in range(fake.fake_launches()) if b"gwi" in fake.fake_launch_name(i)
+         and b"herk" in fake.fake_launch_name(i)]
+    held = lib.gw_workspace_bytes(h)
+    lib.gw_destroy(h)
+    return n, held
+assert shape("bf16", 46656, 128, 1024)[0] == [33489] and shape("bf16", 46656, 128, 1024)[1] < 2 << 20
+n, held = shape("bf16", 2752, 128, 1024)
+assert n == [132 * 7, 132 * 8] and held < 258 << 20, (n, held)
+# whole rounds, parts, their sums
+assert shape("fp32", 1728, 8, 64)[0] == [210, 420]
+for prec in ("bf16", "fp16"):
+    assert shape(prec, 4096, 4, 64)[0] == [256, 64, 128]
+""")
