@@ -355,7 +355,9 @@ int gw_graph_captures(const gw_ctx *ctx);
  * the fastest for (device arch, nr, nv, nc, precision) in the context (and
  * appends it to the file named by the environment variable GW_AUTOTUNE_CACHE
  * when set; that file is read back by later contexts).  Calls with tile = -1
- * then use the tuned tile.  p_scratch: device [nr][nr] complex64 the timing
+ * then use the tuned tile; where that is the default one, its tiles may be cut
+ * along K as in an untuned call, and its time is the better of the two ways.
+ * p_scratch: device [nr][nr] complex64 the timing
  * launches overwrite.  best_tile (host) receives the choice; times_ms (host,
  * [gw_tile_count()], optional) the time of each tile (-1 where the tile does
  * not implement the precision).  Synchronises `stream`.

@@ -506,8 +506,12 @@ int polarizability_r_impl(gw_ctx *ctx, const float2 *psi_v, int nv, const float2
     GW_HIP(ctx, launch_band_exponents(psi_v, nv, psi_c, nc, nr, scale, scale_ld(nc), bexp, s));
   }
   int tile = o.tile;
-  if (tile < 0) tile = tuned_tile(ctx, nr, nv, nc, o.precision);   // -1 when nothing is tuned: the default
-  // a tile that the caller or the tuner chose runs as it is; the default one may share its last tiles
+  if (tile < 0) {
+    tile = tuned_tile(ctx, nr, nv, nc, o.precision);   // -1 when nothing is tuned: the default
+    if (tile == herk_default_tile(o.precision, nr)) tile = -1;
+  }
+  // a tile that the caller chose, or the tuner over the default one, runs as it is; the default one may share its
+  // last tiles
   void *part = nullptr;
   const size_t pbytes = tile < 0 ? herk_part_bytes(o.precision, nr, nv, nc) : 0;
   if (pbytes) part = ws_try(ctx, WS_HERK_PART, pbytes, s);

@@ -8,9 +8,11 @@
 // job j run on the other P buffer, so the latency-bound FP64 factorisation hides under the next
 // update.  Only kernels are captured (no memsets, no allocation, no host copies).
 //
-// The autotuner times every update tile of the requested precision on a reduced K (the same
-// N_r and Nc, at most 8 occupied bands) and caches the fastest per (arch, N_r, Nv, Nc, precision)
-// in the context, and in the file named by GW_AUTOTUNE_CACHE when that variable is set.
+// The autotuner times every update tile of the requested precision, the default one also with its last tiles cut
+// along K, on a reduced K (the same N_r and Nc, at most 8 occupied bands) and caches the fastest per
+// (arch, N_r, Nv, Nc, precision) in the context, and in the file named by GW_AUTOTUNE_CACHE when that variable is set.
+// A tuned tile that is the default one runs as that does, cut where the rule says so.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -136,17 +138,28 @@ int autotune_impl(gw_ctx *ctx, const float2 *psi_v, int nv, const float2 *psi_c,
   GWX_HIP(ctx, hipEventCreate(&e1));
   int bt = -1;
   float bms = 0.f;
-  for (int t = 0; t < herk_tile_count(); ++t) {
-    if (times_ms) times_ms[t] = -1.0;
-    if (!herk_tile_supports(t, precision)) continue;
-    float ms = 0.f;
+  auto time_tile = [&](int t, void *part, float *ms) -> int {
     for (int rep = 0; rep < 2; ++rep) {       // first launch warms caches and code
       GWX_HIP(ctx, hipEventRecord(e0, s));
       GWX_HIP(ctx, launch_herk(precision, t, psi_v, psi_c, (const float *)sb, ldsc, (const int *)bx, (float2 *)pb, nr,
-                             nt, nc, 0, s));   // writes the whole P scratch
+                             nt, nc, 0, s, part));   // writes the whole P scratch
       GWX_HIP(ctx, hipEventRecord(e1, s));
       GWX_HIP(ctx, hipEventSynchronize(e1));
-      GWX_HIP(ctx, hipEventElapsedTime(&ms, e0, e1));
+      GWX_HIP(ctx, hipEventElapsedTime(ms, e0, e1));
+    }
+    return GW_OK;
+  };
+  const size_t pbytes = herk_part_bytes(precision, nr, nt, nc);
+  void *part = pbytes ? api_ws_try(ctx, WS_HERK_PART, pbytes, s) : nullptr;
+  const int cut = part ? herk_default_tile(precision, nr) : -1;
+  for (int t = 0; t < herk_tile_count(); ++t) {
+    if (times_ms) times_ms[t] = -1.0;
+    if (!herk_tile_supports(t, precision)) continue;
+    float ms = 0.f, cms = 0.f;
+    GWX_STATUS(time_tile(t, nullptr, &ms));
+    if (t == cut) {
+      GWX_STATUS(time_tile(t, part, &cms));
+      ms = std::min(ms, cms);
     }
     if (times_ms) times_ms[t] = ms;
     if (bt < 0 || ms < bms) { bt = t; bms = ms; }
@@ -230,6 +243,7 @@ int gw_polarizability_batched(gw_ctx *ctx, const gw_c32 *psi_occ, int nv, const 
   // ---- plans, tiles and workspace (all before any capture) ---------------------------------
   std::vector<SpherePlan> plans(nq);
   std::vector<int> tiles(nq);
+  std::vector<size_t> cut(nq, 0);    // bytes of the parts of the job's update where its tile may be cut
   size_t a1 = 0, a2 = 0, ngmax = 0, y1 = 0;
   for (int j = 0; j < nq; ++j) {
     build_sphere_plan(grid, jobs[j].g_miller, jobs[j].ng, plans[j]);
@@ -253,6 +267,7 @@ int gw_polarizability_batched(gw_ctx *ctx, const gw_c32 *psi_occ, int nv, const 
                              jobs[j].e_c, o.precision, (float2 *)pbuf[0], &t, nullptr, s));
     }
     tiles[j] = t;
+    if (o.tile < 0 && t == herk_default_tile(o.precision, nr)) cut[j] = herk_part_bytes(o.precision, nr, nv, jobs[j].nc);
   }
   void *wa1, *wa2, *wph, *wpht = nullptr, *wq, *weps, *wl, *wx, *wsmall, *wpiv, *wy1 = nullptr;
   GWX_STATUS(api_ws_get(ctx, BS_A1, a1 * sizeof(float2), &wa1, s));
@@ -284,6 +299,11 @@ int gw_polarizability_batched(gw_ctx *ctx, const gw_c32 *psi_occ, int nv, const 
     }
     jd[j] = {(double *)p[0], (float *)p[1], (int *)p[2], (int *)p[3], (int *)p[4], (double *)p[5]};
   }
+  // The updates run one after the other and share the parts' buffer.  It is optional: where it has moved or is gone
+  // since the graph was captured, the graph's key differs.
+  const size_t pbytes = *std::max_element(cut.begin(), cut.end());
+  void *part = pbytes ? api_ws_try(ctx, WS_HERK_PART, pbytes, s) : nullptr;
+  ptrs.push_back(part);
 
   // ---- host inputs to device (every call; the graph reads these buffers) ----------------------
   for (int j = 0; j < nq; ++j) {
@@ -362,7 +382,7 @@ int gw_polarizability_batched(gw_ctx *ctx, const gw_c32 *psi_occ, int nv, const 
         ck(launch_band_exponents((const float2 *)psi_occ, nv, (const float2 *)jb.psi_unocc, nc, nr, jd[j].scale, ldsc,
                                  jd[j].bexp, c->sa));
       ck(launch_herk(o.precision, tiles[j], (const float2 *)psi_occ, (const float2 *)jb.psi_unocc, jd[j].scale, ldsc,
-                     jd[j].bexp, pj, nr, nv, nc, 0, c->sa));
+                     jd[j].bexp, pj, nr, nv, nc, 0, c->sa, cut[j] ? part : nullptr));
       ck(hipEventRecord(ev_herk[j], c->sa));
       // transform / eps / inverse chain (sb)
       ck(hipStreamWaitEvent(c->sb, ev_herk[j], 0));

@@ -26,6 +26,7 @@ std::map<stream_t, bool> capturing;
 std::vector<Copy> recorded;
 std::vector<Launch> launches;
 size_t limit = 0;                       // requests above it fail (0: none do)
+float cut_ms = 1.0f;                    // time between two events after a launch that adds parts of cut tiles
 int last = OK, violations = 0, copies = 0;
 struct Config { dim3 grid, block; size_t shared; stream_t s; } config;
 
@@ -45,6 +46,7 @@ extern "C" {
 
 // ---- for the test --------------------------------------------------------------------------------------
 void fake_limit(size_t bytes) { limit = bytes; }
+void fake_cut_ms(float ms) { cut_ms = ms; }
 void fake_capture(stream_t s, int on) { capturing[s] = on != 0; }
 int fake_violations() { return violations; }
 int fake_recorded() { return (int)recorded.size(); }
@@ -170,7 +172,7 @@ int hipEventDestroy(void *) { return OK; }
 int hipEventRecord(void *, stream_t) { return OK; }
 int hipEventSynchronize(void *) { return OK; }
 int hipEventElapsedTime(float *ms, void *, void *) {
-  *ms = 1.0f;
+  *ms = !launches.empty() && launches.back().name.find("part_sum") != std::string::npos ? cut_ms : 1.0f;
   return OK;
 }
 int hipGetDeviceCount(int *n) {

@@ -199,3 +199,61 @@ assert shape("fp32", 1728, 8, 64)[0] == [210, 420]
 for prec in ("bf16", "fp16"):
     assert shape(prec, 4096, 4, 64)[0] == [256, 64, 128]
 """)
+
+
+TUNED = OPTIONAL + """
+os.environ["GW_AUTOTUNE_CACHE"] = ""
+fake.fake_cut_ms.argtypes = [C.c_float]
+def tune(h):
+    best, times = C.c_int(), (C.c_double * lib.gw_tile_count())()
+    assert lib.gw_autotune(h, ptr(buf(8)), 8, ptr(buf(8)), 64, 1728, ptr(ev), ptr(ec), 0, u, C.byref(best), times, S) == 0
+    return best.value, times[best.value]
+def batch(h, o=opts):
+    m, ng = np.ascontiguousarray(gs.sphere((12, 12, 12), count=200), np.int32), 200
+    jobs = (L.QJob * 2)()
+    for j in jobs:
+        j.psi_unocc, j.nc, j.e_c, j.g_miller, j.ng, j.p_gg = 256, 64, ec.ctypes.data, m.ctypes.data, ng, 256
+        j.q[:] = (0.1, 0.2, 0.3)
+    return lib.gw_polarizability_batched(h, u, 8, ptr(ev), L.Grid(12, 12, 12, 10.0), 2, jobs, C.byref(o), 1.0, S)
+cut = lambda: len(launches("part_sum"))
+"""
+
+
+def test_tuned_shapes_may_be_cut(run):
+    """The tuner times the cut default tile too; where that tile is the fastest, calls and batches of the shape cut
+    it as untuned calls do, and where another one is, they run that."""
+    run(TUNED + """
+default = lib.gw_default_tile(0, 1728)
+h = ctx()
+fake.fake_cut_ms(0.5)
+assert tune(h) == (default, 0.5)
+for call in (update, batch):
+    fake.fake_clear()
+    assert call(h) == 0 and cut() == (1 if call is update else 2)
+    fake.fake_clear()
+    assert call(h, L._opts("fp32", tile=default)) == 0 and cut() == 0 and launches("herk_fp32")
+h = ctx()
+fake.fake_cut_ms(2.0)
+assert tune(h)[0] != default
+fake.fake_clear()
+assert update(h) == 0 and batch(h) == 0 and cut() == 0
+assert fake.fake_violations() == 0
+""")
+
+
+def test_a_batch_follows_its_parts_buffer(run):
+    """A batch whose parts' buffer was freed for another call's needs captures its launches again."""
+    run(TUNED + """
+h = ctx()
+fake.fake_cut_ms(0.5)
+assert batch(h) == 0 and lib.gw_graph_captures(h) == 1
+assert batch(h) == 0 and lib.gw_graph_captures(h) == 1
+need = lib.gw_workspace_bytes(h)
+lib.gw_destroy(h)
+h = ctx(need + (1 << 20))
+assert batch(h) == 0 and lib.gw_graph_captures(h) == 1
+a = buf(16 * 700 * 700)
+assert lib.gw_hpd_inverse(h, ptr(a), 700, ptr(a), S) in (0, 4)      # no kernel sets the pivot word here
+fake.fake_clear()
+assert batch(h) == 0 and lib.gw_graph_captures(h) == 2 and cut() == 0 and fake.fake_violations() == 0
+""")
