@@ -184,13 +184,14 @@ hipError_t launch_pp_finish(double2 *e, const double2 *ei_static, const double *
 hipError_t launch_sqrtv(const int *miller, int ng, double q0, double q1, double q2, double a_bohr, double *sv,
                         hipStream_t s);
 // Static self-energy kernels (sigma.hip).  f: f~ as rows [g][n nv + v].
-size_t contract_part_elems(int nn, int nv, int ng);
+int contract_blocks(int nn, int nv, int ng, int nr);
+size_t contract_part_elems(int nn, int nblk);
 // out[n][n'] = scale sum_g V_g sum_v f[g][n nv + v] conj(f[g][n' nv + v]), V_g = sv_g^2
-hipError_t launch_contract_x(const float2 *f, int nn, int nv, int ng, const double *sv, double scale, double2 *part,
-                             double2 *out, hipStream_t s);
+hipError_t launch_contract_x(const float2 *f, int nn, int nv, int ng, const double *sv, double scale, int nblk,
+                             double2 *part, double2 *out, hipStream_t s);
 // out[n][n'] = scale sum_g sum_v f[g][n nv + v] t[g][n' nv + v]
-hipError_t launch_contract_t(const float2 *f, const double2 *t, int nn, int nv, int ng, double scale, double2 *part,
-                             double2 *out, hipStream_t s);
+hipError_t launch_contract_t(const float2 *f, const double2 *t, int nn, int nv, int ng, double scale, int nblk,
+                             double2 *part, double2 *out, hipStream_t s);
 // out[n][n'] = -sum_a sigma_a sum_v zeta[a][n nv + v] conj(zeta[a][n' nv + v])
 hipError_t launch_contract_modes(const double2 *zeta, int nm, int nv, int nn, const double *sigma, double2 *out,
                                  hipStream_t s);

@@ -35,8 +35,8 @@ int pair_transform(gw_ctx *ctx, const float2 *psi_n, int nn, const float2 *psi_v
                    const int *miller, int ng, float2 **ft, double2 **part, hipStream_t s) {
   const int nr = grid.n1 * grid.n2 * grid.n3, B = nn * nv;
   void *ot, *fg, *a1, *a2;
-  GWX_STATUS(api_ws_get(ctx, SG_F, std::max((size_t)(nn + nv) * nr * sizeof(float2),
-                                            contract_part_elems(nn, nv, ng) * sizeof(double2)), &ot, s));
+  const size_t pe = contract_part_elems(nn, contract_blocks(nn, nv, ng, nr));
+  GWX_STATUS(api_ws_get(ctx, SG_F, std::max((size_t)(nn + nv) * nr * sizeof(float2), pe * sizeof(double2)), &ot, s));
   GWX_STATUS(api_ws_get(ctx, SG_FG, (size_t)B * ng * sizeof(float2), &fg, s));
   // the orbitals grid-major; the first pass forms the products conj(u_n) u_v from them
   float2 *pn = (float2 *)ot, *pv = pn + (size_t)nn * nr;
@@ -91,18 +91,19 @@ int gw_sigma_static(gw_ctx *ctx, const gw_c32 *psi_n, int nn, const gw_c32 *psi_
   GWX_STATUS(pair_transform(ctx, (const float2 *)psi_n, nn, (const float2 *)psi_v, nv, grid, g_miller, ng, &ft, &part, s));
   double *sv;
   GWX_STATUS(sqrtv_on_device(ctx, g_miller, ng, q, grid.a_bohr, &sv, s));
-  const int B = nn * nv;
-  if (sigma_x) GWX_HIP(ctx, launch_contract_x(ft, nn, nv, ng, sv, -1.0, part, (double2 *)sigma_x, s));
+  const int B = nn * nv, nblk = contract_blocks(nn, nv, ng, grid.n1 * grid.n2 * grid.n3);
+  if (sigma_x) GWX_HIP(ctx, launch_contract_x(ft, nn, nv, ng, sv, -1.0, nblk, part, (double2 *)sigma_x, s));
   if (sigma_sex) {
-    // rows of S start on memory lines: the product's 64-byte runs along k would straddle them otherwise
-    const long long lds = (ng + 7) / 8 * 8;
+    // rows of S start on memory lines: the product's 64-byte runs along k would straddle them otherwise (for fewer
+    // than eight pairs the product is a pass over S, and the padding would be more than is saved elsewhere)
+    const long long lds = B < 8 ? ng : (ng + 7) / 8 * 8;
     void *sp, *tp;
     GWX_STATUS(api_ws_get(ctx, SG_S, (size_t)ng * lds * sizeof(double2), &sp, s));
     GWX_STATUS(api_ws_get(ctx, SG_T, (size_t)ng * B * sizeof(double2), &tp, s));
     GWX_HIP(ctx, launch_screening((const double2 *)eps_inv, sv, ng, lds, (double2 *)sp, s));
     // T = -S conj(f~)
     GWX_HIP(ctx, launch_zgemm(ng, B, ng, (const double2 *)sp, lds, Z_N, ft, B, Z_J, (double2 *)tp, B, -1.0, 0.0, s));
-    GWX_HIP(ctx, launch_contract_t(ft, (const double2 *)tp, nn, nv, ng, 1.0, part, (double2 *)sigma_sex, s));
+    GWX_HIP(ctx, launch_contract_t(ft, (const double2 *)tp, nn, nv, ng, 1.0, nblk, part, (double2 *)sigma_sex, s));
   }
   return GW_OK;
 }

@@ -122,34 +122,35 @@ __global__ __launch_bounds__(256) void contract_modes_kernel(const double2 *__re
   if (threadIdx.x == 0) out[(size_t)n * nn + np] = make_double2(-rr[0], -ri[0]);
 }
 
-// blocks of K: at least four units for each of a block's four waves
-static int contract_blocks(int nt, int nv, int ng) {
-  const long long units = (long long)ng * ((nv + CTV - 1) / CTV);
-  return (int)std::max(1LL, std::min((long long)CT_BLOCKS / (nt * nt), units / 16));
+// blocks of K: at least four units for each of a block's four waves, and partial sums no larger than two copies of
+// the pair products on the grid (which bounds calls with one pair)
+int contract_blocks(int nn, int nv, int ng, int nr) {
+  const long long units = (long long)ng * ((nv + CTV - 1) / CTV), nt2 = (long long)((nn + 15) / 16) * ((nn + 15) / 16);
+  return (int)std::max(1LL, std::min({CT_BLOCKS / nt2, units / 16, (long long)nn * nv * nr / (256 * nt2)}));
 }
-size_t contract_part_elems(int nn, int nv, int ng) {
+size_t contract_part_elems(int nn, int nblk) {
   const int nt = (nn + 15) / 16;
-  return (size_t)contract_blocks(nt, nv, ng) * nt * nt * 256;
+  return (size_t)nblk * nt * nt * 256;
 }
 
 template <bool CONJ, typename TB>
 static hipError_t contract(const float2 *f, const TB *b, int nn, int nv, int ng, const double *sv, double scale,
-                           double2 *part, double2 *out, hipStream_t s) {
-  const int nt = (nn + 15) / 16, nblk = contract_blocks(nt, nv, ng);
+                           int nblk, double2 *part, double2 *out, hipStream_t s) {
+  const int nt = (nn + 15) / 16;
   hipLaunchKernelGGL(HIP_KERNEL_NAME(contract_kernel<CONJ, TB>), dim3(nblk, nt * nt), dim3(256), 0, s, f, b, nn, nv, ng,
                      sv, nt, part);
   hipLaunchKernelGGL(contract_sum_kernel, dim3(nn * nn), dim3(64), 0, s, part, nblk, nt, nn, scale, out);
   return hipGetLastError();
 }
 
-hipError_t launch_contract_x(const float2 *f, int nn, int nv, int ng, const double *sv, double scale, double2 *part,
-                             double2 *out, hipStream_t s) {
-  return contract<true>(f, f, nn, nv, ng, sv, scale, part, out, s);
+hipError_t launch_contract_x(const float2 *f, int nn, int nv, int ng, const double *sv, double scale, int nblk,
+                             double2 *part, double2 *out, hipStream_t s) {
+  return contract<true>(f, f, nn, nv, ng, sv, scale, nblk, part, out, s);
 }
 
-hipError_t launch_contract_t(const float2 *f, const double2 *t, int nn, int nv, int ng, double scale, double2 *part,
-                             double2 *out, hipStream_t s) {
-  return contract<false>(f, t, nn, nv, ng, (const double *)nullptr, scale, part, out, s);
+hipError_t launch_contract_t(const float2 *f, const double2 *t, int nn, int nv, int ng, double scale, int nblk,
+                             double2 *part, double2 *out, hipStream_t s) {
+  return contract<false>(f, t, nn, nv, ng, (const double *)nullptr, scale, nblk, part, out, s);
 }
 
 hipError_t launch_contract_modes(const double2 *zeta, int nm, int nv, int nn, const double *sigma, double2 *out,

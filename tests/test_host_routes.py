@@ -257,3 +257,23 @@ assert lib.gw_hpd_inverse(h, ptr(a), 700, ptr(a), S) in (0, 4)      # no kernel 
 fake.fake_clear()
 assert batch(h) == 0 and lib.gw_graph_captures(h) == 2 and cut() == 0 and fake.fake_violations() == 0
 """)
+
+
+def test_exchange_workspace_of_few_pairs(run):
+    """The workspace of an exchange stays below two copies of the pair products on the grid, their transforms, S, and
+    conj(f~) and T in FP64, however few pairs there are."""
+    run("""
+for n, nn, nv, ng in ((24, 1, 1, 4067), (24, 2, 1, 4067), (30, 1, 3, 3001), (16, 1, 1, 900), (8, 1, 1, 60), (12, 17, 2, 400)):
+    m, nr, b = np.ascontiguousarray(gs.sphere((n, n, n), count=ng), np.int32), n ** 3, nn * nv
+    for sex in (None, ptr(buf(8))):
+        h = ctx()
+        q = np.array([0.1, 0.2, 0.3])
+        assert lib.gw_sigma_static(h, ptr(buf(8)), nn, ptr(buf(8)), nv, L.Grid(n, n, n, 10.0), ptr(q), ptr(m), ng,
+                                   ptr(buf(8)), ptr(buf(8)), sex, S) == 0
+        k3 = len(set(m[:, 2])); pairs = len(set(map(tuple, m[:, 1:])))
+        maps = 4 * (n * n * n + n * k3 * n + pairs * n + 2 * n + n * n + n * pairs)
+        limit = 2 * 8 * b * nr + 8 * b * ng + 8 * b * n * (n * k3 + pairs) + maps + 20 * ng + (sex is not None) * (
+            16 * ng * ng + 32 * ng * b)
+        assert lib.gw_workspace_bytes(h) <= limit + 12 * 256, (n, nn, nv, ng, lib.gw_workspace_bytes(h), limit)
+        lib.gw_destroy(h)
+""")
