@@ -470,18 +470,6 @@ hipError_t launch_fft_gather_pass_t(int n, int sign, const float2 *in, float2 *o
 // [plane][pair], over the rows every lane has read.  The planes of one block are consecutive in y1, so
 // the block's output leaves in one contiguous run.  pl is chosen on the host to keep the lanes busy:
 // at n = 36 with 19 rows k2, three planes fill 108 of 128 lanes in phase 1 and 57 of 64 in phase 2.
-// The slots k2s of all rows in scalar registers.  Read where they are needed, behind a branch each, every one was a
-// scalar load with its own wait, which also waits for the LDS accesses before it: 36 in a row per column (both
-// transforms of a 36^3 P 4451 -> 4428 us, the 1152 orbitals of that workload 221 -> 218 us).
-template <int N>
-struct RowSlots {
-  int s[N];
-  __device__ __forceinline__ explicit RowSlots(const int *__restrict__ k2s) {
-#pragma unroll
-    for (int k2 = 0; k2 < N; ++k2) s[k2] = __builtin_amdgcn_readfirstlane(k2s[k2]);
-  }
-};
-
 template <int N, bool HERM>
 __global__ __launch_bounds__(64) void plane_ab_kernel(const float2 *__restrict__ P, long long ldp, int n1, int pl,
                                                       const int *__restrict__ k2s, int nk2,
@@ -498,7 +486,6 @@ __global__ __launch_bounds__(64) void plane_ab_kernel(const float2 *__restrict__
   const int reg = nk2 * LD;
   const bool diag = HERM && roff >= 0 && roff < pl * PLN;   // the diagonal lies in one of the block's planes
   const float2 *src = P + (long long)r * ldp + (long long)i10 * PLN;
-  const RowSlots<N> slot(k2s);
   for (int t0 = 0; t0 < pl * N; t0 += 64) {
     const int t = t0 + lane, p = t / N, i3 = t - p * N;
     if (p >= pfirst && p < pend) {
@@ -526,7 +513,7 @@ __global__ __launch_bounds__(64) void plane_ab_kernel(const float2 *__restrict__
       float2 *L = lds + p * reg + i3;
 #pragma unroll
       for (int k2 = 0; k2 < N; ++k2) {
-        const int sl = slot.s[k2];
+        const int sl = k2s[k2];
         if (sl >= 0) L[sl * LD] = x[k2];
       }
     }
@@ -732,7 +719,6 @@ __global__ __launch_bounds__(128) void orb_plane_kernel(const float2 *__restrict
   const int b = blockIdx.x, i10 = blockIdx.y * pl;
   const int pend = min(pl, n1 - i10);
   const float2 *src = y + ((size_t)b * n1 + i10) * npair;
-  const RowSlots<N> slot(k2s);
   for (int j = tid; j < pend * npair; j += 128) lds[j] = src[j];
   __syncthreads();
   {
@@ -764,7 +750,7 @@ __global__ __launch_bounds__(128) void orb_plane_kernel(const float2 *__restrict
       float2 x[N];
 #pragma unroll
       for (int k2 = 0; k2 < N; ++k2) {
-        const int sl = slot.s[k2];                     // uniform
+        const int sl = k2s[k2];                        // uniform
         x[k2] = sl >= 0 ? col[sl * LD] : make_float2(0.f, 0.f);
       }
       Fft<N, 1>::run(x);
