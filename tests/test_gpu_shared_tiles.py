@@ -83,3 +83,55 @@ def test_cut_tiles_give_way_under_a_workspace_cap(gw):
     tight = gw.Context(0, workspace_cap=(4 + 64) * 8 + 2 * 4 * 64 * 4 + 1024)
     p = gw.polarizability_r(pv, pc, s.e_v, s.e_c, ctx=tight)
     assert torch.equal(p, gw.polarizability_r(pv, pc, s.e_v, s.e_c, tile=tile, ctx=plain))
+
+
+# Whole rounds before the cut tiles in every precision: FP32 256 tiles and 20 in seven parts each, the others 256 blocks
+# and 16 in eight parts each (of the sizes above, the split precisions cut none at 2900 and 4200 points).  That the
+# tiles are cut shows in the workspace, which holds their parts.
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("prec", ["fp32", "bf16", "fp16"])
+def test_cut_after_whole_rounds(gw, prec, accumulate):
+    nr, nv, nc = (2900, 5, 50) if prec == "fp32" else (4096, 4, 250)
+    print(f"[case] {prec} accumulate={accumulate}", flush=True)
+    pv, pc, ev, ec = bands(nr, nv, nc, seed=3)
+    whole, cut = gw.Context(0), gw.Context(0)
+    tile = gw.tile_names().index(gw.default_tile_name(prec))
+    p0 = torch.full((nr, nr), 0.25 - 0.5j, dtype=torch.complex64, device="cuda:0")
+    p0 = torch.triu(p0, 1) + torch.triu(p0, 1).conj().T
+    run = lambda ctx, tile: gw.polarizability_r(dev(pv), dev(pc), ev, ec, precision=prec, accumulate=accumulate,
+                                                out=p0.clone(), tile=tile, ctx=ctx).cpu().numpy()
+    got, plain = run(cut, -1), run(whole, tile)
+    parts = 20 * 7 * 4 if prec == "fp32" else 16 * 8 * 8
+    assert cut.workspace_bytes - whole.workspace_bytes >= parts * 32768
+    ref = reference(pv, pc, ev, ec) + (p0.cpu().numpy() if accumulate else 0.0)
+    tol = 1e-5 if prec == "fp32" else 1e-4
+    assert orc.rel_f(got, ref) < tol and orc.rel_f(plain, ref) < tol
+    assert not np.array_equal(got, plain)
+
+
+def test_cut_fp16_accumulate(gw):
+    pv, pc, ev, ec = bands(1000, 7, 101, seed=4)
+    p0 = torch.eye(1000, dtype=torch.complex64, device="cuda:0")
+    got = gw.polarizability_r(dev(pv), dev(pc), ev, ec, precision="fp16", accumulate=True, out=p0.clone())
+    assert orc.rel_f(got.cpu().numpy(), np.eye(1000) + reference(pv, pc, ev, ec)) < 1e-4
+
+
+def test_tuning_keeps_the_cut(gw):
+    """A tuned shape is no slower than an untuned one, and a batch of it equals the calls of their own bit for bit."""
+    import gwsynth as gs
+    b = gs.make_batched_q(n=10, nv=8, nc=100, r2_psi=9.0, nq=2, sizes=(100, 120))
+    pv = dev(b["psi_v"].astype(np.complex64))
+    ctx = gw.Context(0)
+    jobs = [dict(psi_c=dev(j["psi_c"].astype(np.complex64)), e_c=j["e_c"], q=j["q"], miller=j["miller"],
+                 p_gg=torch.empty((len(j["miller"]),) * 2, dtype=torch.complex64, device="cuda:0"), eps_inv=None)
+            for j in b["jobs"]]
+    gw.polarizability_batched(pv, b["e_v"], b["n"], b["a_bohr"], jobs, precision="fp32", ctx=ctx)
+    for j in jobs:
+        out = gw.polarizability(pv, j["psi_c"], b["e_v"], j["e_c"], b["n"], b["a_bohr"], j["q"], j["miller"],
+                                precision="fp32", ctx=ctx)
+        assert torch.equal(out, j["p_gg"])
+    # 36 tiles on 256 CUs: cut seven-fold they take a fraction of their time in one piece
+    default = gw.tile_names().index(gw.default_tile_name("fp32"))
+    best, times = gw.autotune(pv, jobs[0]["psi_c"], b["e_v"], jobs[0]["e_c"], precision="fp32", ctx=gw.Context(0))
+    assert best == default and times[gw.tile_names()[best]] < 0.5 * min(v for k, v in times.items()
+                                                                         if k != gw.tile_names()[best])
