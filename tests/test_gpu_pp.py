@@ -172,3 +172,36 @@ def test_long_blocks(gw, ng):
     for j in range(nm):
         gap = np.min(np.abs(np.delete(w, j) - w[j]))
         assert abs(abs(np.vdot(u[:, j], modes[:, j])) - 1.0) < max(1e-9, (1e-9 * abs(w[0]) / gap) ** 2)
+
+
+def test_a_value_that_is_not_finite_is_passed_on(gw):
+    """A NaN in eps^-1 gives NaN strengths, in one iteration, and no error."""
+    rng = np.random.default_rng(0)
+    n, q, ng = (8, 8, 8), np.array([0.1, 0.2, 0.3]), 60
+    eps_inv = np.eye(ng, dtype=np.complex128) * 0.5
+    eps_inv[3, 4] = np.nan
+    psi = (rng.standard_normal((2, 512)) + 1j * rng.standard_normal((2, 512))).astype(np.complex64)
+    sig, _, _, its, _ = gw.plasmon_pole(dev(eps_inv), n, gs.cell_side(8), q, gs.sphere(n, count=ng, q=q), dev(psi),
+                                        n_modes=4)
+    assert its == 1 and np.all(np.isnan(sig.cpu().numpy()))
+
+
+# The one-pass pole form (up to 32 modes) and the three-pass one, at the edges of the 64 x 64 tiles, with the row and
+# column of q + G = 0 from the static matrix.  All weights of one frequency have the same sign, so the moduli of an
+# entry's terms add up to at most the largest diagonal entry, and their rounding to 50 x 4 x 1.1e-16 = 2e-14 of it.
+@pytest.mark.parametrize("ng,nm", [(1, 1), (63, 32), (64, 1), (65, 33), (130, 32), (130, 50)])
+def test_pole_form_of_given_modes(gw, ng, nm):
+    print(f"[case] ng={ng} nm={nm}", flush=True)
+    rng = np.random.default_rng(ng + nm)
+    for q in (np.zeros(3), np.array([0.1, 0.2, 0.3])):
+        n, a = (12, 12, 12), gs.cell_side(12)
+        mill = gs.sphere(n, count=ng, q=q)
+        sv = orc.coulomb_sqrt(n, a, q, mill)
+        ei = rng.standard_normal((ng, ng)) + 1j * rng.standard_normal((ng, ng))
+        modes = rng.standard_normal((ng, nm)) + 1j * rng.standard_normal((ng, nm))
+        sig, om, freqs = -rng.uniform(0.1, 1.0, nm), rng.uniform(1.0, 2.0, nm), np.array([0.0, 0.5, 3.0])
+        got = gw.pp_eps_inverse(dev(ei), n, a, q, mill, dev(modes), dev(sig), dev(om), freqs).cpu().numpy()
+        ref = pp.pp_eps_inverse(ei, sig, om, modes, sv, freqs)
+        assert np.max(np.abs(got - ref)) <= 1e-13 * np.max(np.abs(ref))
+        if not q.any():
+            assert np.array_equal(got[:, 0], ref[:, 0]) and np.array_equal(got[:, :, 0], ref[:, :, 0])
