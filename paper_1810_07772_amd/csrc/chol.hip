@@ -480,6 +480,7 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
   __shared__ double dv[NB];
   const int m = tid % 16, c = tid / 16;
   static_assert(PD_THREADS == 16 * NB && NB == 32, "one row per 16 lanes, two columns per lane");
+  double2 row[2];
   {
     double2 z[2];
     __syncthreads();
@@ -488,34 +489,33 @@ __global__ __launch_bounds__(PD_THREADS) void potrf_diag_kernel(const double2 *_
       const int k = 16 * h + m;
       z[h] = a[max(c, k)][min(c, k)];
       if (kp > 0 && min(c, k) >= 16) {
+        double2 v[4];                                        // added first, so that the entry is rounded once
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const double2 v = quarter[g][max(c, k) - 16][min(c, k) - 16];
-          z[h].x -= v.x;
-          z[h].y -= v.y;
-        }
+        for (int g = 0; g < 4; ++g) v[g] = quarter[g][max(c, k) - 16][min(c, k) - 16];
+        z[h].x -= (v[0].x + v[1].x) + (v[2].x + v[3].x);
+        z[h].y -= (v[0].y + v[1].y) + (v[2].y + v[3].y);
       }
       if (k > c) z[h].y = -z[h].y;
     }
-    eliminate32(z, w, dv, wave, NB, [](double d) { return rcp_nr(d); });
+    eliminate32(z, row, w, dv, wave, NB, [](double d) { return rcp_nr(d); });
   }
   __syncthreads();
-  // With r_j = sqrt(d_j): row j of L^-1 is r_j w[j] up to the diagonal, column j of L is r_j conj(w[j]) from it
-  // on.  The first pivot that is not positive and finite (1-based, over the whole matrix) is flagged; it
-  // scales by 1.
+  // With r_j = sqrt(d_j): row j of L^-1 is row_j / r_j up to the diagonal, column j of L is conj(row_j) / r_j from it on
+  // (w[j] r_j would round once more).  The first pivot that is not positive and finite (1-based, over the whole matrix)
+  // is flagged; it scales by 1.
   if (wave == 0) {
     const bool wrong = tid < nb && !(dv[tid % NB] > 0.0 && isfinite(dv[tid % NB]));
     const unsigned long long first = __ballot(wrong);
     if (tid == 0) bad = first ? k0 + __ffsll(first) : 0;
   }
   {
-    const double d = dv[c], r = d > 0.0 && isfinite(d) ? sqrt(d) : 1.0;
+    const double d = dv[c], r = d > 0.0 && isfinite(d) ? sqrt(d) : 1.0, ir = rcp_nr(r);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k = 16 * h + m;
-      const double2 v = w[c][k];
-      x[c][k] = k <= c ? make_double2(v.x * r, v.y * r) : make_double2(0.0, 0.0);
-      if (k >= c) a[k][c] = k == c ? make_double2(r, 0.0) : make_double2(v.x * r, -v.y * r);
+      const double2 v = make_double2(div_nr(row[h].x, r, ir), div_nr(row[h].y, r, ir));
+      x[c][k] = k <= c ? v : make_double2(0.0, 0.0);
+      if (k >= c) a[k][c] = k == c ? make_double2(r, 0.0) : make_double2(v.x, -v.y);
     }
   }
   __syncthreads();

@@ -549,7 +549,7 @@ __global__ __launch_bounds__(512) void block_chol_kernel(const double2 *__restri
     dinv[tid] = d > 0.0 && isfinite(d) ? 1.0 / sqrt(d) : 0.0;
   }
   __syncthreads();
-  double2 z[2];
+  double2 z[2], row[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int k = 16 * h + m;
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(512) void block_chol_kernel(const double2 *__restri
     const double f = 0.5 * dinv[c] * dinv[k];
     z[h] = make_double2(f * (a.x + t.x), f * (a.y - t.y));
   }
-  eliminate32(z, w, dv, __builtin_amdgcn_readfirstlane(tid >> 6), b, [](double d) { return d > 1e-14 ? rcp_nr(d) : 0.0; });
+  eliminate32(z, row, w, dv, __builtin_amdgcn_readfirstlane(tid >> 6), b, [](double d) { return d > 1e-14 ? rcp_nr(d) : 0.0; });
   __syncthreads();
   // row c of the inverse of L is sqrt(d_c) w[c]; u[k][c] = dinv[k] conj(Linv[c][k])
   if (c < b) {

@@ -65,3 +65,22 @@ def test_newton(gw, n):
     got, its, _ = gw.newton_inverse(torch.from_numpy(a).cuda())
     ref = np.linalg.inv(a)
     assert np.linalg.norm(got.cpu().numpy() - ref) < 1e-12 * np.linalg.norm(ref)
+
+
+def test_inverse_rounds_once_per_step(gw):
+    """An entry of the factor's diagonal block is rounded once per elimination step and once for the columns applied
+    to it.  Against inverses refined in extended precision, three dielectric matrices of 130 rows come to 4.7e-16 so on
+    the mean, and to 5.5e-16 with two roundings a step; the bound lies between."""
+    err = []
+    for seed in range(3):
+        n, rng = 130, np.random.default_rng(130000 + seed)
+        x = (rng.standard_normal((n, 2 * n)) + 1j * rng.standard_normal((n, 2 * n))) / np.sqrt(2)
+        d = 2.0 / (0.3 + np.sort(rng.uniform(0.05, 12.0, n))) ** 0.75
+        h = x @ x.conj().T / (2 * n)
+        a = np.eye(n) + d[:, None] * (0.5 * (h + h.conj().T)) * d[None, :]
+        got = gw.hpd_inverse(torch.from_numpy(a).to("cuda:0")).cpu().numpy()
+        ref = np.linalg.inv(a).astype(np.clongdouble)
+        ref = ref @ (2 * np.eye(n, dtype=np.clongdouble) - a.astype(np.clongdouble) @ ref)
+        err.append(float(np.sqrt(np.sum(np.abs(got - ref) ** 2) / np.sum(np.abs(ref) ** 2))))
+    print(f"relative errors {err}")
+    assert np.mean(err) < 5.1e-16
