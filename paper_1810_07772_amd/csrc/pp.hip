@@ -779,12 +779,11 @@ __global__ __launch_bounds__(256) void pp_pole_kernel(const double2 *__restrict_
         acc[i][j].y += u[i].y * v[j].x - u[i].x * v[j].y;
       }
   }
-  double rg[4], rh[4];                 // 1 / sqrt(V), 0 where it vanishes
+  double vg[4], vh[4];                 // sqrt(V)
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const double x = sv[min(g0 + ty + 16 * i, ng - 1)], y = sv[min(h0 + tx + 16 * i, ng - 1)];
-    rg[i] = x > 0.0 ? 1.0 / x : 0.0;
-    rh[i] = y > 0.0 ? 1.0 / y : 0.0;
+    vg[i] = sv[min(g0 + ty + 16 * i, ng - 1)];
+    vh[i] = sv[min(h0 + tx + 16 * i, ng - 1)];
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -794,8 +793,8 @@ __global__ __launch_bounds__(256) void pp_pole_kernel(const double2 *__restrict_
       if (g < ng && h < ng) {
         const size_t at = (size_t)g * ng + h;
         double2 v = acc[i][j];
-        if (rg[i] > 0.0 && rh[j] > 0.0) {
-          const double f = rg[i] * rh[j];
+        if (vg[i] > 0.0 && vh[j] > 0.0) {
+          const double f = 1.0 / (vg[i] * vh[j]);      // as in pp_finish_kernel
           v.x *= f;
           v.y *= f;
           if (g == h) v.x += 1.0;

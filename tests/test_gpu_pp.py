@@ -205,3 +205,17 @@ def test_pole_form_of_given_modes(gw, ng, nm):
         assert np.max(np.abs(got - ref)) <= 1e-13 * np.max(np.abs(ref))
         if not q.any():
             assert np.array_equal(got[:, 0], ref[:, 0]) and np.array_equal(got[:, :, 0], ref[:, :, 0])
+
+
+def test_pole_forms_round_alike(gw):
+    """One mode by the one-pass form and, with 32 modes of zeros beside it, by the three-pass one: with powers of two
+    for its values the sums are exact, and the division by sqrt(V) sqrt(V') leaves the same bits."""
+    rng = np.random.default_rng(0)
+    n, q, ng = (12, 12, 12), np.array([0.1, 0.2, 0.3]), 200
+    mill = gs.sphere(n, count=ng, q=q)
+    one = dev(2.0 ** rng.integers(-2, 3, (ng, 1)) + 0j)
+    many = torch.cat([one, torch.zeros((ng, 32), dtype=one.dtype, device=one.device)], 1)
+    ei = dev(np.eye(ng, dtype=np.complex128))
+    out = [gw.pp_eps_inverse(ei, n, gs.cell_side(12), q, mill, m.contiguous(), dev(np.full(m.shape[1], -1.0)),
+                             dev(np.ones(m.shape[1])), [0.0]) for m in (one, many)]
+    assert torch.equal(out[0], out[1])
