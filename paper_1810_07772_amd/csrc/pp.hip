@@ -378,10 +378,6 @@ struct JacobiPair {
   }
 };
 
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
 __global__ __launch_bounds__(512) void herm_jacobi_kernel(const double2 *__restrict__ gpart, int nblk, int b,
                                                           double *__restrict__ evals, double2 *__restrict__ z,
                                                           int max_sweeps) {
