@@ -34,10 +34,11 @@ __global__ void scale_table_kernel(const double *__restrict__ e_v, int nv, const
 
 // Energies in the kernel's own arguments (a copy made at the launch) instead of two copies from pageable memory,
 // which the host stages and waits for: 12 x 200 bands on 27^3 138.8 -> 136.2 us a call, 12^3 FP32 build 130 -> 127.
-// ENERGY_ARG doubles fit beside the other arguments into the 4 KB a launch takes; a longer list goes in several
-// launches, and one of more than ENERGY_LAUNCHES by copies.  Under capture any list goes by copies: a graph whose
-// launches held the energies would replay those of the capture, copies read the caller's arrays at every replay.
-constexpr int ENERGY_ARG = 488, ENERGY_LAUNCHES = 4;
+// ENERGY_ARG doubles fit beside the other arguments into the 4 KB a launch takes; a longer list goes by the copies
+// (2 x 600 bands on 20^3: in three launches 30.1 us a call, 29.3 by copies; 2 x 800 on 16^3 26.3 and 23.2).  Under capture any list goes by
+// copies: a graph whose launches held the energies would replay those of the capture, copies read the caller's arrays
+// at every replay.
+constexpr int ENERGY_ARG = 488;
 struct EnergyArg { double e[ENERGY_ARG]; };
 
 __global__ void energies_kernel(EnergyArg a, int n, double *__restrict__ out) {
@@ -45,30 +46,16 @@ __global__ void energies_kernel(EnergyArg a, int n, double *__restrict__ out) {
   if (i < n) out[i] = a.e[i];
 }
 
-static hipError_t upload_part(const double *e, int n, double *dst, hipStream_t s) {
-  EnergyArg a;
-  for (int i0 = 0; i0 < n; i0 += ENERGY_ARG) {
-    const int m = std::min(n - i0, ENERGY_ARG);
-    std::copy(e + i0, e + i0 + m, a.e);
-    hipLaunchKernelGGL(energies_kernel, dim3((m + 255) / 256), dim3(256), 0, s, a, m, dst + i0);
-  }
-  return hipGetLastError();
-}
+bool pair_energies_fit(int nv, int nc) { return (long long)nv + nc <= ENERGY_ARG; }
 
 // dev[0 .. nv) = e_v, dev[nv .. nv + nc) = e_c (host arrays, read before the call returns unless it is captured)
 hipError_t upload_energies(const double *e_v, int nv, const double *e_c, int nc, double *dev, hipStream_t s) {
-  const long long n = (long long)nv + nc;
-  const bool by_args = n <= (long long)ENERGY_ARG * ENERGY_LAUNCHES && !stream_capturing(s);
-  if (by_args && n <= ENERGY_ARG) {
+  if (pair_energies_fit(nv, nc) && !stream_capturing(s)) {
     EnergyArg a;
     std::copy(e_v, e_v + nv, a.e);
     std::copy(e_c, e_c + nc, a.e + nv);
-    hipLaunchKernelGGL(energies_kernel, dim3(((int)n + 255) / 256), dim3(256), 0, s, a, (int)n, dev);
+    hipLaunchKernelGGL(energies_kernel, dim3((nv + nc + 255) / 256), dim3(256), 0, s, a, nv + nc, dev);
     return hipGetLastError();
-  }
-  if (by_args) {
-    const hipError_t e = upload_part(e_v, nv, dev, s);
-    return e != hipSuccess ? e : upload_part(e_c, nc, dev + nv, s);
   }
   const hipError_t e = hipMemcpyAsync(dev, e_v, (size_t)nv * sizeof(double), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return e;
@@ -169,8 +156,6 @@ hipError_t launch_pair_products(const float2 *psi_v, int nv, const float2 *psi_c
                                 int ldsc, float2 *f, hipStream_t s) {
   return launch_pairs<false>(psi_v, nv, psi_c, nc, nr, scale, ldsc, 1.0, f, 0, s);
 }
-
-bool pair_energies_fit(int nv, int nc) { return (long long)nv + nc <= ENERGY_ARG; }
 
 hipError_t launch_pair_products_e(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const double *e_v,
                                   const double *e_c, double prefactor, float2 *f, hipStream_t s) {

@@ -277,3 +277,17 @@ for n, nn, nv, ng in ((24, 1, 1, 4067), (24, 2, 1, 4067), (30, 1, 3, 3001), (16,
         assert lib.gw_workspace_bytes(h) <= limit + 12 * 256, (n, nn, nv, ng, lib.gw_workspace_bytes(h), limit)
         lib.gw_destroy(h)
 """)
+
+
+def test_energies_of_eager_calls(run):
+    """As many energies as one launch's arguments hold go in one launch, more by two copies (several launches took
+    longer than those)."""
+    run("""
+opts = L._opts("fp32")
+for nv, nc, n in ((8, 480, 1), (8, 481, 0), (100, 900, 0)):
+    ev, ec = np.linspace(-0.5, -0.1, nv), np.linspace(0.1, 1.0, nc)
+    fake.fake_clear()
+    assert lib.gw_polarizability_r(ctx(), ptr(buf(8)), nv, ptr(buf(8)), nc, 64, ptr(ev), ptr(ec), C.byref(opts),
+                                   ptr(buf(8)), S) == 0
+    assert len(launches("energies_kernel")) == n and fake.fake_copies() == 2 - 2 * n
+""")
