@@ -1,7 +1,7 @@
 // Pair products f_vc(r) = conj(u_v(r)) u_c(r) sqrt(p/(E_c - E_v))  (Eq.(fdef)) and the scale table.
 //
-// Bound by writing nv*nc*nr complex64 values.  A workgroup owns a segment of PP_P grid points, PP_VB occupied
-// and PP_CB unoccupied bands: their values at the segment pass through LDS once and serve PP_VB * PP_CB rows of F.
+// Bound by writing nv*nc*nr complex64 values.  A workgroup owns a segment of P grid points, VB occupied
+// and CB unoccupied bands: their values at the segment pass through LDS once and serve VB * CB rows of F.
 // Rows of F start anywhere in a 128-byte line (nr need not be a multiple of 16), so each row's segment runs from
 // line boundary to line boundary, and a wave stores whole lines, 1 KB per instruction, whatever nr is: stores
 // that straddled lines reached 3.6 TB/s at nr = 19683 (27^3) and 4.2 at 19684, against 5.1 on rows that are aligned
@@ -10,6 +10,11 @@
 // Segments by VB x CB at nr = 19683: 512 by 8 x 4 79 us, 256 by 8 x 8 79, 384 by 8 x 8 80, 512 by 8 x 8 83, 1024 by
 // 4 x 4 86, 512 by 4 x 8 88; at 36^3, 8 x 256 bands, 142, 150, 148, 145, 148 and 146 us.  Stores that are not
 // non-temporal: 3 to 20% slower.
+// The occupied bands are split evenly over as few blocks of at most 8 as hold them, and a block loads as many rows as
+// it has: with blocks of 8 throughout, 9 x 500 bands on 24^3 took 112 us (kernel alone; blocks of 5 87, a kernel that
+// loops over the occupied bands 100), 12 x 200 on 27^3 74 (6: 70), 10 x 490 on 18^3 54 (5: 45).  With four bands or
+// fewer the segment is 256 points by 4 x 4 or 3 x 4 (2 x 600 bands on 20^3 23.4 -> 18.7 us, 3 x 500 on 24^3 37.5 -> 34.1), with one
+// 512 by 1 x 4 (600 bands on 20^3 17.8 -> 12.2).
 #include <algorithm>
 #include <type_traits>
 
@@ -78,34 +83,34 @@ __device__ __forceinline__ float2 conj_mul_scale(float2 v, float2 c, float s) {
 }
 
 constexpr int PP_THREADS = 256;
-constexpr int PP_P = 512;      // points per row segment
-constexpr int PP_VB = 8;       // occupied bands per workgroup
 constexpr int PP_CB = 4;       // unoccupied bands per workgroup
 constexpr int PP_LINE = 16;    // values in a 128-byte line
 
 // The pair scales come from the table, or (ARG) from the energies in the arguments: no launch before this one.
-template <bool ARG>
+// P points of VB occupied bands per workgroup.
+template <int P, int VB, bool ARG>
 __global__ __launch_bounds__(PP_THREADS) void pair_products_kernel(const float2 *__restrict__ psi_v, int nv,
                                                                    const float2 *__restrict__ psi_c, int nc, int nr,
                                                                    int cbase, const float *__restrict__ scale, int ldsc,
                                                                    double prefactor, float2 *__restrict__ f,
                                                                    std::conditional_t<ARG, EnergyArg, int> energies) {
-  __shared__ float2 sv[PP_VB][PP_P + PP_LINE], sc[PP_CB][PP_P + PP_LINE];
-  __shared__ float ss[PP_VB][PP_CB];
+  __shared__ float2 sv[VB][P + PP_LINE], sc[PP_CB][P + PP_LINE];
+  __shared__ float ss[VB][PP_CB];
+  static_assert(P % PP_LINE == 0, "a segment's end falls on the line boundary its start is shifted to");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nvb = (nv + PP_VB - 1) / PP_VB;
-  const int v0 = ((int)blockIdx.x % nvb) * PP_VB, p0 = ((int)blockIdx.x / nvb) * PP_P;
+  const int nvb = (nv + VB - 1) / VB;
+  const int v0 = ((int)blockIdx.x % nvb) * VB, p0 = ((int)blockIdx.x / nvb) * P;
   const int c0 = cbase + (int)blockIdx.y * PP_CB;
-  const int mv = min(PP_VB, nv - v0), mc = min(PP_CB, nc - c0);
-  const int np = min(PP_P + PP_LINE, nr - p0);
-  for (int i = tid; i < PP_P + PP_LINE; i += PP_THREADS) {
+  const int mv = min(VB, nv - v0), mc = min(PP_CB, nc - c0);
+  const int np = min(P + PP_LINE, nr - p0);
+  for (int i = tid; i < P + PP_LINE; i += PP_THREADS) {
     const int q = min(i, np - 1);
 #pragma unroll
-    for (int k = 0; k < PP_VB; ++k) sv[k][i] = psi_v[(size_t)min(v0 + k, nv - 1) * nr + p0 + q];
+    for (int k = 0; k < VB; ++k) sv[k][i] = psi_v[(size_t)min(v0 + k, nv - 1) * nr + p0 + q];
 #pragma unroll
     for (int k = 0; k < PP_CB; ++k) sc[k][i] = psi_c[(size_t)min(c0 + k, nc - 1) * nr + p0 + q];
   }
-  if (tid < PP_VB * PP_CB) {
+  if (tid < VB * PP_CB) {
     const int k = tid / PP_CB, j = tid % PP_CB;
     const int v = min(v0 + k, nv - 1), c = min(c0 + j, nc - 1);
     if constexpr (ARG) ss[k][j] = (float)sqrt(prefactor / (energies.e[nv + c] - energies.e[v]));
@@ -121,7 +126,7 @@ __global__ __launch_bounds__(PP_THREADS) void pair_products_kernel(const float2 
     // From the first line boundary (the row's start for its first segment) to the first one past the segment
     // (the row's end for its last); a wave's stores start at a boundary, if need be before the row's start.
     const int off = (int)((a0 + at) & (PP_LINE - 1)), sh = (PP_LINE - off) & (PP_LINE - 1);
-    const int beg = p0 == 0 ? 0 : sh, end = min(PP_P + sh, nr - p0);   // PP_P is a multiple of a line
+    const int beg = p0 == 0 ? 0 : sh, end = min(P + sh, nr - p0);   // P is a multiple of a line
     const float s = ss[k][j];
     for (int i = (p0 == 0 ? -off : sh) + 2 * lane; i < end; i += 128) {
       const int x = max(i, 0), y = max(min(i + 1, np - 1), 0);
@@ -137,19 +142,34 @@ __global__ __launch_bounds__(PP_THREADS) void pair_products_kernel(const float2 
   }
 }
 
-static_assert(PP_P % PP_LINE == 0, "a segment's end falls on the line boundary its start is shifted to");
+template <int P, int VB, bool ARG>
+static hipError_t launch_pairs_tile(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const float *scale,
+                                    int ldsc, double prefactor, float2 *f, std::conditional_t<ARG, EnergyArg, int> e,
+                                    hipStream_t s) {
+  constexpr int CY = 65535 * PP_CB;                    // unoccupied bands per launch
+  for (int cb = 0; cb < nc; cb += CY) {
+    const dim3 grid(((nr + P - 1) / P) * ((nv + VB - 1) / VB), (std::min(CY, nc - cb) + PP_CB - 1) / PP_CB);
+    hipLaunchKernelGGL(HIP_KERNEL_NAME(pair_products_kernel<P, VB, ARG>), grid, dim3(PP_THREADS), 0, s, psi_v, nv, psi_c,
+                       nc, nr, cb, scale, ldsc, prefactor, f, e);
+  }
+  return hipGetLastError();
+}
 
 template <bool ARG>
 static hipError_t launch_pairs(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const float *scale,
                                int ldsc, double prefactor, float2 *f, std::conditional_t<ARG, EnergyArg, int> e,
                                hipStream_t s) {
-  constexpr int CY = 65535 * PP_CB;                    // unoccupied bands per launch
-  for (int cb = 0; cb < nc; cb += CY) {
-    const dim3 grid(((nr + PP_P - 1) / PP_P) * ((nv + PP_VB - 1) / PP_VB), (std::min(CY, nc - cb) + PP_CB - 1) / PP_CB);
-    hipLaunchKernelGGL(HIP_KERNEL_NAME(pair_products_kernel<ARG>), grid, dim3(PP_THREADS), 0, s, psi_v, nv, psi_c, nc,
-                       nr, cb, scale, ldsc, prefactor, f, e);
+  const int blocks = (int)((nv + 7ll) / 8);
+  switch ((nv + blocks - 1) / blocks) {
+    case 1: return launch_pairs_tile<512, 1, ARG>(psi_v, nv, psi_c, nc, nr, scale, ldsc, prefactor, f, e, s);
+    case 3: return launch_pairs_tile<256, 3, ARG>(psi_v, nv, psi_c, nc, nr, scale, ldsc, prefactor, f, e, s);
+    case 2:
+    case 4: return launch_pairs_tile<256, 4, ARG>(psi_v, nv, psi_c, nc, nr, scale, ldsc, prefactor, f, e, s);
+    case 5: return launch_pairs_tile<512, 5, ARG>(psi_v, nv, psi_c, nc, nr, scale, ldsc, prefactor, f, e, s);
+    case 6: return launch_pairs_tile<512, 6, ARG>(psi_v, nv, psi_c, nc, nr, scale, ldsc, prefactor, f, e, s);
+    case 7: return launch_pairs_tile<512, 7, ARG>(psi_v, nv, psi_c, nc, nr, scale, ldsc, prefactor, f, e, s);
+    default: return launch_pairs_tile<512, 8, ARG>(psi_v, nv, psi_c, nc, nr, scale, ldsc, prefactor, f, e, s);
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_pair_products(const float2 *psi_v, int nv, const float2 *psi_c, int nc, int nr, const float *scale,

@@ -36,3 +36,12 @@ def test_rows_at_every_line_offset(gw, nr, nv, nc, offset):
     assert np.max(np.abs(out.cpu().numpy() - ref)) < 2e-7 * np.max(np.abs(ref))
     rest = torch.cat([buf[:offset], buf[offset + nv * nc * nr:]])
     assert bool((rest == 7.0).all())                       # nothing written outside the output
+
+
+# Each split of the occupied bands over workgroups (one band, up to four, five to eight, two blocks of five to eight of
+# which the last is short or full), at the edges of its segments and with the scales from the table (490 bands) and
+# from the launch's arguments.
+@pytest.mark.parametrize("nv", [1, 2, 3, 4, 5, 6, 7, 8, 9, 11, 12, 13, 17])
+@pytest.mark.parametrize("nr,nc,offset", [(1, 3, 1), (255, 5, 0), (257, 490, 7), (513, 6, 15), (1040, 4, 0)])
+def test_splits_of_the_occupied_bands(gw, nr, nv, nc, offset):
+    test_rows_at_every_line_offset(gw, nr, nv, nc, offset)
