@@ -135,7 +135,13 @@ int ws_get(gw_ctx *ctx, int slot, size_t bytes, void **out, hipStream_t s) {
 void *ws_try(gw_ctx *ctx, int slot, size_t bytes, hipStream_t s) {
   void *p = nullptr;
   if (stream_capturing(s)) return nullptr;
+  if ((int)ctx->slots.size() <= slot) ctx->slots.resize(slot + 1);
+  const gw_ctx::Slot &sl = ctx->slots[slot];
+  // what did not fit on the device once is not asked for on every call
+  if (sl.refused && bytes >= sl.refused && bytes > sl.bytes) return nullptr;
+  const bool under_cap = !ctx->cap || ctx->held - sl.bytes + (bytes + 255) / 256 * 256 <= ctx->cap;
   if (ws_alloc(ctx, slot, bytes, &p, s) == GW_OK) return p;
+  if (under_cap) ctx->slots[slot].refused = bytes;
   ctx->err.clear();
   return nullptr;
 }

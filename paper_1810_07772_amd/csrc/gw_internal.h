@@ -23,7 +23,11 @@ struct gw_ctx {
   size_t cap = 0;             // workspace cap in bytes (0: none)
   size_t held = 0;            // bytes currently allocated in slots
   std::string err;            // text of the last failure
-  struct Slot { void *ptr = nullptr; size_t bytes = 0; };
+  struct Slot {
+    void *ptr = nullptr;
+    size_t bytes = 0;
+    size_t refused = 0;       // an optional buffer of this size did not fit on the device (0: none)
+  };
   std::vector<Slot> slots;    // grow-only named workspace buffers
   int *pivot_host = nullptr;  // pinned host word for the Cholesky pivot flag
   double *result_host = nullptr;       // pinned host word for an iteration's residual (same allocation)

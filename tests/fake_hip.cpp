@@ -27,7 +27,7 @@ std::vector<Copy> recorded;
 std::vector<Launch> launches;
 size_t limit = 0;                       // requests above it fail (0: none do)
 float cut_ms = 1.0f;                    // time between two events after a launch that adds parts of cut tiles
-int last = OK, violations = 0, copies = 0;
+int last = OK, violations = 0, copies = 0, mallocs = 0;
 struct Config { dim3 grid, block; size_t shared; stream_t s; } config;
 
 bool any_capture() {
@@ -57,6 +57,7 @@ void fake_replay() {
   for (const Copy &c : recorded) memcpy(c.dst, c.src, c.bytes);
 }
 int fake_copies() { return copies; }
+int fake_mallocs() { return mallocs; }          // requests, those that failed among them
 int fake_launches() { return (int)launches.size(); }
 const char *fake_launch_name(int i) { return launches[(size_t)i].name.c_str(); }
 unsigned fake_launch_grid(int i) { return launches[(size_t)i].grid.x; }
@@ -100,6 +101,7 @@ int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **, size_t, strea
   return OK;
 }
 int hipMalloc(void **p, size_t bytes) {
+  ++mallocs;
   if (any_capture()) return in_capture();
   if (limit && bytes > limit) return fail(OUT_OF_MEMORY);
   std::vector<void *> &f = freed[bytes];

@@ -291,3 +291,20 @@ for nv, nc, n in ((8, 480, 1), (8, 481, 0), (100, 900, 0)):
                                    ptr(buf(8)), S) == 0
     assert len(launches("energies_kernel")) == n and fake.fake_copies() == 2 - 2 * n
 """)
+
+
+def test_an_optional_buffer_that_did_not_fit_is_not_asked_for_again(run):
+    """The device is asked once for a buffer that calls can do without; a smaller one may still fit."""
+    run(OPTIONAL + """
+h = ctx()
+assert update(h, L._opts("fp32", tile=4)) == 0
+fake.fake_limit(3 << 20)
+for _ in range(3):
+    before = fake.fake_mallocs()
+    assert update(h) == 0 and train(h) == 0 and not launches("part_sum")
+first = fake.fake_mallocs()
+assert update(h) == 0 and train(h) == 0 and fake.fake_mallocs() == first
+fake.fake_clear()
+assert train(h, 100) == 0 and backward() == [7]             # all the parts that 100 rows have
+assert train(h, 1) == 0 and fake.fake_mallocs() == first + 1
+""")
