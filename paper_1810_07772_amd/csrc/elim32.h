@@ -54,7 +54,7 @@ __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, J..
 // row of the pivot, divided by it, goes through LDS (w[j], a row of its own for every step, so one
 // barrier per step orders the writes before the reads), written by the wave that holds it and read as two
 // words of 16 bytes per lane by the waves that still have rows below it.  inv(d) stands for 1 / d; pivots
-// that are not positive are the caller's to find.  About 440 cycles per step.
+// that are not positive are the caller's to find.  About 450 cycles per step.
 //
 // Out: w[j][m] = row_j(m) inv(d_j), A's entries right of the diagonal, X's on it (X_jj = 1) and left of it; dv[j] = d_j;
 // for j < n, complete after the caller's next barrier; row = row_c(m) and row_c(16 + m) of the lane's own row c < n, as

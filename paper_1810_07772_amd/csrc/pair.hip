@@ -13,8 +13,8 @@
 // The occupied bands are split evenly over as few blocks of at most 8 as hold them, and a block loads as many rows as
 // it has: with blocks of 8 throughout, 9 x 500 bands on 24^3 took 112 us (kernel alone; blocks of 5 87, a kernel that
 // loops over the occupied bands 100), 12 x 200 on 27^3 74 (6: 70), 10 x 490 on 18^3 54 (5: 45).  With four bands or
-// fewer the segment is 256 points by 4 x 4 or 3 x 4 (2 x 600 bands on 20^3 23.4 -> 18.7 us, 3 x 500 on 24^3 37.5 -> 34.1), with one
-// 512 by 1 x 4 (600 bands on 20^3 17.8 -> 12.2).
+// fewer the segment is 256 points by 4 x 4 or 3 x 4 (2 x 600 bands on 20^3 23.4 -> 18.7 us, 3 x 500 on 24^3 37.5 ->
+// 34.1), with one 512 by 1 x 4 (600 bands on 20^3 17.8 -> 12.2).
 #include <algorithm>
 #include <type_traits>
 

@@ -102,7 +102,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // 64 rows per workgroup, 16 complex k per stage, so a workgroup has 16 KB of A in flight in registers while the
 // FP64 MFMAs of the stage before run (k' = (k, re/im) as in zgemm_kernel: Re C += [Re A, Im A] . [Re B; -Im B],
 // Im C += [Re A, Im A] . [Im B; Re B]); wave w owns rows 16 w .. +15 and all 32 columns.  Bound by memory and the
-// matrix cores alike (16 bytes and 256 flop per entry of A).  3071 x 3071 by 24 columns: 103 us in the 64 x 64 tiles
+// matrix cores alike (16 bytes and 256 flop per entry of A).  3071 x 3071 by 32 columns: 103 us in the 64 x 64 tiles
 // of zgemm_kernel, half of whose columns are padding here, 59 us so with one stage of loads in flight, 50 us with two
 // and no branch between a load and its use.
 constexpr int TPM = 64, TPK = 16;
@@ -223,9 +223,10 @@ size_t thin_part_elems(int M, int N, int K) { return (size_t)thin_splits(M, K) *
 // time in LDS, all their loads in flight together; each of eight waves forms the real or imaginary part of one
 // 16 x 16 tile on the FP64 MFMA, with k' = (row, re/im): Re = [Re X; Im X]^T [Re Y; Im Y],
 // Im = [Re X; Im X]^T [Im Y; -Re Y].  Bound by latency, and so is its consumer, one workgroup that reads every
-// partial matrix: the split is the one that keeps their sum shortest.  3071 rows, b = 24: 64 blocks of
-// 48 rows on the vector units took 8.6 us, their sum 12 us of the consumer's; 32 of 96 rows 6.6 us and 7 (48 blocks
-// 5.5 and 10, 24 blocks 8.7 and 6).
+// partial matrix: the split is the one that keeps their sum shortest.  3071 rows, b = 32: 64 blocks of
+// 48 rows on the vector units took 8.6 us, their sum 12 us of the consumer's; 32 of 96 rows 6.5 us and 7 (48 blocks
+// 5.5 and 10, 24 blocks 8.7 and 6).  From 3073 rows on every block makes a second pass: 7.9 us there and 8.9 at
+// 4067; more blocks of one pass each would lengthen the consumer's sum by as much.
 constexpr int GRAM_ROWS = 96;
 constexpr int GRAM_BLOCKS = 32;
 __global__ __launch_bounds__(512) void block_gram_kernel(const double2 *__restrict__ x, const double2 *__restrict__ y,
@@ -529,7 +530,7 @@ __global__ __launch_bounds__(512) void herm_jacobi_kernel(const double2 *__restr
 // problem close to diagonal, which saves its Jacobi sweeps.  A direction whose squared length falls below
 // 1e-14 of its column's once the earlier columns are projected out is dropped (u gets a zero column), as is a zero
 // column.  One workgroup; the pivots are its time.
-// (b = 24 from 64 partial matrices: 28.2 us with a column per lane, one pivot's column and row through LDS; 24.4 us in
+// (b = 32 from 64 partial matrices: 28.2 us with a column per lane, one pivot's column and row through LDS; 24.4 us in
 // this form, 12 us of it the sum, and 16.7 us from 32.)
 __global__ __launch_bounds__(512) void block_chol_kernel(const double2 *__restrict__ gpart, int nblk, int b,
                                                          double2 *__restrict__ u) {
